@@ -29,7 +29,6 @@ struct attn_batch {
     int ma, mb, target, tile;
   };
   std::vector<Tune> tuned;
-  int default_target = (int)kMvTarget;   // the single-handle split
 
   struct Merged {
     std::vector<SWTask> sw_tasks;
@@ -118,7 +117,7 @@ T* bupload(attn_batch* b, const std::vector<T>& v) {
 int target_for(const attn_batch* b, int ma, int mb) {
   for (auto& t : b->tuned)
     if (t.ma == ma && t.mb == mb) return t.target;
-  return b->default_target;
+  return (int)mv_target(ma);   // the single-handle split
 }
 
 int tile_for(const attn_batch* b, int ma, int mb) {
@@ -211,8 +210,8 @@ void add_sandwich(attn_batch* b, attn_handle* h, int n, const void* x, attn_batc
         for (int s = 0; s < ns; s += 2) m.sw_wus2.push_back(make_int4(ti, s, 0, std::min(2, ns - s)));
       } else if (mf) {
         for (int s = 0; s < ns; s++)
-          for (int st = 0; st < ma / 16; st += 4) m.sw_wus.push_back(make_int4(ti, s, st, mb / 16));
-        m.sw_lds = std::max(m.sw_lds, (size_t)ma * (mb + 2) * esz);
+          for (int st = 0; st < sw_strips(ma); st += 4) m.sw_wus.push_back(make_int4(ti, s, st, sw_strips(mb)));
+        m.sw_lds = std::max(m.sw_lds, sw_mfma_lds(ma, mb, esz));
       } else {
         for (int s = 0; s < ns; s++)
           for (int e = 0; e < ma * mb; e += 256) m.sw_wus.push_back(make_int4(ti, s, e, 0));
@@ -239,7 +238,7 @@ void add_chains(attn_batch* b, attn_handle* h, int n, const void* x, attn_batch:
       if (g.mfma && !mf) throw BatchFail{ATTN_ERR_UNSUPPORTED, "batched form: legs above 64"};
       for (MPTask t : g.tasks) {
         t.job0 += j0;
-        t.pad = mf ? g.mj / 16 : 0;
+        t.pad = mf ? sw_strips(g.mj) : 0;
         m.mp_tasks[k].push_back(t);
       }
       for (MPJob jb : g.jobs) {
@@ -247,7 +246,7 @@ void add_chains(attn_batch* b, attn_handle* h, int n, const void* x, attn_batch:
         m.mp_jobs[k].push_back(jb);
       }
       for (int2 wu : g.wus) m.mp_wus[k].push_back(make_int2(wu.x + t0, wu.y));
-      if (mf) m.mp_lds[k] = std::max(m.mp_lds[k], (size_t)g.mj * 66 * esz);
+      if (mf) m.mp_lds[k] = std::max(m.mp_lds[k], mode_lds(g.mj, ModeTile{1, 1}, esz));
     }
   const uintptr_t c0 = (uintptr_t)h->d_chain, c1 = c0 + (uintptr_t)h->chain_cap * 8;
   for (const RDSrc& r : D.srcs)
@@ -583,14 +582,14 @@ void autotune(attn_batch* b) {
       }
     }
   }
-  const int cands[4] = {64, 256, (int)kMvTarget, 4096};   // the single-handle split among them
-  hipEvent_t e0, e1;
+    hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
   const int nsteps = (int)b->steps.size();
   for (auto& sh : shapes) {
+    const int cands[4] = {64, 256, (int)mv_target(sh.first), 4096};   // the single-handle split among them
     float best = 1e30f;
-    int best_c = b->default_target, best_tile = 1;
+    int best_c = cands[2], best_tile = 1;
     const int ntile = w2_allowed(b, sh.first, sh.second) ? 2 : 1;
     for (int tile = 1; tile <= ntile; tile++)
       for (int c : cands) {

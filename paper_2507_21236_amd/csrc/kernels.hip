@@ -26,14 +26,14 @@ __device__ __forceinline__ void fail_status(KrylovState* st, int v) {
 
 // ============================================================================ mode product
 // (device bodies: mode_body.hpp)
-template <typename T, int NI, int QS>
+template <typename T, int NI, int QS, int FT>
 __global__ __launch_bounds__(256) void k_mode(const MPTask* __restrict__ tasks,
                                               const MPJob* __restrict__ jobs,
                                               const int2* __restrict__ wus,
                                               const T* __restrict__ xbase) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int2 wu = wus[blockIdx.x];
-  mode_mfma<T, NI, QS>(tasks[wu.x], jobs, wu, xbase, smem_raw);
+  mode_mfma<T, NI, QS, FT>(tasks[wu.x], jobs, wu, xbase, smem_raw);
 }
 
 // Mode product for contracted leg j = 0 or 1 with 16 | d2: a 16-wide tile of
@@ -159,8 +159,8 @@ __global__ __launch_bounds__(256) void k_copy(double* __restrict__ dst, const do
 // partial[j][j'] (column-major) = sum_{f in [f0, f1)} X[f][j] Z[f][j'].
 template <int NI>
 __global__ __launch_bounds__(256) void k_gram(const GRTask* __restrict__ tasks) {
-  constexpr int mj = 16 * NI;
-  constexpr int ld = mj + 2;
+  constexpr int mjp = 16 * NI;
+  constexpr int ld = mjp + 2;
   constexpr int NT = NI * NI;
   constexpr int MAXT = (NT + 3) / 4;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -168,6 +168,7 @@ __global__ __launch_bounds__(256) void k_gram(const GRTask* __restrict__ tasks) 
   double* lz = lx + 64 * ld;
   const GRTask& t = tasks[blockIdx.x];
   const int j = t.j, d0 = t.d0, d1 = t.d1, d2 = t.d2;
+  const int mj = j == 0 ? d0 : (j == 1 ? d1 : d2);   // <= 16 NI: tiles past the end are staged as zeros
   const double* X = (const double*)t.X;
   const double* Z = (const double*)t.Z;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -178,18 +179,20 @@ __global__ __launch_bounds__(256) void k_gram(const GRTask* __restrict__ tasks) 
   for (int64_t fb = t.f0; fb < t.f1; fb += 64) {
     __syncthreads();
     if (j == 2) {
-      for (int e = threadIdx.x; e < 64 * mj; e += 256) {
-        const int fl = e / mj, i = e - fl * mj;
-        const int64_t ad = mode_addr(j, d0, d1, d2, i, fb + fl);
-        lx[fl * ld + i] = X[ad];
-        lz[fl * ld + i] = Z[ad];
+      for (int e = threadIdx.x; e < 64 * mjp; e += 256) {
+        const int fl = e / mjp, i = e - fl * mjp;
+        const bool in = i < mj && fb + fl < t.f1;
+        const int64_t ad = in ? mode_addr(j, d0, d1, d2, i, fb + fl) : 0;
+        lx[fl * ld + i] = in ? X[ad] : 0.0;
+        lz[fl * ld + i] = in ? Z[ad] : 0.0;
       }
     } else {
-      for (int e = threadIdx.x; e < 64 * mj; e += 256) {
+      for (int e = threadIdx.x; e < 64 * mjp; e += 256) {
         const int i = e >> 6, fl = e & 63;
-        const int64_t ad = mode_addr(j, d0, d1, d2, i, fb + fl);
-        lx[fl * ld + i] = X[ad];
-        lz[fl * ld + i] = Z[ad];
+        const bool in = i < mj && fb + fl < t.f1;
+        const int64_t ad = in ? mode_addr(j, d0, d1, d2, i, fb + fl) : 0;
+        lx[fl * ld + i] = in ? X[ad] : 0.0;
+        lz[fl * ld + i] = in ? Z[ad] : 0.0;
       }
     }
     __syncthreads();
@@ -213,7 +216,10 @@ __global__ __launch_bounds__(256) void k_gram(const GRTask* __restrict__ tasks) 
     if (tt < NT) {
       const int tj = tt / NI, tk = tt - tj * NI;
 #pragma unroll
-      for (int i = 0; i < 4; i++) P[(int64_t)(16 * tk + l16) * mj + 16 * tj + drow<double>(l4, i)] = acc[q][i];
+      for (int i = 0; i < 4; i++) {
+        const int r = 16 * tj + drow<double>(l4, i), c = 16 * tk + l16;
+        if (r < mj && c < mj) P[(int64_t)c * mj + r] = acc[q][i];
+      }
     }
   }
 }
@@ -2103,7 +2109,7 @@ __device__ __forceinline__ void trinv_blocks(const double* A, double* X, int lan
 }
 
 template <int N>
-__global__ __launch_bounds__(64) void k_chol_inv_blk(const double* __restrict__ G, double* __restrict__ R,
+__global__ __launch_bounds__(64) void k_chol_inv_blk(const double* __restrict__ G, int n, double* __restrict__ R,
                                                      double* __restrict__ RinvRow, int shift_mode, int64_t rows,
                                                      KrylovState* __restrict__ st) {
   static_assert(N % 16 == 0 && N <= 64, "blocks of 16, one lane per row");
@@ -2111,19 +2117,19 @@ __global__ __launch_bounds__(64) void k_chol_inv_blk(const double* __restrict__ 
   __shared__ double A[64 * kCholLd];   // A(i, j) at j * kCholLd + i
   __shared__ double X[64 * kCholLd];
   const int lane = threadIdx.x;
-  const bool own = lane < N;
-  const double tr = wave_sum(own ? G[(int64_t)lane * N + lane] : 0.0);
+  const bool own = lane < n;   // n <= N; the matrix is continued by the identity
+  const double tr = wave_sum(own ? G[(int64_t)lane * n + lane] : 0.0);
   const double shift =
-      shift_mode ? 11.0 * ((double)rows * N + (double)N * (N + 1)) * 1.1102230246251565e-16 * tr : 0.0;
+      shift_mode ? 11.0 * ((double)rows * n + (double)n * (n + 1)) * 1.1102230246251565e-16 * tr : 0.0;
   // A = G + shift I, column by column (coalesced); only the lower triangle
   // takes part in the factorisation: an entry above the diagonal only ever
   // meets a zero multiplier or is overwritten
   {
     double g[N];   // all loads in flight at once
 #pragma unroll
-    for (int j = 0; j < N; j++) g[j] = own ? G[(int64_t)j * N + lane] : 0.0;
+    for (int j = 0; j < N; j++) g[j] = own && j < n ? G[(int64_t)j * n + lane] : 0.0;
 #pragma unroll
-    for (int j = 0; j < N; j++) A[j * kCholLd + lane] = g[j] + (lane == j ? shift : 0.0);
+    for (int j = 0; j < N; j++) A[j * kCholLd + lane] = g[j] + (lane == j ? (j < n ? shift : 1.0) : 0.0);
   }
   wave_sync();
   int bad = 0;
@@ -2157,11 +2163,13 @@ __global__ __launch_bounds__(64) void k_chol_inv_blk(const double* __restrict__ 
 #pragma unroll
     for (int j = 0; j < N; j++) r[j] = (j >> 4) >= (lane >> 4) ? A[lane * kCholLd + j] : 0.0;
 #pragma unroll
-    for (int j = 0; j < N; j++) R[(int64_t)j * N + lane] = r[j];
+    for (int j = 0; j < N; j++)
+      if (j < n) R[(int64_t)j * n + lane] = r[j];
 #pragma unroll
     for (int j = 0; j < N; j++) r[j] = (j >> 4) <= (lane >> 4) ? X[j * kCholLd + lane] : 0.0;
 #pragma unroll
-    for (int j = 0; j < N; j++) RinvRow[(int64_t)j * N + lane] = r[j];
+    for (int j = 0; j < N; j++)
+      if (j < n) RinvRow[(int64_t)j * n + lane] = r[j];
   }
   if (lane == 0 && bad && st) fail_status(st, 2);
 }
@@ -2339,14 +2347,11 @@ __global__ __launch_bounds__(64) void k_small_matmul(const double* __restrict__ 
 static inline unsigned grid1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 template <typename T, int NI>
-static hipError_t mode_launch(const MPTask* tasks, const MPJob* jobs, const int2* wus, int nwu,
+static hipError_t mode_launch(int mj, const MPTask* tasks, const MPJob* jobs, const int2* wus, int nwu,
                               const void* xbase, hipStream_t s) {
-  // m_j = 32 or 64: the output rows of a work unit are spread over 2 or 4
-  // workgroups (each stages a quarter or half of the free block)
-  constexpr int QS = mode_qs(NI);
-  const size_t lds = (size_t)16 * NI * 66 * sizeof(T);
-  hipLaunchKernelGGL((k_mode<T, NI, QS>), dim3(nwu, QS), dim3(256), lds, s, tasks, jobs, wus,
-                     (const T*)xbase);
+  constexpr ModeTile m = mode_tile(NI);
+  hipLaunchKernelGGL((k_mode<T, NI, m.qs, m.ft>), dim3(nwu, 64 / mode_width(m)), dim3(256), mode_lds(mj, m, sizeof(T)),
+                     s, tasks, jobs, wus, (const T*)xbase);
   return hipGetLastError();
 }
 
@@ -2379,15 +2384,15 @@ hipError_t launch_mode(int dtype, int mj, bool mfma, const MPTask* tasks, const 
     return hipGetLastError();
   }
 #define MODE_CASES(T)                                                        \
-  switch (mj / 16) {                                                         \
-    case 1: return mode_launch<T, 1>(tasks, jobs, wus, nwu, xbase, s);       \
-    case 2: return mode_launch<T, 2>(tasks, jobs, wus, nwu, xbase, s);       \
-    case 3: return mode_launch<T, 3>(tasks, jobs, wus, nwu, xbase, s);       \
-    case 4: return mode_launch<T, 4>(tasks, jobs, wus, nwu, xbase, s);       \
-    case 5: return mode_launch<T, 5>(tasks, jobs, wus, nwu, xbase, s);       \
-    case 6: return mode_launch<T, 6>(tasks, jobs, wus, nwu, xbase, s);       \
-    case 7: return mode_launch<T, 7>(tasks, jobs, wus, nwu, xbase, s);       \
-    case 8: return mode_launch<T, 8>(tasks, jobs, wus, nwu, xbase, s);       \
+  switch (sw_strips(mj)) {                                                         \
+    case 1: return mode_launch<T, 1>(mj, tasks, jobs, wus, nwu, xbase, s);       \
+    case 2: return mode_launch<T, 2>(mj, tasks, jobs, wus, nwu, xbase, s);       \
+    case 3: return mode_launch<T, 3>(mj, tasks, jobs, wus, nwu, xbase, s);       \
+    case 4: return mode_launch<T, 4>(mj, tasks, jobs, wus, nwu, xbase, s);       \
+    case 5: return mode_launch<T, 5>(mj, tasks, jobs, wus, nwu, xbase, s);       \
+    case 6: return mode_launch<T, 6>(mj, tasks, jobs, wus, nwu, xbase, s);       \
+    case 7: return mode_launch<T, 7>(mj, tasks, jobs, wus, nwu, xbase, s);       \
+    case 8: return mode_launch<T, 8>(mj, tasks, jobs, wus, nwu, xbase, s);       \
   }
   if (dtype == 0) { MODE_CASES(double) }
   else { MODE_CASES(float) }
@@ -2417,7 +2422,7 @@ hipError_t launch_gram(int mj, bool mfma, const GRTask* tasks, int ntask, hipStr
     hipLaunchKernelGGL(k_gram_gen, dim3(grid1((int64_t)mj * mj), ntask), dim3(256), 0, s, tasks, mj);
     return hipGetLastError();
   }
-  switch (mj / 16) {
+  switch (sw_strips(mj)) {
     case 1: return gram_launch<1>(tasks, ntask, s);
     case 2: return gram_launch<2>(tasks, ntask, s);
     case 3: return gram_launch<3>(tasks, ntask, s);
@@ -2578,11 +2583,11 @@ hipError_t launch_tiny(const TJob* jobs, int nj, int minM, int maxM, int kreq, h
 
 hipError_t launch_chol_inv(const double* G, int n, double* R, double* RinvRow, int shift_mode,
                            int64_t rows, KrylovState* st, double* ws, hipStream_t s) {
-  switch (n) {
-    case 16: hipLaunchKernelGGL(k_chol_inv_blk<16>, dim3(1), dim3(64), 0, s, G, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
-    case 32: hipLaunchKernelGGL(k_chol_inv_blk<32>, dim3(1), dim3(64), 0, s, G, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
-    case 48: hipLaunchKernelGGL(k_chol_inv_blk<48>, dim3(1), dim3(64), 0, s, G, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
-    case 64: hipLaunchKernelGGL(k_chol_inv_blk<64>, dim3(1), dim3(64), 0, s, G, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
+  switch (sw_strips(n)) {
+    case 1: hipLaunchKernelGGL(k_chol_inv_blk<16>, dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
+    case 2: hipLaunchKernelGGL(k_chol_inv_blk<32>, dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
+    case 3: hipLaunchKernelGGL(k_chol_inv_blk<48>, dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
+    case 4: hipLaunchKernelGGL(k_chol_inv_blk<64>, dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
     default: break;
   }
   if (n <= 128) {
@@ -2664,14 +2669,23 @@ hipError_t prepare_kernel_attributes() {
   if (hipError_t e = prepare_sandwich_attributes()) return e;
   const void* fns[] = {
       (const void*)k_batch_mode<double>, (const void*)k_batch_mode<float>,
-      (const void*)k_mode<double, 1, mode_qs(1)>, (const void*)k_mode<double, 2, mode_qs(2)>,
-      (const void*)k_mode<double, 3, mode_qs(3)>, (const void*)k_mode<double, 4, mode_qs(4)>,
-      (const void*)k_mode<double, 5, mode_qs(5)>, (const void*)k_mode<double, 6, mode_qs(6)>,
-      (const void*)k_mode<double, 7, mode_qs(7)>, (const void*)k_mode<double, 8, mode_qs(8)>,
-      (const void*)k_mode<float, 1, mode_qs(1)>, (const void*)k_mode<float, 2, mode_qs(2)>,
-      (const void*)k_mode<float, 3, mode_qs(3)>, (const void*)k_mode<float, 4, mode_qs(4)>,
-      (const void*)k_mode<float, 5, mode_qs(5)>, (const void*)k_mode<float, 6, mode_qs(6)>,
-      (const void*)k_mode<float, 7, mode_qs(7)>, (const void*)k_mode<float, 8, mode_qs(8)>, (const void*)k_mlp_grad};
+      (const void*)k_mode<double, 1, mode_tile(1).qs, mode_tile(1).ft>,
+      (const void*)k_mode<double, 2, mode_tile(2).qs, mode_tile(2).ft>,
+      (const void*)k_mode<double, 3, mode_tile(3).qs, mode_tile(3).ft>,
+      (const void*)k_mode<double, 4, mode_tile(4).qs, mode_tile(4).ft>,
+      (const void*)k_mode<double, 5, mode_tile(5).qs, mode_tile(5).ft>,
+      (const void*)k_mode<double, 6, mode_tile(6).qs, mode_tile(6).ft>,
+      (const void*)k_mode<double, 7, mode_tile(7).qs, mode_tile(7).ft>,
+      (const void*)k_mode<double, 8, mode_tile(8).qs, mode_tile(8).ft>,
+      (const void*)k_mode<float, 1, mode_tile(1).qs, mode_tile(1).ft>,
+      (const void*)k_mode<float, 2, mode_tile(2).qs, mode_tile(2).ft>,
+      (const void*)k_mode<float, 3, mode_tile(3).qs, mode_tile(3).ft>,
+      (const void*)k_mode<float, 4, mode_tile(4).qs, mode_tile(4).ft>,
+      (const void*)k_mode<float, 5, mode_tile(5).qs, mode_tile(5).ft>,
+      (const void*)k_mode<float, 6, mode_tile(6).qs, mode_tile(6).ft>,
+      (const void*)k_mode<float, 7, mode_tile(7).qs, mode_tile(7).ft>,
+      (const void*)k_mode<float, 8, mode_tile(8).qs, mode_tile(8).ft>,
+      (const void*)k_mlp_grad};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;

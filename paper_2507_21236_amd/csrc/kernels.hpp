@@ -13,7 +13,8 @@ namespace attn {
 // ---------------------------------------------------------------- sandwich
 // Y_s (+)= sum_items coef * A X_s B^T over slices s of a spectator leg:
 // X_s[a][b] at x + s*xs_slice + a*xs_row + b (same for y).  A acts on the
-// a leg (ma x ma), B on the b leg (mb x mb).
+// a leg (ma x ma), B on the b leg (mb x mb); a null pointer stands for the
+// identity.  The items of a list that have no B come first.
 struct SWItem {
   const void* A;
   const void* B;
@@ -44,6 +45,21 @@ struct MPJob {
   const void* in;
   double coef;
 };
+
+// Tile of a mode product's workgroup (legs of 16 NI): qs groups of row tiles by
+// 4 / qs groups of ft tiles of free columns.  Up to legs of 64 many small
+// workgroups, above column pairs (each A element then serves two products).
+struct ModeTile {
+  int qs, ft;
+};
+constexpr ModeTile mode_tile(int NI) {
+  return NI == 8 ? ModeTile{4, 2} : NI == 4 ? ModeTile{4, 1} : (NI == 2 || NI == 6) ? ModeTile{2, 1} : ModeTile{1, 1};
+}
+constexpr int mode_width(ModeTile m) { return 16 * m.ft * (4 / m.qs); }
+// LDS bytes of the staged tile (whole K steps of rows, two elements of padding)
+constexpr size_t mode_lds(int mj, ModeTile m, size_t esz) {
+  return (size_t)((mj + 3) / 4 * 4) * (mode_width(m) + 2) * esz;
+}
 
 struct MPTask {
   void* out;
@@ -96,6 +112,21 @@ constexpr size_t gen_slice_lds(int ma, int mb, size_t esz) {
   return (ma * mb <= 256 && (size_t)(2 * ma * mb + ma * ma + mb * mb) * esz <= 32768)
              ? (size_t)(2 * ma * mb + ma * ma + mb * mb) * esz
              : 0;
+}
+
+// 16-wide tiles of a leg, and the rule for the matrix-core form of the
+// sandwich: legs of whole tiles up to 128, and every other pair up to 128 that
+// the slice form above does not take (a slice of a few hundred entries spends
+// its time on latency either way; above that one thread per output entry
+// measured 0.09 TFLOP/s at legs of 50, the ragged tiles 32).
+constexpr int sw_strips(int m) { return (m + 15) / 16; }
+constexpr bool sw_on_mfma(int ma, int mb) {
+  return ma <= 128 && mb <= 128 && ((ma % 16 == 0 && mb % 16 == 0) || gen_slice_lds(ma, mb, 8) == 0);
+}
+// LDS bytes of its staged slice: whole K steps of rows, whole tiles of columns
+// (rows padded by two elements)
+constexpr size_t sw_mfma_lds(int ma, int mb, size_t esz) {
+  return (size_t)((ma + 3) / 4 * 4) * (16 * sw_strips(mb) + 2) * esz;
 }
 
 struct RDSrc {

@@ -53,6 +53,23 @@ __device__ __forceinline__ T gload(const T* p) {
   return *(const __attribute__((address_space(1))) T*)p;
 }
 
+// Bounds-checked loads of an operator block: a buffer resource over its n
+// elements (wave-uniform, scalar registers), the lane's byte offset and a
+// uniform one.  Elements past the end read as zero, so the K steps and tiles
+// of a leg that is not a multiple of 16 need no guards, and the addresses
+// cost no vector instructions.
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t block_rsrc(const T* p, int n) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, n * (int)sizeof(T), 0x00027000);
+}
+template <typename T>
+__device__ __forceinline__ T bload(__amdgpu_buffer_rsrc_t r, int lane_bytes, int uniform_bytes) {
+  if constexpr (sizeof(T) == 8)
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, lane_bytes, uniform_bytes, 0));
+  else
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane_bytes, uniform_bytes, 0));
+}
+
 // The rows of Y_s owned by this wave for items [i0, i1), written to y.
 // Column order of a 16-wide tile as the products see it: tile row m of both
 // MFMA stages stands for column colperm(m).  FP64: the accumulator rows of a

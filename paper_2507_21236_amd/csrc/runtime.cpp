@@ -79,7 +79,7 @@ void slice_geom(int spect, const int* dm, int& ma, int& mb, int& ns, int64_t& sl
   else { ma = dm[0]; mb = dm[1]; ns = dm[2]; sl = (int64_t)dm[0] * dm[1]; row = dm[1]; }
 }
 
-bool sw_mfma(int ma, int mb) { return ma % 16 == 0 && mb % 16 == 0 && ma <= 128 && mb <= 128; }
+bool sw_mfma(int ma, int mb) { return sw_on_mfma(ma, mb); }
 
 void add_sw_task(SWGroup& g, SWTask t, int ns) {
   g.ma = t.ma;
@@ -95,8 +95,7 @@ void add_sw_task(SWGroup& g, SWTask t, int ns) {
   for (int i = i0; i < i1; i++)
     g.flops += 2.0 * M * ((g.items[i].A ? t.ma : 0) + (g.items[i].B ? t.mb : 0));
   if (sw_mfma(t.ma, t.mb)) {
-    for (int s = 0; s < ns; s++)
-      for (int st = 0; st < t.ma / 16; st += 4) g.wus.push_back(make_int4(ti, s, st, 0));
+    for (int s = 0; s < ns; s++) g.wus.push_back(make_int4(ti, s, 0, 0));   // a wavefront per strip
   } else {
     for (int s = 0; s < ns; s++)
       for (int e = 0; e < t.ma * t.mb; e += 256) g.wus.push_back(make_int4(ti, s, e, 0));
@@ -127,7 +126,7 @@ void add_mp_task(MPGroup& g, MPTask t) {
   const int mj = t.j == 0 ? t.d0 : (t.j == 1 ? t.d1 : t.d2);
   const int64_t M = (int64_t)t.d0 * t.d1 * t.d2;
   if (g.mfma) {
-    for (int64_t f = 0; f < M / mj / 64; f++) g.wus.push_back(make_int2(ti, (int)f));
+    for (int64_t f = 0; f < mode_blocks(mj, M); f++) g.wus.push_back(make_int2(ti, (int)f));
   } else {
     for (int64_t e = 0; e < M; e += 256) g.wus.push_back(make_int2(ti, (int)e));
   }
@@ -189,7 +188,8 @@ bool mode_nt_ok(const std::vector<MPTask>& ts, bool mfma) {
   if (!mfma || ts.empty()) return false;
   for (const MPTask& t : ts) {
     const int mj = t.j == 0 ? t.d0 : (t.j == 1 ? t.d1 : t.d2);
-    if (t.j > 1 || mj > 64 || t.d2 % 16) return false;
+    if (t.j > 1 || mj > 64 || mj % 16 || t.d2 % 16) return false;
+    if ((int64_t)t.d0 * t.d1 * t.d2 / mj % 64) return false;
   }
   return true;
 }
@@ -212,7 +212,7 @@ void mv_chunks(const MatvecPlan& P, const int* dm, const int64_t target[3], int 
     int ns;
     int64_t sl, row;
     slice_geom(sp, dm, ma[sp], mb[sp], ns, sl, row);
-    units[sp] = sw_mfma(ma[sp], mb[sp]) ? (int64_t)ns * ((ma[sp] / 16 + 3) / 4)
+    units[sp] = sw_mfma(ma[sp], mb[sp]) ? (int64_t)ns
                                         : (int64_t)ns * ((ma[sp] * mb[sp] + 255) / 256);
   }
   mv_chunk_counts(nit, ma, mb, units, (int64_t)dm[0] * dm[1] * dm[2], target, out);
@@ -235,7 +235,8 @@ void build_mv_dev(attn_handle* h, int n, std::vector<int64_t>& comb_off_out) {
   for (size_t i = 0; i < P.combines.size(); i++) h->comb_blocks[n].push_back({off[i], P.combines[i].dim});
   int64_t part_used = 0;
   int nchs[3];
-  const int64_t target[3] = {kMvTarget, kMvTarget, kMvTarget};
+  int64_t target[3];
+  mv_targets(dm, target);
   mv_chunks(P, dm, target, nchs);
   // two-leg items and local operators, grouped by spectator
   for (int sp = 0; sp < 3; sp++) {
@@ -370,7 +371,7 @@ bool gram_nt_ok(const std::vector<GRTask>& ts, bool mfma) {
   if (!mfma || ts.empty()) return false;
   for (const GRTask& t : ts) {
     const int mj = t.j == 0 ? t.d0 : (t.j == 1 ? t.d1 : t.d2);
-    if (t.j > 1 || mj > 64 || t.d2 % 16 || t.f0 % 16 || t.f1 % 16) return false;
+    if (t.j > 1 || mj > 64 || mj % 16 || t.d2 % 16 || t.f0 % 16 || t.f1 % 16) return false;
     if ((uintptr_t)t.X % 32 || (uintptr_t)t.Z % 32) return false;
   }
   return true;
@@ -417,7 +418,7 @@ std::vector<int> env_pieces(const Model& M, const EnvPlan& P, int& cap_out) {
   std::vector<int> pc(P.outs.size(), 0);
   int64_t W = 0;
   for (size_t o = 0; o < P.outs.size(); o++) W += (int64_t)P.outs[o].items.size();
-  const int64_t strips = std::max(1, (g.ma / 16 + 3) / 4);
+  const int64_t strips = (sw_strips(g.ma) + 3) / 4;
   const int64_t ntask = std::max<int64_t>(1, (kEnvWorkgroups + g.ns * strips - 1) / (g.ns * strips));
   const int cap = sw_mfma(g.ma, g.mb) ? (int)std::max<int64_t>(4, (W + ntask - 1) / ntask) : 1 << 30;
   for (size_t o = 0; o < P.outs.size(); o++) {
@@ -455,16 +456,12 @@ void build_env_dev(attn_handle* h, const EnvPlan& P, EnvDev& D) {
   const int64_t F = Msz / mj;
   const bool gmf = gram_mfma_ok(mj, Msz);
   int64_t fchunk = F;
-  if (gmf) {
-    // enough gram workgroups: ~8 chunks of the free index per output at most
-    fchunk = std::max<int64_t>(64, ((F / 8) + 63) / 64 * 64);
-    while (F % fchunk) fchunk += 64;
-  }
-  const int nfc = (int)(F / fchunk);
+  if (gmf) fchunk = gram_chunk(F, 8);   // enough gram workgroups: ~8 chunks of the free index per output at most
+  const int nfc = (int)((F + fchunk - 1) / fchunk);
   int cap = 0;
   const std::vector<int> pieces = env_pieces(M, P, cap);
   const bool multi = sw_mfma(ma, mb);
-  const int64_t strips = std::max(1, (ma / 16 + 3) / 4);
+  const int64_t strips = (sw_strips(ma) + 3) / 4;
   size_t o0 = 0;
   while (o0 < P.outs.size()) {
     // chunk: consecutive outputs whose pieces fit the Z budget
@@ -496,7 +493,7 @@ void build_env_dev(attn_handle* h, const EnvPlan& P, EnvDev& D) {
           GRTask gt;
           gt.X = T; gt.Z = Z; gt.partial = h->d_grpart + (pslot + (int64_t)k * nfc + c) * mj * mj;
           gt.d0 = dm[0]; gt.d1 = dm[1]; gt.d2 = dm[2]; gt.j = j;
-          gt.f0 = (int)(c * fchunk); gt.f1 = (int)((c + 1) * fchunk);
+          gt.f0 = (int)(c * fchunk); gt.f1 = (int)std::min<int64_t>(F, (c + 1) * fchunk);
           ch.gr.tasks.push_back(gt);
         }
         zslot++;
@@ -945,18 +942,15 @@ void build_qr_dev(attn_handle* h, int n, int leg, QRDev& Q) {
   Q.mj = mj; Q.rows = rows; Q.Msz = Msz;
   Q.gmf = gram_mfma_ok(mj, Msz);
   int64_t fchunk = rows;
-  if (Q.gmf) {
-    fchunk = std::max<int64_t>(64, ((rows / 32) + 63) / 64 * 64);
-    while (rows % fchunk) fchunk += 64;
-  }
-  Q.nfc = (int)(rows / fchunk);
+  if (Q.gmf) fchunk = gram_chunk(rows, 32);
+  Q.nfc = (int)((rows + fchunk - 1) / fchunk);
   GRReduce gr;
   gr.partial = h->d_grpart; gr.out = G; gr.m = mj; gr.npart = Q.nfc; gr.coef = 1.0; gr.accumulate = 0; gr.pad = 0;
   Q.d_gr = upload(h, std::vector<GRReduce>{gr});
   Q.h_gr = {gr};
   Q.mmf = mode_mfma_ok(mj, Msz);
   std::vector<int2> wus;
-  if (Q.mmf) for (int64_t f = 0; f < rows / 64; f++) wus.push_back(make_int2(0, (int)f));
+  if (Q.mmf) for (int64_t f = 0; f < mode_blocks(mj, Msz); f++) wus.push_back(make_int2(0, (int)f));
   else for (int64_t e = 0; e < Msz; e += 256) wus.push_back(make_int2(0, (int)e));
   Q.nwus = (int)wus.size();
   Q.d_wus = upload(h, wus);
@@ -969,7 +963,7 @@ void build_qr_dev(attn_handle* h, int n, int leg, QRDev& Q) {
     for (int c = 0; c < Q.nfc; c++) {
       gt[c].X = src; gt[c].Z = src; gt[c].partial = h->d_grpart + (int64_t)c * mj * mj;
       gt[c].d0 = dm[0]; gt[c].d1 = dm[1]; gt[c].d2 = dm[2]; gt[c].j = leg;
-      gt[c].f0 = (int)(c * fchunk); gt[c].f1 = (int)((c + 1) * fchunk);
+      gt[c].f0 = (int)(c * fchunk); gt[c].f1 = (int)std::min<int64_t>(rows, (c + 1) * fchunk);
     }
     Q.gnt = gram_nt_ok(gt, Q.gmf) && (pass == 0 || Q.gnt);
     Q.d_gt[pass] = upload(h, gt);
@@ -997,7 +991,7 @@ void build_ab_dev(attn_handle* h, int q, int leg, ABDev& A) {
   A.mj = mj; A.Msz = Msz;
   A.mmf = mode_mfma_ok(mj, Msz);
   std::vector<int2> wus;
-  if (A.mmf) for (int64_t f = 0; f < Msz / mj / 64; f++) wus.push_back(make_int2(0, (int)f));
+  if (A.mmf) for (int64_t f = 0; f < mode_blocks(mj, Msz); f++) wus.push_back(make_int2(0, (int)f));
   else for (int64_t e = 0; e < Msz; e += 256) wus.push_back(make_int2(0, (int)e));
   A.nwus = (int)wus.size();
   A.d_wus = upload(h, wus);
@@ -1370,7 +1364,8 @@ attn_status attn_build_tpo(const attn_problem* p, attn_handle** out) {
       const int64_t Msz = (int64_t)dm[0] * dm[1] * dm[2];
       const MatvecPlan& P = h->M.mv[n];
       int nparts = 0, nchs[3];
-      const int64_t target[3] = {kMvTarget, kMvTarget, kMvTarget};
+      int64_t target[3];
+      mv_targets(dm, target);
       mv_chunks(P, dm, target, nchs);
       for (int sp = 0; sp < 3; sp++) nparts += nchs[sp];
       part_need = std::max(part_need, nparts * Msz);
@@ -2159,7 +2154,7 @@ struct Checker {
       const bool mf = sw_mfma(t.ma, t.mb);
       int64_t rows_hi;
       if (mf) {
-        if (wu.z % 4 || wu.z * 16 >= t.ma) { fail("sandwich: strip"); return; }
+        if (wu.z != 0) { fail("sandwich: strip"); return; }
         rows_hi = t.ma;   // the WG stages all rows of the slice
       } else {
         if (wu.z < 0 || wu.z >= t.ma * t.mb) { fail("sandwich: element"); return; }
@@ -2183,6 +2178,7 @@ struct Checker {
       for (auto& rg : ranges) {
         if (rg.first < 0 || rg.first + rg.second > (int)g.items.size()) { fail("sandwich: item range"); return; }
         for (int i = rg.first; i < rg.first + rg.second; i++) {
+          if (i > rg.first && !g.items[i].B && g.items[i - 1].B) { fail("sandwich: item without B behind one with B"); return; }
           if (g.items[i].A) span(g.items[i].A, (int64_t)t.ma * t.ma * esz, "sandwich A");
           if (g.items[i].B) span(g.items[i].B, (int64_t)t.mb * t.mb * esz, "sandwich B");
         }
@@ -2197,7 +2193,7 @@ struct Checker {
       const int mj = t.j == 0 ? t.d0 : (t.j == 1 ? t.d1 : t.d2);
       if (mj != g.mj) { fail("mode: group dims"); return; }
       const int64_t M = (int64_t)t.d0 * t.d1 * t.d2;
-      if (g.mfma) { if ((int64_t)(wu.y + 1) * 64 * mj > M) { fail("mode: tile"); return; } }
+      if (g.mfma) { if (wu.y < 0 || wu.y >= mode_blocks(mj, M) || M * esz > INT32_MAX) { fail("mode: tile"); return; } }
       else if (wu.y < 0 || wu.y >= M) { fail("mode: element"); return; }
       span(t.out, M * esz, "mode out");
       if (t.job0 < 0 || t.job0 + t.njob > (int)g.jobs.size()) { fail("mode: job range"); return; }
@@ -2214,7 +2210,7 @@ struct Checker {
       const int mj = t.j == 0 ? t.d0 : (t.j == 1 ? t.d1 : t.d2);
       const int64_t M = (int64_t)t.d0 * t.d1 * t.d2;
       if (t.f0 < 0 || t.f1 > M / mj || t.f0 >= t.f1) { fail("gram: f range"); return; }
-      if (mfma && ((t.f1 - t.f0) % 64 || t.f0 % 64)) { fail("gram: f range not tiled"); return; }
+      if (mfma && t.f0 % 64) { fail("gram: f range not tiled"); return; }
       span(t.X, M * 8, "gram X");
       span(t.Z, M * 8, "gram Z");
       span(t.partial, (int64_t)mj * mj * 8, "gram partial");

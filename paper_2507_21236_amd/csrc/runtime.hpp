@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstring>
 #include <functional>
+#include <map>
 #include <string>
 #include <vector>
 
@@ -140,8 +141,22 @@ struct ABDev {
   MPGroup h_mp;   // host copy for validation
 };
 
-inline bool mode_mfma_ok(int mj, int64_t M) { return mj % 16 == 0 && mj <= 128 && (M / mj) % 64 == 0; }
-inline bool gram_mfma_ok(int mj, int64_t M) { return mj % 16 == 0 && mj <= 128 && (M / mj) % 64 == 0; }
+// Matrix-core mode products: whole tiles, and ragged legs above half a tile
+// over at least one tile of free indices (smaller ones are a few loads per
+// output entry, one thread each).  Tensors are addressed by 32-bit byte offsets.
+inline bool mode_mfma_ok(int mj, int64_t M) {
+  return mj <= 128 && M < ((int64_t)1 << 27) && ((mj % 16 == 0 && (M / mj) % 64 == 0) || (mj > 8 && M / mj >= 16));
+}
+inline int64_t mode_blocks(int mj, int64_t M) { return (M / mj + 63) / 64; }
+inline bool gram_mfma_ok(int mj, int64_t M) { return mode_mfma_ok(mj, M); }
+// Free indices per gram work unit (whole 64-wide blocks, the last unit takes
+// what is left): about `parts` units where the free range allows it.
+inline int64_t gram_chunk(int64_t F, int parts) {
+  int64_t c = std::max<int64_t>(64, ((F / parts) + 63) / 64 * 64);
+  if (F % 64 == 0)
+    while (F % c) c += 64;   // equal units
+  return c;
+}
 
 }  // namespace rt
 
@@ -291,12 +306,18 @@ double* block_ptr(attn_handle* h, const BRef& b, double* comb_base, const std::v
 void slice_geom(int spect, const int* dm, int& ma, int& mb, int& ns, int64_t& sl, int64_t& row);
 // item chunks per spectator of the matvec plan of a node with dims dm
 // (target workgroups per launch, per spectator's slice shape)
-// matvec work units per spectator group (three groups per node): 3 x 768 =
-// three rounds of the 768 workgroups resident at three per CU.  Measured
-// against 1024 (four rounds) and 512: sweep 0.581 vs 0.584 and 0.582 s, and a
-// quarter fewer partial outputs to write and sum than with 1024.  The batched
-// form takes the same split unless it is autotuned.
-constexpr int64_t kMvTarget = 768;
+// Matvec work units per spectator group (three groups per node).  Four strips
+// (the full nodes): 3 x 1024 = three rounds of the 1024 workgroups resident at
+// four per CU; measured at the heaviest 16 x 16 m = 64 node (contraction + sum of
+// the partial outputs) 1141 + 43 us, against 1158 + 34 with 768 and 1178 + 29
+// with 683.  Fewer strips: 768, where the launches are shorter than the spread
+// of their workgroups.  The batched form takes the same split unless it is
+// autotuned.
+inline int64_t mv_target(int ma) { return sw_strips(ma) >= 4 ? 1024 : 768; }
+inline void mv_targets(const int* dm, int64_t target[3]) {
+  target[0] = mv_target(dm[1]);   // the a leg of each spectator's slices
+  target[1] = target[2] = mv_target(dm[0]);
+}
 void mv_chunks(const MatvecPlan& P, const int* dm, const int64_t target[3], int out[3]);
 bool sw_mfma(int ma, int mb);
 // Doubles of the QR matrices of a handle whose widest link is mmax: G, R0, R1,
@@ -308,6 +329,75 @@ inline int64_t qrmat_doubles(int64_t mmax) { return 6 * mmax * mmax + mmax * (mm
 // still spread over the chip.
 inline int64_t chunk_cap(int64_t Msz) {
   return Msz >= 65536 ? 32 : std::min<int64_t>(128, std::max<int64_t>(32, ((int64_t)1 << 19) / Msz));
+}
+// C chunks shared out over n spectators in proportion to their item counts by
+// largest remainders, at least one each.
+inline void chunk_shares(int64_t C, const int64_t* items, int n, int64_t* c) {
+  int64_t tot = 0, rem[3], sum = 0;
+  for (int g = 0; g < n; g++) tot += items[g];
+  for (int g = 0; g < n; g++) {
+    c[g] = C * items[g] / tot;
+    rem[g] = C * items[g] - c[g] * tot;   // remainder of the exact share, in units of 1 / tot
+    if (c[g] == 0) { c[g] = 1; rem[g] -= tot; }   // every spectator with items gets a chunk
+    sum += c[g];
+  }
+  while (sum < C) {   // the largest remainders get one more chunk (lowest spectator first on ties)
+    int best = 0;
+    for (int g = 1; g < n; g++)
+      if (rem[g] > rem[best]) best = g;
+    c[best]++;
+    rem[best] -= tot;
+    sum++;
+  }
+  while (sum > C) {   // the smallest remainders among spectators with two chunks or more give one back
+    int worst = -1;
+    for (int g = 0; g < n; g++)
+      if (c[g] > 1 && (worst < 0 || rem[g] < rem[worst])) worst = g;
+    if (worst < 0) break;
+    c[worst]--;
+    rem[worst] += tot;
+    sum--;
+  }
+}
+// Chunks of a launch whose slices have more than four strips.  Few such
+// workgroups are resident (two per CU at five and six strips, one at seven
+// and eight), and a chunk is as many of them as the spectator has slices, so
+// a fixed count leaves the last round part empty (128 slices x 9 chunks on 256
+// slots: 4.5 rounds).  The count with the shortest list schedule is taken,
+// between two and eight rounds: a workgroup lasts its items and one more (its
+// slice in and out), and a chunk costs the write and the later read of a
+// partial output, 50 / m items of the whole chip (16 bytes per entry at
+// 4.75 TB/s against 4 m flops per entry and item at 60 TFLOP/s).
+inline int64_t wide_chunks(const int64_t* items, int n, int64_t units, int m, int strips) {
+  const int64_t slots = 256 * (strips <= 6 ? 2 : 1);
+  const int64_t lo = std::max<int64_t>(n, 2 * slots / units), hi = std::max<int64_t>(lo, 8 * slots / units);
+  double best = 0;
+  int64_t bestC = lo;
+  for (int64_t C = lo; C <= hi; C++) {
+    int64_t c[3];
+    chunk_shares(C, items, n, c);
+    std::vector<int64_t> len;
+    for (int g = 0; g < n; g++)
+      for (int64_t k = 0; k < c[g]; k++) len.push_back(items[g] * (k + 1) / c[g] - items[g] * k / c[g]);
+    std::sort(len.rbegin(), len.rend());
+    std::map<double, int64_t> idle;   // slots by the time they become free
+    idle[0.0] = slots;
+    double end = 0;
+    for (int64_t l : len)
+      for (int64_t left = units; left > 0;) {
+        const auto it = idle.begin();
+        const double t = it->first;
+        const int64_t k = std::min(left, it->second);
+        it->second -= k;
+        if (it->second == 0) idle.erase(it);
+        idle[t + (double)l + 1.0] += k;
+        end = std::max(end, t + (double)l + 1.0);
+        left -= k;
+      }
+    const double cost = end + (double)C * units / slots * (50.0 / m);
+    if (C == lo || cost < best) { best = cost; bestC = C; }
+  }
+  return bestC;
 }
 // Item chunks per spectator of a matvec plan.  Spectators whose slices have
 // the same shape share one launch; the launch gets C = (number of such
@@ -324,35 +414,13 @@ inline void mv_chunk_counts(const int64_t nitems[3], const int ma[3], const int 
   for (int sp = 0; sp < 3; sp++) {
     if (nitems[sp] <= 0 || done[sp]) continue;
     int grp[3], ng = 0;
-    int64_t tot = 0;
+    int64_t it[3], c[3];
     for (int q = 0; q < 3; q++)
-      if (nitems[q] > 0 && ma[q] == ma[sp] && mb[q] == mb[sp]) { grp[ng++] = q; tot += nitems[q]; done[q] = true; }
-    const int64_t C = ng * std::max<int64_t>(1, target[sp] / std::max<int64_t>(1, units[sp]));
-    int64_t c[3], rem[3], sum = 0;
-    for (int g = 0; g < ng; g++) {
-      const int q = grp[g];
-      c[g] = C * nitems[q] / tot;
-      rem[g] = C * nitems[q] - c[g] * tot;   // remainder of the exact share, in units of 1 / tot
-      if (c[g] == 0) { c[g] = 1; rem[g] -= tot; }   // every spectator with items gets a chunk
-      sum += c[g];
-    }
-    while (sum < C) {   // the largest remainders get one more chunk (lowest spectator first on ties)
-      int best = 0;
-      for (int g = 1; g < ng; g++)
-        if (rem[g] > rem[best]) best = g;
-      c[best]++;
-      rem[best] -= tot;
-      sum++;
-    }
-    while (sum > C) {   // the smallest remainders among spectators with two chunks or more give one back
-      int worst = -1;
-      for (int g = 0; g < ng; g++)
-        if (c[g] > 1 && (worst < 0 || rem[g] < rem[worst])) worst = g;
-      if (worst < 0) break;
-      c[worst]--;
-      rem[worst] += tot;
-      sum--;
-    }
+      if (nitems[q] > 0 && ma[q] == ma[sp] && mb[q] == mb[sp]) { it[ng] = nitems[q]; grp[ng++] = q; done[q] = true; }
+    int64_t C = ng * std::max<int64_t>(1, target[sp] / std::max<int64_t>(1, units[sp]));
+    if (sw_on_mfma(ma[sp], mb[sp]) && sw_strips(ma[sp]) > 4)
+      C = wide_chunks(it, ng, units[sp], ma[sp], sw_strips(ma[sp]));
+    chunk_shares(C, it, ng, c);
     for (int g = 0; g < ng; g++) {
       const int q = grp[g];
       out[q] = (int)std::max<int64_t>(1, std::min<int64_t>(c[g], std::min<int64_t>(nitems[q], chunk_cap(Msz))));

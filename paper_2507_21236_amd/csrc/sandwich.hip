@@ -20,19 +20,19 @@ namespace attn {
 
 // ============================================================================ sandwich
 // One work unit = (task, slice s, first 16-row strip).  The WG stages X_s in LDS;
-// wave w owns rows [16 (strip0 + w), +16) of Y_s.  Per item:
+// wave w owns rows [16 (strip0 + w), +16) of Y_s; mb <= 16 NB.  Per item:
 //   stage 1: T1^T[p][a'] = sum_a X_s[a][p] A[a'][a]           (or X_s^T if A = 1)
 //   stage 2: Y^T[p'][a'] += sum_p B[p'][p] T1^T[p][a']        (or T1^T if B = 1)
 // Stage 2 consumes the stage-1 accumulators directly as the B operand by
 // walking K = p in the order {16 tp + drow(j, i) : j = 0..3} for fixed (tp, i),
 // which is exactly how the accumulator layout spreads p over lane groups.
-template <typename T, int NB>
+template <typename T, int NB, bool SQ>
 __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __restrict__ items, int i0, int i1,
                                               void* y, int accumulate, int s, int strip0, const T* lds) {
   typedef typename V4<T>::type v4;
-  const int ma = t.ma;
-  constexpr int mb = 16 * NB;
-  constexpr int ld = mb + 2;
+  const int ma = t.ma, mb = t.mb;
+  constexpr int mbp = 16 * NB;
+  constexpr int ld = mbp + 2;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int strip = strip0 + wave;
   if (strip * 16 >= ma) return;
@@ -45,15 +45,42 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
   v4 acc[NB];
 #pragma unroll
   for (int q = 0; q < NB; q++) acc[q] = v4{0, 0, 0, 0};
-  if (ma == mb) {
-    // Square slices (the full nodes): both stages fully unrolled with the
+  // items without B (the summed operator of the a leg, first in its list) in a
+  // loop of their own: a second way to update the accumulators inside the loop
+  // below makes the compiler keep two copies of them (FP64, four tiles: 146
+  // registers and three wavefronts per SIMD instead of 118 and four)
+  for (; i0 < i1 && !items[i0].B; i0++) {
+    const T* A = (const T*)items[i0].A;
+    const T coef = (T)items[i0].coef;
+    if (!A) {
+      const T* xr = lds + (arow < ma ? arow : ma - 1) * ld;
+#pragma unroll
+      for (int q = 0; q < NB; q++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) acc[q][i] += xr[16 * q + pk[i]] * coef;
+      continue;
+    }
+    const __amdgpu_buffer_rsrc_t ra = block_rsrc(A, ma * ma);
+    for (int ks = 0; 4 * ks < ma; ks++) {
+      const T b0 = bload<T>(ra, (l4 * ma + arow) * (int)sizeof(T), 4 * ks * ma * (int)sizeof(T)) * coef;
+      const T* xr = lds + (4 * ks + l4) * ld + pc;
+#pragma unroll
+      for (int q = 0; q < NB; q++) acc[q] = mfma16(xr[16 * q], b0, acc[q]);
+    }
+  }
+  if constexpr (SQ) {
+    // Square slices of whole tiles (the full nodes): both stages fully unrolled with the
     // operator loads issued a fixed distance ahead of the products that use
     // them (PA A elements, PB groups of NB B elements), each step fenced off
     // so that the scheduler keeps that distance.  Same products in the same
     // order as the general loop below.
-    constexpr int KS = mb / 4;
+    constexpr int KS = mbp / 4, astep = 4 * mbp * (int)sizeof(T), bstep = 16 * mbp * (int)sizeof(T);
+    const int ao = (l4 * mbp + arow) * (int)sizeof(T);
+    int bo[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) bo[i] = (pk[i] * mbp + pc) * (int)sizeof(T);
     constexpr int PA = 2;
-    constexpr int PB = 2;
+    constexpr int PB = sizeof(T) == 8 && NB > 4 ? 1 : 2;   // NB products of a group cover the load
     for (int it = i0; it < i1; it++) {
       const T* A = (const T*)items[it].A;
       const T* B = (const T*)items[it].B;
@@ -62,14 +89,14 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
       if (A) {
 #pragma unroll
         for (int q = 0; q < NB; q++) t1[q] = v4{0, 0, 0, 0};
-        const T* Ap = A + arow;
+        const __amdgpu_buffer_rsrc_t ra = block_rsrc(A, mbp * mbp);
         T ab[PA];
 #pragma unroll
-        for (int k = 0; k < PA; k++) ab[k] = gload(Ap + (int64_t)(4 * k + l4) * mb);
+        for (int k = 0; k < PA; k++) ab[k] = bload<T>(ra, ao, k * astep);
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
           const T bop = ab[ks % PA] * coef;
-          if (ks + PA < KS) ab[ks % PA] = gload(Ap + (int64_t)(4 * (ks + PA) + l4) * mb);
+          if (ks + PA < KS) ab[ks % PA] = bload<T>(ra, ao, (ks + PA) * astep);
           const T* xr = lds + (4 * ks + l4) * ld + pc;
 #pragma unroll
           for (int q = 0; q < NB; q++) t1[q] = mfma16(xr[16 * q], bop, t1[q]);
@@ -82,14 +109,14 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
 #pragma unroll
           for (int i = 0; i < 4; i++) t1[q][i] = xr[16 * q + pk[i]] * coef;
       }
-      if (B) {
+      {
         // group g = (tp, i) = (g / 4, g % 4): the B elements of row 16 tp + pk[i]
+        const __amdgpu_buffer_rsrc_t rb = block_rsrc(B, mbp * mbp);
         T bb[PB][NB];
 #pragma unroll
         for (int g = 0; g < PB; g++)
 #pragma unroll
-          for (int tq = 0; tq < NB; tq++)
-            bb[g][tq] = gload(B + (int64_t)(16 * (g / 4) + pk[g % 4]) * mb + pc + 16 * tq);
+          for (int tq = 0; tq < NB; tq++) bb[g][tq] = bload<T>(rb, bo[g] + 16 * tq * (int)sizeof(T), 0);
 #pragma unroll
         for (int g = 0; g < 4 * NB; g++) {
           T bv[NB];
@@ -99,55 +126,107 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
             const int gn = g + PB;
 #pragma unroll
             for (int tq = 0; tq < NB; tq++)
-              bb[g % PB][tq] = gload(B + (int64_t)(16 * (gn / 4) + pk[gn % 4]) * mb + pc + 16 * tq);
+              bb[g % PB][tq] = bload<T>(rb, bo[gn % 4] + 16 * tq * (int)sizeof(T), (gn / 4) * bstep);
           }
 #pragma unroll
           for (int tq = 0; tq < NB; tq++) acc[tq] = mfma16(bv[tq], t1[g / 4][g % 4], acc[tq]);
           __builtin_amdgcn_sched_barrier(0);
         }
-      } else {
-#pragma unroll
-        for (int q = 0; q < NB; q++) acc[q] += t1[q];
       }
     }
-  } else
-  for (int it = i0; it < i1; it++) {
-    const T* A = (const T*)items[it].A;
-    const T* B = (const T*)items[it].B;
-    const T coef = (T)items[it].coef;
-    v4 t1[NB];
-    if (A) {
+  } else {
+    // Every other shape of legs up to 128 (rectangular slices, legs that are
+    // not multiples of 16): the slice is staged with zeros up to the tile
+    // edges, the blocks are read through bounds-checked buffer loads (rows past
+    // the end are zero and add nothing; columns past the end only reach
+    // results that are not stored), and products of K rows that lie wholly past
+    // the end are left out.  Operator loads run two steps (A) or two groups (B)
+    // ahead of their products, as above.  Legs of 50 (8 x 8 lattice, heaviest
+    // node, 11.3 GFLOP): 127 ms with one thread per output entry, 0.31 ms
+    // here (32 TFLOP/s; 1.7x of its work is in the padding of the tiles).
+    const int KS = (ma + 3) >> 2;
+    const int rowc = arow < ma ? arow : ma - 1;
+    const int ao = (l4 * ma + arow) * (int)sizeof(T), astep = 4 * ma * (int)sizeof(T);
+    int bo[4];
 #pragma unroll
-      for (int q = 0; q < NB; q++) t1[q] = v4{0, 0, 0, 0};
-      const T* Ap = A + arow;
-      for (int k0 = 0; k0 < ma; k0 += 4) {
-        const T bop = gload(Ap + (int64_t)(k0 + l4) * ma) * coef;
-        const T* xr = lds + (k0 + l4) * ld + pc;
+    for (int i = 0; i < 4; i++) bo[i] = (pk[i] * mb + pc) * (int)sizeof(T);
+    const int bstep = 16 * mb * (int)sizeof(T);
+    for (int it = i0; it < i1; it++) {
+      const T* A = (const T*)items[it].A;
+      const T* B = (const T*)items[it].B;
+      const T coef = (T)items[it].coef;
+      v4 t1[NB];
+      if (A) {
+        const __amdgpu_buffer_rsrc_t ra = block_rsrc(A, ma * ma);
 #pragma unroll
-        for (int q = 0; q < NB; q++) t1[q] = mfma16(xr[16 * q], bop, t1[q]);
-      }
-    } else {
-      const T* xr = lds + arow * ld;
+        for (int q = 0; q < NB; q++) t1[q] = v4{0, 0, 0, 0};
+        const T* xr = lds + l4 * ld + pc;
+        T a0 = bload<T>(ra, ao, 0), a1 = bload<T>(ra, ao, astep);
+        for (int ks = 0; ks < KS; ks += 2) {
+          const T b0 = a0 * coef;
+          a0 = bload<T>(ra, ao, (ks + 2) * astep);
 #pragma unroll
-      for (int q = 0; q < NB; q++)
+          for (int q = 0; q < NB; q++) t1[q] = mfma16(xr[16 * q], b0, t1[q]);
+          __builtin_amdgcn_sched_barrier(0);
+          if (ks + 1 < KS) {
+            const T b1 = a1 * coef;
+            a1 = bload<T>(ra, ao, (ks + 3) * astep);
 #pragma unroll
-        for (int i = 0; i < 4; i++) t1[q][i] = xr[16 * q + pk[i]] * coef;
-    }
-    if (B) {
-#pragma unroll
-      for (int tp = 0; tp < NB; tp++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const T* Bp = B + (int64_t)(16 * tp + pk[i]) * mb + pc;
-#pragma unroll
-          for (int tq = 0; tq < NB; tq++) acc[tq] = mfma16(gload(Bp + 16 * tq), t1[tp][i], acc[tq]);
+            for (int q = 0; q < NB; q++) t1[q] = mfma16(xr[4 * ld + 16 * q], b1, t1[q]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          xr += 8 * ld;
         }
-    } else {
+      } else {
+        const T* xr = lds + rowc * ld;
 #pragma unroll
-      for (int q = 0; q < NB; q++) acc[q] += t1[q];
+        for (int q = 0; q < NB; q++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) t1[q][i] = xr[16 * q + pk[i]] * coef;
+      }
+      {
+        const __amdgpu_buffer_rsrc_t rb = block_rsrc(B, mb * mb);
+        constexpr int PB = sizeof(T) == 8 && NB > 4 ? 1 : 2;
+        T bb[PB][NB];
+#pragma unroll
+        for (int g = 0; g < PB; g++)
+#pragma unroll
+          for (int tq = 0; tq < NB; tq++) bb[g][tq] = bload<T>(rb, bo[g] + 16 * tq * (int)sizeof(T), 0);
+#pragma unroll
+        for (int g = 0; g < 4 * NB; g++) {
+          // the lowest row of the group (wave-uniform): past the end, no product
+          if (g / 4 == NB - 1 && 16 * (NB - 1) + colperm<T>(drow<T>(0, g % 4)) >= mb) continue;
+          T bv[NB];
+#pragma unroll
+          for (int tq = 0; tq < NB; tq++) bv[tq] = bb[g % PB][tq];
+          if (g + PB < 4 * NB) {
+            const int gn = g + PB;
+#pragma unroll
+            for (int tq = 0; tq < NB; tq++)
+              bb[g % PB][tq] = bload<T>(rb, bo[gn % 4] + 16 * tq * (int)sizeof(T), (gn / 4) * bstep);
+          }
+#pragma unroll
+          for (int tq = 0; tq < NB; tq++) acc[tq] = mfma16(bv[tq], t1[g / 4][g % 4], acc[tq]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
   }
+  if (arow >= ma) return;
   T* Y = (T*)y + (int64_t)s * t.ys_slice + (int64_t)arow * t.ys_row;
+  if (mb != mbp) {   // ragged columns: single elements (rows are not 16-byte aligned)
+#pragma unroll
+    for (int q = 0; q < NB; q++)
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int c = 16 * q + pk[i];
+        if (c >= mb) continue;
+        T v = acc[q][i];
+        if (accumulate) v += Y[c];
+        __builtin_nontemporal_store(v, Y + c);
+      }
+    return;
+  }
   if constexpr (sizeof(T) == 8) {
 #pragma unroll
     for (int q = 0; q < NB; q++) {
@@ -180,43 +259,71 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
 }
 
 
-template <typename T, int NB>
+template <typename T, int NB, bool SQ>
 __device__ __forceinline__ void sandwich_mfma(const SWTask& t, const SWItem* __restrict__ items,
                                               const int4 wu, const T* __restrict__ xbase,
                                               unsigned char* smem_raw, const SWOut* __restrict__ outs = nullptr) {
   T* lds = reinterpret_cast<T*>(smem_raw);
   const int s = wu.y;
-  const int ma = t.ma;
-  constexpr int mb = 16 * NB;
-  constexpr int ld = mb + 2;
+  const int ma = t.ma, mb = t.mb;
+  constexpr int mbp = 16 * NB;
+  constexpr int ld = mbp + 2;
   const T* X = (t.x ? (const T*)t.x : xbase) + (int64_t)s * t.xs_slice;
-  for (int e = threadIdx.x; e < ma * mb; e += 256) {
-    const int a = e / mb, b = e - a * mb;
-    lds[a * ld + b] = X[(int64_t)a * t.xs_row + b];
+  // eight loads in flight per thread; zeros up to whole K steps and tiles
+  const int n = (SQ ? mbp : (ma + 3) & ~3) * mbp, nt = blockDim.x;
+  for (int e0 = threadIdx.x; e0 < n; e0 += 8 * nt) {
+    T v[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const int e = e0 + u * nt, a = e / mbp, b = e - a * mbp;
+      const bool in = SQ ? e < n : a < ma && b < mb;
+      v[u] = gload(X + (in ? (int64_t)a * t.xs_row + b : 0));
+      if (!SQ && !in) v[u] = 0;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const int e = e0 + u * nt, a = e / mbp, b = e - a * mbp;
+      if (e < n) lds[a * ld + b] = v[u];
+    }
   }
   __syncthreads();
   if (outs && t.pad) {   // several outputs: items of output o go to outs[o].y
     for (int o = t.item0; o < t.item0 + t.nitem; o++)
-      sandwich_rows<T, NB>(t, items, outs[o].item0, outs[o].item0 + outs[o].nitem, outs[o].y, t.accumulate, s,
+      sandwich_rows<T, NB, SQ>(t, items, outs[o].item0, outs[o].item0 + outs[o].nitem, outs[o].y, t.accumulate, s,
                            wu.z, lds);
   } else {
-    sandwich_rows<T, NB>(t, items, t.item0, t.item0 + t.nitem, t.y, t.accumulate, s, wu.z, lds);
+    sandwich_rows<T, NB, SQ>(t, items, t.item0, t.item0 + t.nitem, t.y, t.accumulate, s, wu.z, lds);
   }
 }
 
-template <typename T, int NB>
-__global__ __launch_bounds__(256) void k_sandwich(const SWTask* __restrict__ tasks,
+// One wavefront per 16-row strip (up to eight share a staged slice): at legs
+// of 96 and 128 the slice fills half or most of the LDS, and splitting its
+// strips over workgroups of four wavefronts staged it twice and left one
+// wavefront per SIMD (8 x 8 lattice, heaviest node: FP32 legs of 96 1884 ->
+// 1367 us, 112 3.2 -> 2.4 ms; FP64 legs of 128, where one workgroup of eight
+// wavefronts fills a CU either way, 7.10 -> 7.17 ms).
+template <typename T, int NB, bool SQ>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && NB <= 6 ? 3 : 2)))
+void k_sandwich(const SWTask* __restrict__ tasks,
                                                   const SWItem* __restrict__ items,
                                                   const int4* __restrict__ wus,
                                                   const T* __restrict__ xbase,
                                                   const SWOut* __restrict__ outs) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int4 wu = wus[blockIdx.x];
-  sandwich_mfma<T, NB>(tasks[wu.x], items, wu, xbase, smem_raw, outs);
+  sandwich_mfma<T, NB, SQ>(tasks[wu.x], items, wu, xbase, smem_raw, outs);
 }
 
-// Generic sandwich for dimensions that are not multiples of 16: one thread per
-// output element of one slice.  wu = (task, slice, first element).
+// either form, for the launches that mix shapes
+template <typename T, int NB>
+__device__ __forceinline__ void sandwich_any(const SWTask& t, const SWItem* __restrict__ items, const int4 wu,
+                                             unsigned char* smem_raw) {
+  if (t.ma == 16 * NB && t.mb == 16 * NB) sandwich_mfma<T, NB, true>(t, items, wu, nullptr, smem_raw);
+  else sandwich_mfma<T, NB, false>(t, items, wu, nullptr, smem_raw);
+}
+
+// Generic sandwich for legs above 128: one thread per output element of one
+// slice.  wu = (task, slice, first element).
 template <typename T>
 __device__ __forceinline__ void sandwich_gen_elem(const SWTask& t, const SWItem* __restrict__ items,
                                                   int s, int e, const T* __restrict__ xbase) {
@@ -332,7 +439,7 @@ __device__ __forceinline__ f4 mfma_bf(bf8 a, bf8 b, f4 c) {
 }
 
 template <int NB>
-__global__ __launch_bounds__(256) void k_sandwich_bf2(const SWTask* __restrict__ tasks,
+__global__ __launch_bounds__(512) void k_sandwich_bf2(const SWTask* __restrict__ tasks,
                                                       const SWItem* __restrict__ items,
                                                       const int4* __restrict__ wus,
                                                       const float* __restrict__ xbase) {
@@ -346,7 +453,7 @@ __global__ __launch_bounds__(256) void k_sandwich_bf2(const SWTask* __restrict__
   __bf16* xh = reinterpret_cast<__bf16*>(smem_raw);
   __bf16* xl = xh + mb * lda;
   const float* X = (t.x ? (const float*)t.x : xbase) + (int64_t)s * t.xs_slice;
-  for (int e = threadIdx.x; e < ma * mb; e += 256) {
+  for (int e = threadIdx.x; e < ma * mb; e += blockDim.x) {
     const int a = e / mb, b = e - a * mb;
     const float v = X[(int64_t)a * t.xs_row + b];
     const __bf16 hi = (__bf16)v;
@@ -847,12 +954,43 @@ __device__ __forceinline__ void sandwich_w2(const SWTask& t, const SWItem* __res
   int pk[4];
 #pragma unroll
   for (int i = 0; i < 4; i++) pk[i] = colperm<T>(drow<T>(l4, i));
+  constexpr int astep = 4 * mb * (int)sizeof(T), bstep = 16 * mb * (int)sizeof(T);
+  const int ao = (l4 * mb + r0 + l16) * (int)sizeof(T);
+  int bo[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) bo[i] = (pk[i] * mb + pc) * (int)sizeof(T);
   v4 acc[2][NB];
 #pragma unroll
   for (int a = 0; a < 2; a++)
 #pragma unroll
     for (int q = 0; q < NB; q++) acc[a][q] = v4{0, 0, 0, 0};
-  for (int it = t.item0; it < t.item0 + t.nitem; it++) {
+  int i0 = t.item0;
+  const int i1 = t.item0 + t.nitem;
+  for (; i0 < i1 && !items[i0].B; i0++) {   // items without B first, as in sandwich_rows
+    const T* A = (const T*)items[i0].A;
+    const T coef = (T)items[i0].coef;
+    if (!A) {
+#pragma unroll
+      for (int a = 0; a < 2; a++) {
+        const T* xr = L + (r0 + 16 * a + l16) * ld;
+#pragma unroll
+        for (int q = 0; q < NB; q++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) acc[a][q][i] += xr[16 * q + pk[i]] * coef;
+      }
+      continue;
+    }
+    for (int ks = 0; ks < KS; ks++) {
+      const T* xr = L + (4 * ks + l4) * ld + pc;
+#pragma unroll
+      for (int a = 0; a < 2; a++) {
+        const T bop = gload(A + r0 + 16 * a + l16 + (4 * ks + l4) * mb) * coef;
+#pragma unroll
+        for (int q = 0; q < NB; q++) acc[a][q] = mfma16(xr[16 * q], bop, acc[a][q]);
+      }
+    }
+  }
+  for (int it = i0; it < i1; it++) {
     const T* A = (const T*)items[it].A;
     const T* B = (const T*)items[it].B;
     const T coef = (T)items[it].coef;
@@ -862,12 +1000,12 @@ __device__ __forceinline__ void sandwich_w2(const SWTask& t, const SWItem* __res
       for (int a = 0; a < 2; a++)
 #pragma unroll
         for (int q = 0; q < NB; q++) t1[a][q] = v4{0, 0, 0, 0};
-      const T* Ap = A + r0 + l16;
+      const __amdgpu_buffer_rsrc_t ra = block_rsrc(A, mb * mb);
       T ab[PA][2];
 #pragma unroll
       for (int k = 0; k < PA; k++)
 #pragma unroll
-        for (int a = 0; a < 2; a++) ab[k][a] = gload(Ap + 16 * a + (int64_t)(4 * k + l4) * mb);
+        for (int a = 0; a < 2; a++) ab[k][a] = bload<T>(ra, ao + 16 * a * (int)sizeof(T), k * astep);
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) {
         T bop[2];
@@ -875,7 +1013,7 @@ __device__ __forceinline__ void sandwich_w2(const SWTask& t, const SWItem* __res
         for (int a = 0; a < 2; a++) bop[a] = ab[ks % PA][a] * coef;
         if (ks + PA < KS)
 #pragma unroll
-          for (int a = 0; a < 2; a++) ab[ks % PA][a] = gload(Ap + 16 * a + (int64_t)(4 * (ks + PA) + l4) * mb);
+          for (int a = 0; a < 2; a++) ab[ks % PA][a] = bload<T>(ra, ao + 16 * a * (int)sizeof(T), (ks + PA) * astep);
         const T* xr = L + (4 * ks + l4) * ld + pc;
 #pragma unroll
         for (int q = 0; q < NB; q++) {
@@ -895,13 +1033,14 @@ __device__ __forceinline__ void sandwich_w2(const SWTask& t, const SWItem* __res
           for (int i = 0; i < 4; i++) t1[a][q][i] = xr[16 * q + pk[i]] * coef;
       }
     }
-    if (B) {
+    {
+      const __amdgpu_buffer_rsrc_t rb = block_rsrc(B, mb * mb);
       T bb[PB][NB];
 #pragma unroll
       for (int g = 0; g < PB; g++)
 #pragma unroll
         for (int tq = 0; tq < NB; tq++)
-          bb[g][tq] = gload(B + (int64_t)(16 * (g / 4) + pk[g % 4]) * mb + pc + 16 * tq);
+          bb[g][tq] = bload<T>(rb, bo[g] + 16 * tq * (int)sizeof(T), 0);
 #pragma unroll
       for (int g = 0; g < 4 * NB; g++) {
         T bv[NB];
@@ -911,7 +1050,7 @@ __device__ __forceinline__ void sandwich_w2(const SWTask& t, const SWItem* __res
           const int gn = g + PB;
 #pragma unroll
           for (int tq = 0; tq < NB; tq++)
-            bb[g % PB][tq] = gload(B + (int64_t)(16 * (gn / 4) + pk[gn % 4]) * mb + pc + 16 * tq);
+            bb[g % PB][tq] = bload<T>(rb, bo[gn % 4] + 16 * tq * (int)sizeof(T), (gn / 4) * bstep);
         }
 #pragma unroll
         for (int tq = 0; tq < NB; tq++)
@@ -919,11 +1058,6 @@ __device__ __forceinline__ void sandwich_w2(const SWTask& t, const SWItem* __res
           for (int a = 0; a < 2; a++) acc[a][tq] = mfma16(bv[tq], t1[a][g / 4][g % 4], acc[a][tq]);
         __builtin_amdgcn_sched_barrier(0);
       }
-    } else {
-#pragma unroll
-      for (int a = 0; a < 2; a++)
-#pragma unroll
-        for (int q = 0; q < NB; q++) acc[a][q] += t1[a][q];
     }
   }
 #pragma unroll
@@ -957,7 +1091,7 @@ __global__ __launch_bounds__(256) void k_sandwich_w2(const SWTask* __restrict__ 
 // nodes of several problem instances): the kind of each unit selects the body.
 // Sandwich: wu.w = NB (legs multiples of 16, mb = 16 NB <= 64) or 0 (generic).
 template <typename T>
-__global__ __launch_bounds__(256) void k_batch_sandwich(const SWTask* __restrict__ tasks,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_batch_sandwich(const SWTask* __restrict__ tasks,
                                                         const SWItem* __restrict__ items,
                                                         const int4* __restrict__ wus) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -970,10 +1104,10 @@ __global__ __launch_bounds__(256) void k_batch_sandwich(const SWTask* __restrict
       else
         sandwich_gen_elem<T>(t, items, wu.y, wu.z + threadIdx.x, nullptr);
       break;
-    case 1: sandwich_mfma<T, 1>(t, items, wu, nullptr, smem_raw); break;
-    case 2: sandwich_mfma<T, 2>(t, items, wu, nullptr, smem_raw); break;
-    case 3: sandwich_mfma<T, 3>(t, items, wu, nullptr, smem_raw); break;
-    case 4: sandwich_mfma<T, 4>(t, items, wu, nullptr, smem_raw); break;
+    case 1: sandwich_any<T, 1>(t, items, wu, smem_raw); break;
+    case 2: sandwich_any<T, 2>(t, items, wu, smem_raw); break;
+    case 3: sandwich_any<T, 3>(t, items, wu, smem_raw); break;
+    case 4: sandwich_any<T, 4>(t, items, wu, smem_raw); break;
     default: break;
   }
 }
@@ -1078,10 +1212,10 @@ __device__ __noinline__ void pm_sandwich(const SWTask* tp, const SWItem* items_,
       else
         sandwich_gen_elem<T>(t, items, s, z + threadIdx.x, nullptr);
       break;
-    case 1: sandwich_mfma<T, 1>(t, items, wu, nullptr, smem_raw); break;
-    case 2: sandwich_mfma<T, 2>(t, items, wu, nullptr, smem_raw); break;
-    case 3: sandwich_mfma<T, 3>(t, items, wu, nullptr, smem_raw); break;
-    case 4: sandwich_mfma<T, 4>(t, items, wu, nullptr, smem_raw); break;
+    case 1: sandwich_any<T, 1>(t, items, wu, smem_raw); break;
+    case 2: sandwich_any<T, 2>(t, items, wu, smem_raw); break;
+    case 3: sandwich_any<T, 3>(t, items, wu, smem_raw); break;
+    case 4: sandwich_any<T, 4>(t, items, wu, smem_raw); break;
     default: break;
   }
 }
@@ -1186,10 +1320,14 @@ void k_batch_matvec(const PMArgs a) {
 // ============================================================================ launchers
 template <typename T, int NB>
 static hipError_t sand_launch(const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
-                              int ma, const void* xbase, hipStream_t s, const SWOut* outs) {
-  const size_t lds = (size_t)ma * (16 * NB + 2) * sizeof(T);
-  hipLaunchKernelGGL((k_sandwich<T, NB>), dim3(nwu), dim3(256), lds, s, tasks, items, wus,
-                     (const T*)xbase, outs);
+                              int ma, int mb, const void* xbase, hipStream_t s, const SWOut* outs) {
+  const size_t lds = sw_mfma_lds(ma, 16 * NB, sizeof(T));
+  if (ma == 16 * NB && mb == 16 * NB)
+    hipLaunchKernelGGL((k_sandwich<T, NB, true>), dim3(nwu), dim3(64 * sw_strips(ma)), lds, s, tasks, items, wus,
+                       (const T*)xbase, outs);
+  else
+    hipLaunchKernelGGL((k_sandwich<T, NB, false>), dim3(nwu), dim3(64 * sw_strips(ma)), lds, s, tasks, items, wus,
+                       (const T*)xbase, outs);
   return hipGetLastError();
 }
 
@@ -1197,7 +1335,7 @@ template <int NB>
 static hipError_t sand_bf2_launch(const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
                                   int ma, const void* xbase, hipStream_t s) {
   const size_t lds = (size_t)2 * (16 * NB) * (ma + 8) * sizeof(__bf16);
-  hipLaunchKernelGGL((k_sandwich_bf2<NB>), dim3(nwu), dim3(256), lds, s, tasks, items, wus,
+  hipLaunchKernelGGL((k_sandwich_bf2<NB>), dim3(nwu), dim3(64 * sw_strips(ma)), lds, s, tasks, items, wus,
                      (const float*)xbase);
   return hipGetLastError();
 }
@@ -1241,22 +1379,22 @@ hipError_t launch_sandwich(int dtype, int ma, int mb, const SWTask* tasks, const
     }
     return hipErrorInvalidValue;
   }
-  const bool mf = (ma % 16 == 0) && (mb % 16 == 0) && ma <= 128 && mb <= 128;
+  const bool mf = sw_on_mfma(ma, mb);
   if (dtype == 0) {
     if (!mf) {
       hipLaunchKernelGGL(k_sandwich_gen<double>, dim3(nwu), dim3(256), gen_slice_lds(ma, mb, 8), s, tasks, items,
                          wus, (const double*)xbase);
       return hipGetLastError();
     }
-    switch (mb / 16) {
-      case 1: return sand_launch<double, 1>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 2: return sand_launch<double, 2>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 3: return sand_launch<double, 3>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 4: return sand_launch<double, 4>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 5: return sand_launch<double, 5>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 6: return sand_launch<double, 6>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 7: return sand_launch<double, 7>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 8: return sand_launch<double, 8>(tasks, items, wus, nwu, ma, xbase, s, outs);
+    switch (sw_strips(mb)) {
+      case 1: return sand_launch<double, 1>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 2: return sand_launch<double, 2>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 3: return sand_launch<double, 3>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 4: return sand_launch<double, 4>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 5: return sand_launch<double, 5>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 6: return sand_launch<double, 6>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 7: return sand_launch<double, 7>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 8: return sand_launch<double, 8>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
     }
   } else {
     if (!mf) {
@@ -1264,15 +1402,15 @@ hipError_t launch_sandwich(int dtype, int ma, int mb, const SWTask* tasks, const
                          wus, (const float*)xbase);
       return hipGetLastError();
     }
-    switch (mb / 16) {
-      case 1: return sand_launch<float, 1>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 2: return sand_launch<float, 2>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 3: return sand_launch<float, 3>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 4: return sand_launch<float, 4>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 5: return sand_launch<float, 5>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 6: return sand_launch<float, 6>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 7: return sand_launch<float, 7>(tasks, items, wus, nwu, ma, xbase, s, outs);
-      case 8: return sand_launch<float, 8>(tasks, items, wus, nwu, ma, xbase, s, outs);
+    switch (sw_strips(mb)) {
+      case 1: return sand_launch<float, 1>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 2: return sand_launch<float, 2>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 3: return sand_launch<float, 3>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 4: return sand_launch<float, 4>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 5: return sand_launch<float, 5>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 6: return sand_launch<float, 6>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 7: return sand_launch<float, 7>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 8: return sand_launch<float, 8>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
     }
   }
   return hipErrorInvalidValue;
@@ -1308,14 +1446,22 @@ hipError_t batch_matvec_occupancy(int dtype, size_t lds, int* per_cu) {
 hipError_t prepare_sandwich_attributes() {
   const void* fns[] = {
       (const void*)k_batch_sandwich<double>, (const void*)k_batch_sandwich<float>,
-      (const void*)k_sandwich<double, 1>, (const void*)k_sandwich<double, 2>,
-      (const void*)k_sandwich<double, 3>, (const void*)k_sandwich<double, 4>,
-      (const void*)k_sandwich<double, 5>, (const void*)k_sandwich<double, 6>,
-      (const void*)k_sandwich<double, 7>, (const void*)k_sandwich<double, 8>,
-      (const void*)k_sandwich<float, 1>, (const void*)k_sandwich<float, 2>,
-      (const void*)k_sandwich<float, 3>, (const void*)k_sandwich<float, 4>,
-      (const void*)k_sandwich<float, 5>, (const void*)k_sandwich<float, 6>,
-      (const void*)k_sandwich<float, 7>, (const void*)k_sandwich<float, 8>,
+      (const void*)k_sandwich<double, 1, true>, (const void*)k_sandwich<double, 1, false>,
+      (const void*)k_sandwich<double, 2, true>, (const void*)k_sandwich<double, 2, false>,
+      (const void*)k_sandwich<double, 3, true>, (const void*)k_sandwich<double, 3, false>,
+      (const void*)k_sandwich<double, 4, true>, (const void*)k_sandwich<double, 4, false>,
+      (const void*)k_sandwich<double, 5, true>, (const void*)k_sandwich<double, 5, false>,
+      (const void*)k_sandwich<double, 6, true>, (const void*)k_sandwich<double, 6, false>,
+      (const void*)k_sandwich<double, 7, true>, (const void*)k_sandwich<double, 7, false>,
+      (const void*)k_sandwich<double, 8, true>, (const void*)k_sandwich<double, 8, false>,
+      (const void*)k_sandwich<float, 1, true>, (const void*)k_sandwich<float, 1, false>,
+      (const void*)k_sandwich<float, 2, true>, (const void*)k_sandwich<float, 2, false>,
+      (const void*)k_sandwich<float, 3, true>, (const void*)k_sandwich<float, 3, false>,
+      (const void*)k_sandwich<float, 4, true>, (const void*)k_sandwich<float, 4, false>,
+      (const void*)k_sandwich<float, 5, true>, (const void*)k_sandwich<float, 5, false>,
+      (const void*)k_sandwich<float, 6, true>, (const void*)k_sandwich<float, 6, false>,
+      (const void*)k_sandwich<float, 7, true>, (const void*)k_sandwich<float, 7, false>,
+      (const void*)k_sandwich<float, 8, true>, (const void*)k_sandwich<float, 8, false>,
       (const void*)k_sandwich_bf2<2>, (const void*)k_sandwich_bf2<4>,
       (const void*)k_sandwich_bf2w<2, 2>, (const void*)k_sandwich_bf2w<2, 4>,
       (const void*)k_sandwich_bf2w<4, 2>, (const void*)k_sandwich_bf2d<4, 4>,
