@@ -17,6 +17,7 @@
 //    stacked lists (split over the summed index, partials summed in order).
 #include <array>
 #include <map>
+#include <unordered_map>
 
 #include "measure.hpp"
 #include "runtime.hpp"
@@ -26,45 +27,81 @@ using namespace rt;
 
 namespace {
 
+// Device memory of one scope of the engine, taken from a workspace of the
+// handle and given back to it at the end of the scope (every launch and upload
+// runs in order on one stream, so the next scope may write it at once).
 struct Buf {
-  std::vector<void*> ptrs;
-  double* get(int64_t n) {
-    void* p = nullptr;
-    HIPCHK(hipMalloc(&p, std::max<int64_t>(n, 1) * sizeof(double)));
-    ptrs.push_back(p);
-    return (double*)p;
-  }
-  ~Buf() {
-    for (void* p : ptrs) (void)hipFree(p);
-  }
+  Workspace& w;
+  Workspace::Mark m;
+  explicit Buf(Workspace& ws) : w(ws), m(ws.mark()) {}
+  Buf(const Buf&) = delete;
+  double* get(int64_t n) { return (double*)w.get((size_t)std::max<int64_t>(n, 1) * sizeof(double)); }
+  ~Buf() { w.reset(m); }
 };
 
 template <typename T>
-T* upload_tmp(Buf& b, const std::vector<T>& v) {
-  double* p = b.get((int64_t)((v.size() * sizeof(T) + 7) / 8));
-  HIPCHK(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
-  return (T*)p;
+T* upload_tmp(attn_handle* h, Buf& b, const std::vector<T>& v, hipStream_t s) {
+  T* p = (T*)b.w.get(std::max<size_t>(v.size() * sizeof(T), 8));
+  h->xstage.upload(p, v.data(), v.size() * sizeof(T), s);
+  return p;
 }
 
-// GEMM jobs of one launch and their work units
+// GEMM jobs of one launch.  A launch with few 64 x 64 tiles of a long
+// contraction is cut along K into partial products (about 1024 work units, at
+// least 128 of K each), summed in order by a second launch: a single tile walks
+// K at the latency of its loads (K = 1024: 77 us).
 struct GemmList {
   std::vector<GMJob> jobs;
-  std::vector<int4> wus;
+  std::vector<int> batches;
   void add(const GMJob& j, int batch) {
-    const int id = (int)jobs.size();
     jobs.push_back(j);
-    const int tm = (j.M + 63) / 64, tn = (j.N + 63) / 64;
-    for (int b = 0; b < batch; b++)
-      for (int x = 0; x < tm; x++)
-        for (int y = 0; y < tn; y++) wus.push_back(int4{id, b, x, y});
+    batches.push_back(batch);
   }
-  void run(Buf& buf, hipStream_t s) {
+  void run(attn_handle* h, Buf& buf, hipStream_t s) {
     if (jobs.empty()) return;
-    GMJob* dj = upload_tmp(buf, jobs);
-    int4* dw = upload_tmp(buf, wus);
+    int64_t units = 0;
+    for (size_t i = 0; i < jobs.size(); i++)
+      units += (int64_t)batches[i] * ((jobs[i].M + 63) / 64) * ((jobs[i].N + 63) / 64);
+    const int64_t want = std::max<int64_t>(1, 1024 / units);
+    std::vector<GMJob> out;
+    std::vector<int4> wus;
+    std::vector<SPJob> sums;
+    int64_t maxn = 0;
+    for (size_t i = 0; i < jobs.size(); i++) {
+      const GMJob& j = jobs[i];
+      const int nb = batches[i], tm = (j.M + 63) / 64, tn = (j.N + 63) / 64;
+      const int64_t n = (int64_t)j.M * j.N;
+      const bool whole = j.ldc == j.N && (nb == 1 || j.sc == n) && !j.accumulate;   // one contiguous result
+      const int q = whole ? (int)std::max<int64_t>(1, std::min<int64_t>(want, j.K / 128)) : 1;
+      const int kc = ((j.K + q - 1) / q + 15) / 16 * 16;
+      double* part = q > 1 ? buf.get(q * nb * n) : nullptr;
+      int nq = 0;
+      for (int k0 = 0; k0 < j.K; k0 += kc, nq++) {
+        GMJob c = j;
+        c.K = std::min(kc, j.K - k0);
+        c.A += j.ta ? (int64_t)k0 * j.lda : k0;
+        c.B += j.tb ? k0 : (int64_t)k0 * j.ldb;
+        if (part) { c.C = part + (int64_t)nq * nb * n; c.sc = n; }
+        const int id = (int)out.size();
+        out.push_back(c);
+        for (int b = 0; b < nb; b++)
+          for (int x = 0; x < tm; x++)
+            for (int y = 0; y < tn; y++) wus.push_back(int4{id, b, x, y});
+      }
+      if (part) {
+        sums.push_back(SPJob{part, j.C, nb * n, nb * n, nq, 0});
+        maxn = std::max(maxn, nb * n);
+      }
+    }
+    GMJob* dj = upload_tmp(h, buf, out, s);
+    int4* dw = upload_tmp(h, buf, wus, s);
     HIPCHK(launch_gemm_jobs(dj, dw, (int)wus.size(), s));
+    if (!sums.empty()) {
+      SPJob* ds = upload_tmp(h, buf, sums, s);
+      HIPCHK(launch_sum_parts(ds, (int)sums.size(), maxn, s));
+    }
     jobs.clear();
-    wus.clear();
+    batches.clear();
   }
 };
 
@@ -121,13 +158,23 @@ void XEngine::run(const std::vector<XProd>& prods, std::vector<double>& out, hip
   const int dd = d * d;
   out.assign(prods.size(), 0.0);
   if (prods.empty()) return;
-  Buf buf;
-  double* d_ops = upload_tmp(buf, ops.empty() ? std::vector<double>(1, 0.0) : ops);
+  // an earlier run that failed may have left work on the stream
+  HIPCHK(hipStreamSynchronize(s));
+  h->xstage.used = 0;
+  Buf buf(h->xkeep);   // to the end of the run
+  double* d_ops = upload_tmp(h, buf, ops.empty() ? std::vector<double>(1, 0.0) : ops, s);
   auto Tptr = [&](int n) { return h->d_T + h->T_off[n]; };
 
   // ---- images (content-keyed) and, per product, its lowest common node
   std::vector<Img> imgs;
-  std::map<std::pair<int, std::vector<std::pair<int, int>>>, int> memo;
+  struct KeyHash {
+    size_t operator()(const std::pair<int, std::vector<std::pair<int, int>>>& k) const {
+      size_t v = (size_t)k.first * 0x9E3779B97F4A7C15ull;
+      for (auto& x : k.second) v = (v ^ ((size_t)x.first << 32 | (unsigned)x.second)) * 0x100000001B3ull;
+      return v;
+    }
+  };
+  std::unordered_map<std::pair<int, std::vector<std::pair<int, int>>>, int, KeyHash> memo;
   std::function<int(int, const std::vector<std::pair<int, int>>&)> image =
       [&](int edge, const std::vector<std::pair<int, int>>& fs) -> int {
     auto key = std::make_pair(edge, fs);
@@ -160,7 +207,7 @@ void XEngine::run(const std::vector<XProd>& prods, std::vector<double>& out, hip
   };
   struct Eval {
     std::vector<int> L, R;   // distinct image ids (-1 = identity)
-    std::map<int, int> li, ri;
+    std::unordered_map<int, int> li, ri;
   };
   std::map<int, Eval> evals;
   std::vector<std::array<int, 3>> where(prods.size());   // (node, left index, right index)
@@ -237,7 +284,7 @@ void XEngine::run(const std::vector<XProd>& prods, std::vector<double>& out, hip
         need += 2 * M;
         chunk.push_back(todo[k++]);
       }
-      Buf lb;   // freed (after the device has finished with it) at the end of the chunk
+      Buf lb(h->xtmp);   // to the end of the chunk
       double* z = lb.get(need);
       GemmList ga, gb, gc;
       int64_t off = 0;
@@ -261,9 +308,9 @@ void XEngine::run(const std::vector<XProd>& prods, std::vector<double>& out, hip
         }
         gc.add(gm(T, cur, im.dev, dp, dp, dl * dr, dp, dp, dp, 1, 0), 1);
       }
-      ga.run(lb, s);
-      gb.run(lb, s);
-      gc.run(lb, s);
+      ga.run(h, lb, s);
+      gb.run(h, lb, s);
+      gc.run(h, lb, s);
     }
   }
   // ---- Gram matrices of the parent links, from the root down
@@ -276,7 +323,7 @@ void XEngine::run(const std::vector<XProd>& prods, std::vector<double>& out, hip
     int64_t off = 0;
     for (int n = 0; n < nn; n++) { G[n] = gs + off; off += (int64_t)tr.nodes[n].dims[2] * tr.nodes[n].dims[2]; }
     const double one = 1.0;
-    HIPCHK(hipMemcpy(G[tr.root], &one, sizeof(double), hipMemcpyHostToDevice));
+    h->xstage.upload(G[tr.root], &one, sizeof(double), s);
   }
   for (int dep = 0; dep <= dmax; dep++) {
     std::vector<int> lvl;
@@ -285,7 +332,7 @@ void XEngine::run(const std::vector<XProd>& prods, std::vector<double>& out, hip
     GemmList gw, gg;
     std::vector<PMJob> pm;
     int64_t maxM = 0;
-    Buf lb;
+    Buf lb(h->xtmp);
     for (int n : lvl) {
       const Node& nd = tr.nodes[n];
       const int dl = nd.dims[0], dr = nd.dims[1], dp = nd.dims[2];
@@ -304,126 +351,175 @@ void XEngine::run(const std::vector<XProd>& prods, std::vector<double>& out, hip
         gg.add(gm(tp, wp, G[nd.child[1]], dr, dr, dl * dp, dl * dp, dl * dp, dr, 0, 1), 1);
       }
     }
-    gw.run(lb, s);
+    gw.run(h, lb, s);
     if (!pm.empty()) {
-      PMJob* dpm = upload_tmp(lb, pm);
+      PMJob* dpm = upload_tmp(h, lb, pm, s);
       HIPCHK(launch_permute_jobs(dpm, (int)pm.size(), maxM, s));
     }
-    gg.run(lb, s);
+    gg.run(h, lb, s);
   }
   // ---- closing products at every lowest common node.  The needed (left,
   // right) pairs of a node are evaluated either as all pairs of two stacked
   // lists (one matrix product, when most pairs are needed) or pair by pair
-  // (when the images are specific to single products); the stacked images
-  // are formed in groups that fit kUVBudget doubles.
-  const int64_t kUVBudget = (int64_t)1 << 28;
-  std::map<int, std::map<std::pair<int, int>, double>> vals;
+  // (when the images are specific to single products).  Nodes are closed in
+  // groups that share their launches, as many as kGroup doubles of stacked
+  // images hold; a node above that on its own, in blocks of kUVBudget doubles.
+  // The values stay on the device until one copy at the end.
+  const int64_t kUVBudget = (int64_t)1 << 28, kGroup = (int64_t)1 << 24;
+  struct Close {
+    int n;
+    bool all;        // all pairs; else the sorted list
+    int64_t M, off;  // values at res + off
+    std::vector<std::pair<int, int>> pairs;
+  };
   std::map<int, std::vector<std::pair<int, int>>> needed;
   for (size_t p = 0; p < prods.size(); p++) needed[where[p][0]].push_back({where[p][1], where[p][2]});
+  std::vector<Close> cl_nodes;
+  std::vector<int> close_of(nn, -1);
+  int64_t n_res = 0;
   for (auto& kv : needed) {
-    std::sort(kv.second.begin(), kv.second.end());
-    kv.second.erase(std::unique(kv.second.begin(), kv.second.end()), kv.second.end());
+    std::vector<std::pair<int, int>>& pr = kv.second;
+    std::sort(pr.begin(), pr.end());
+    pr.erase(std::unique(pr.begin(), pr.end()), pr.end());
+    const Node& nd = tr.nodes[kv.first];
+    const Eval& ev = evals[kv.first];
+    Close c;
+    c.n = kv.first;
+    c.M = (int64_t)nd.dims[0] * nd.dims[1] * nd.dims[2];
+    c.all = (int64_t)ev.L.size() * (int64_t)ev.R.size() <= 4 * (int64_t)pr.size();
+    c.off = n_res;
+    n_res += c.all ? (int64_t)ev.L.size() * (int64_t)ev.R.size() : (int64_t)pr.size();
+    c.pairs.swap(pr);
+    close_of[c.n] = (int)cl_nodes.size();
+    cl_nodes.push_back(std::move(c));
   }
-  for (auto& kv : evals) {
-    const int n = kv.first;
-    const Eval& ev = kv.second;
-    const Node& nd = tr.nodes[n];
-    const int dl = nd.dims[0], dr = nd.dims[1], dp = nd.dims[2];
-    const int64_t M = (int64_t)dl * dr * dp;
-    const int nl = (int)ev.L.size(), nr = (int)ev.R.size();
-    const std::vector<std::pair<int, int>>& pairs = needed[n];
-    std::map<std::pair<int, int>, double>& out_n = vals[n];
-    Buf nb;   // this node's stacked images and partials
-    // U_i = R_l^T x_l T (or T), V_j = R_r x_r W (or W), written at given addresses
-    auto make_u = [&](GemmList& g, int i, double* dst) {
-      if (ev.L[i] < 0) HIPCHK(launch_copy(dst, Tptr(n), M, s));
-      else g.add(gm(imgs[ev.L[i]].dev, Tptr(n), dst, dl, dr * dp, dl, dl, dr * dp, dr * dp, 1, 0), 1);
+  double* res = buf.get(n_res);
+  // U_i = R_l^T x_l T (or T), V_j = R_r x_r W (or W), written at given addresses
+  auto make_u = [&](GemmList& g, const Close& c, int i, double* dst) {
+    const Node& nd = tr.nodes[c.n];
+    const int dl = nd.dims[0], dr = nd.dims[1], dp = nd.dims[2], im = evals[c.n].L[i];
+    if (im < 0) HIPCHK(launch_copy(dst, Tptr(c.n), c.M, s));
+    else g.add(gm(imgs[im].dev, Tptr(c.n), dst, dl, dr * dp, dl, dl, dr * dp, dr * dp, 1, 0), 1);
+  };
+  auto make_v = [&](GemmList& g, const Close& c, int j, double* dst) {
+    const Node& nd = tr.nodes[c.n];
+    const int dl = nd.dims[0], dr = nd.dims[1], dp = nd.dims[2], im = evals[c.n].R[j];
+    if (im < 0) HIPCHK(launch_copy(dst, W[c.n], c.M, s));
+    else g.add(gm(imgs[im].dev, W[c.n], dst, dr, dp, dr, dr, dp, dp, 0, 0, 0, (int64_t)dr * dp, (int64_t)dr * dp), dl);
+  };
+  size_t k0 = 0;
+  while (k0 < cl_nodes.size()) {
+    // a group of small nodes
+    size_t k1 = k0;
+    int64_t need = 0;
+    auto size_of = [&](const Close& c) {
+      return ((int64_t)evals[c.n].L.size() + (int64_t)evals[c.n].R.size()) * c.M;
     };
-    auto make_v = [&](GemmList& g, int j, double* dst) {
-      if (ev.R[j] < 0) HIPCHK(launch_copy(dst, W[n], M, s));
-      else
-        g.add(gm(imgs[ev.R[j]].dev, W[n], dst, dr, dp, dr, dr, dp, dp, 0, 0, 0, (int64_t)dr * dp, (int64_t)dr * dp),
-              dl);
-    };
-    const int64_t cap = std::max<int64_t>(2, kUVBudget / M);   // stacked vectors held at once
-    if ((int64_t)nl * nr <= 4 * (int64_t)pairs.size()) {
-      // all pairs: C (nl x nr) block by block
+    while (k1 < cl_nodes.size() && need + size_of(cl_nodes[k1]) <= kGroup) need += size_of(cl_nodes[k1++]);
+    if (k1 > k0) {
+      Buf nb(h->xtmp);
+      double* at = nb.get(need);
+      GemmList images, products;
+      std::vector<double*> base;
+      for (size_t k = k0; k < k1; k++) {
+        const Close& c = cl_nodes[k];
+        const int nl = (int)evals[c.n].L.size(), nr = (int)evals[c.n].R.size();
+        base.push_back(at);
+        for (int i = 0; i < nl; i++) make_u(images, c, i, at + i * c.M);
+        for (int j = 0; j < nr; j++) make_v(images, c, j, at + (nl + j) * c.M);
+        if (c.all)
+          products.add(gm(at, at + nl * c.M, res + c.off, nl, nr, (int)c.M, (int)c.M, (int)c.M, nr, 0, 1), 1);
+        at += (int64_t)(nl + nr) * c.M;
+      }
+      images.run(h, nb, s);
+      products.run(h, nb, s);
+      for (size_t k = k0; k < k1; k++) {
+        const Close& c = cl_nodes[k];
+        if (c.all) continue;
+        const int nl = (int)evals[c.n].L.size();
+        std::vector<int2> pl;
+        for (auto& pr : c.pairs) pl.push_back(int2{pr.first, nl + pr.second});
+        int2* dpl = upload_tmp(h, nb, pl, s);
+        HIPCHK(launch_pair_dots(base[k - k0], dpl, (int)pl.size(), c.M, res + c.off, s));
+      }
+      k0 = k1;
+      continue;
+    }
+    // one large node, in blocks
+    const Close& c = cl_nodes[k0++];
+    const int nl = (int)evals[c.n].L.size(), nr = (int)evals[c.n].R.size();
+    const int64_t cap = std::max<int64_t>(2, kUVBudget / c.M);   // stacked vectors held at once
+    if (c.all) {
       const int cl = (int)std::max<int64_t>(1, std::min<int64_t>(nl, cap / 2));
       const int cr = (int)std::max<int64_t>(1, std::min<int64_t>(nr, cap - cl));
-      double* U = nb.get((int64_t)cl * M);
-      double* V = nb.get((int64_t)cr * M);
-      std::vector<double> Cn((size_t)nl * nr);
+      Buf nb(h->xtmp);
+      double* U = nb.get((int64_t)cl * c.M);
+      double* V = nb.get((int64_t)cr * c.M);
       for (int i0 = 0; i0 < nl; i0 += cl) {
         const int ml = std::min(cl, nl - i0);
+        Buf ub(h->xtmp);
         GemmList gu;
-        for (int i = 0; i < ml; i++) make_u(gu, i0 + i, U + (int64_t)i * M);
-        gu.run(nb, s);
+        for (int i = 0; i < ml; i++) make_u(gu, c, i0 + i, U + (int64_t)i * c.M);
+        gu.run(h, ub, s);
         for (int j0 = 0; j0 < nr; j0 += cr) {
           const int mr = std::min(cr, nr - j0);
-          GemmList gv;
-          for (int j = 0; j < mr; j++) make_v(gv, j0 + j, V + (int64_t)j * M);
-          gv.run(nb, s);
-          const int64_t tiles = (int64_t)((ml + 63) / 64) * ((mr + 63) / 64);
-          int nq = (int)std::max<int64_t>(1, std::min<int64_t>({256, M / 2048, std::max<int64_t>(1, 1024 / tiles)}));
-          const int64_t kc = (M + nq - 1) / nq;
-          nq = (int)((M + kc - 1) / kc);
-          double* part = nb.get((int64_t)nq * ml * mr);
-          double* Cb = nb.get((int64_t)ml * mr);
-          GemmList gp;
-          for (int q = 0; q < nq; q++) {
-            const int64_t k0 = (int64_t)q * kc;
-            const int K = (int)std::min<int64_t>(kc, M - k0);
-            gp.add(gm(U + k0, V + k0, part + (int64_t)q * ml * mr, ml, mr, K, (int)M, (int)M, mr, 0, 1), 1);
+          Buf vb(h->xtmp);
+          GemmList gv, gp;
+          for (int j = 0; j < mr; j++) make_v(gv, c, j0 + j, V + (int64_t)j * c.M);
+          gv.run(h, vb, s);
+          // the block, then its rows to their places
+          double* Cb = vb.get((int64_t)ml * mr);
+          gp.add(gm(U, V, Cb, ml, mr, (int)c.M, (int)c.M, (int)c.M, mr, 0, 1), 1);
+          gp.run(h, vb, s);
+          if (mr == nr) {
+            HIPCHK(launch_copy(res + c.off + (int64_t)i0 * nr, Cb, (int64_t)ml * mr, s));
+          } else {
+            for (int i = 0; i < ml; i++)
+              HIPCHK(launch_copy(res + c.off + (int64_t)(i0 + i) * nr + j0, Cb + (int64_t)i * mr, mr, s));
           }
-          gp.run(nb, s);
-          std::vector<SPJob> sp(1, SPJob{part, Cb, (int64_t)ml * mr, (int64_t)ml * mr, nq, 0});
-          SPJob* dsp = upload_tmp(nb, sp);
-          HIPCHK(launch_sum_parts(dsp, 1, (int64_t)ml * mr, s));
-          std::vector<double> hb((size_t)ml * mr);
-          HIPCHK(hipMemcpyAsync(hb.data(), Cb, hb.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-          HIPCHK(hipStreamSynchronize(s));
-          for (int i = 0; i < ml; i++)
-            for (int j = 0; j < mr; j++) Cn[(size_t)(i0 + i) * nr + j0 + j] = hb[(size_t)i * mr + j];
         }
       }
-      for (auto& pr : pairs) out_n[pr] = Cn[(size_t)pr.first * nr + pr.second];
     } else {
       // pair by pair, in groups whose distinct images fit the budget
       size_t k = 0;
-      double* UV = nb.get(cap * M);
-      while (k < pairs.size()) {
+      while (k < c.pairs.size()) {
         std::map<int, int> su, sv;
         std::vector<int2> pl;
-        size_t k1 = k;
-        while (k1 < pairs.size()) {
-          const int nu = (int)su.size() + (su.count(pairs[k1].first) ? 0 : 1);
-          const int nv = (int)sv.size() + (sv.count(pairs[k1].second) ? 0 : 1);
-          if (nu + nv > cap && k1 > k) break;
-          if (!su.count(pairs[k1].first)) { const int id = (int)su.size(); su[pairs[k1].first] = id; }
-          if (!sv.count(pairs[k1].second)) { const int id = (int)sv.size(); sv[pairs[k1].second] = id; }
-          k1++;
+        size_t ke = k;
+        while (ke < c.pairs.size()) {
+          const int nu = (int)su.size() + (su.count(c.pairs[ke].first) ? 0 : 1);
+          const int nv = (int)sv.size() + (sv.count(c.pairs[ke].second) ? 0 : 1);
+          if (nu + nv > cap && ke > k) break;
+          if (!su.count(c.pairs[ke].first)) { const int id = (int)su.size(); su[c.pairs[ke].first] = id; }
+          if (!sv.count(c.pairs[ke].second)) { const int id = (int)sv.size(); sv[c.pairs[ke].second] = id; }
+          ke++;
         }
         const int nu = (int)su.size();
+        Buf nb(h->xtmp);
+        double* UV = nb.get((int64_t)(nu + (int)sv.size()) * c.M);
         GemmList gu;
-        for (auto& x : su) make_u(gu, x.first, UV + (int64_t)x.second * M);
-        for (auto& x : sv) make_v(gu, x.first, UV + (int64_t)(nu + x.second) * M);
-        gu.run(nb, s);
-        for (size_t q = k; q < k1; q++) pl.push_back(int2{su[pairs[q].first], nu + sv[pairs[q].second]});
-        int2* dpl = upload_tmp(nb, pl);
-        double* res = nb.get((int64_t)pl.size());
-        HIPCHK(launch_pair_dots(UV, dpl, (int)pl.size(), M, res, s));
-        std::vector<double> hr(pl.size());
-        HIPCHK(hipMemcpyAsync(hr.data(), res, hr.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        for (size_t q = k; q < k1; q++) out_n[pairs[q]] = hr[q - k];
-        k = k1;
+        for (auto& x : su) make_u(gu, c, x.first, UV + (int64_t)x.second * c.M);
+        for (auto& x : sv) make_v(gu, c, x.first, UV + (int64_t)(nu + x.second) * c.M);
+        gu.run(h, nb, s);
+        for (size_t q = k; q < ke; q++) pl.push_back(int2{su[c.pairs[q].first], nu + sv[c.pairs[q].second]});
+        int2* dpl = upload_tmp(h, nb, pl, s);
+        HIPCHK(launch_pair_dots(UV, dpl, (int)pl.size(), c.M, res + c.off + (int64_t)k, s));
+        k = ke;
       }
     }
   }
+  std::vector<double> hres((size_t)n_res);
+  HIPCHK(hipMemcpyAsync(hres.data(), res, hres.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
   for (size_t p = 0; p < prods.size(); p++) {
     const auto& w = where[p];
-    out[p] = vals[w[0]].at({w[1], w[2]});
+    const Close& c = cl_nodes[close_of[w[0]]];
+    const int64_t at = c.all ? (int64_t)w[1] * (int64_t)evals[c.n].R.size() + w[2]
+                             : std::lower_bound(c.pairs.begin(), c.pairs.end(), std::make_pair(w[1], w[2])) - c.pairs.begin();
+    out[p] = hres[(size_t)(c.off + at)];
   }
+  h->xkeep.trim(Workspace::kKeep);
+  h->xtmp.trim(Workspace::kKeep);
 }
 
 }  // namespace rt

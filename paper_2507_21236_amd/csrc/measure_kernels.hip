@@ -26,28 +26,40 @@ __global__ __launch_bounds__(256) void k_gemm_jobs(const GMJob* __restrict__ job
   for (int r = 0; r < 4; r++)
 #pragma unroll
     for (int c = 0; c < 4; c++) acc[r][c] = 0.0;
+  // the next K step is on its way into registers while this one is multiplied
+  double ra[4], rb[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int e = tid + 256 * q;
+      const int i = J.ta ? e & 63 : e >> 4, k = J.ta ? e >> 6 : e & 15;
+      const int gi = m0 + i, gk = k0 + k;
+      const bool in = gi < J.M && gk < J.K;
+      const double v = A[in ? (J.ta ? (int64_t)gk * J.lda + gi : (int64_t)gi * J.lda + gk) : 0];
+      ra[q] = in ? v : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int e = tid + 256 * q;
+      const int j = J.tb ? e >> 4 : e & 63, k = J.tb ? e & 15 : e >> 6;
+      const int gj = n0 + j, gk = k0 + k;
+      const bool in = gj < J.N && gk < J.K;
+      const double v = B[in ? (J.tb ? (int64_t)gj * J.ldb + gk : (int64_t)gk * J.ldb + gj) : 0];
+      rb[q] = in ? v : 0.0;
+    }
+  };
+  load(0);
   for (int k0 = 0; k0 < J.K; k0 += 16) {
 #pragma unroll
     for (int q = 0; q < 4; q++) {
       const int e = tid + 256 * q;
-      int i, k;
-      if (J.ta) { k = e >> 6; i = e & 63; } else { i = e >> 4; k = e & 15; }
-      const int gi = m0 + i, gk = k0 + k;
-      double v = 0.0;
-      if (gi < J.M && gk < J.K) v = J.ta ? A[(int64_t)gk * J.lda + gi] : A[(int64_t)gi * J.lda + gk];
-      As[k][i] = v;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const int e = tid + 256 * q;
-      int j, k;
-      if (J.tb) { j = e >> 4; k = e & 15; } else { k = e >> 6; j = e & 63; }
-      const int gj = n0 + j, gk = k0 + k;
-      double v = 0.0;
-      if (gj < J.N && gk < J.K) v = J.tb ? B[(int64_t)gj * J.ldb + gk] : B[(int64_t)gk * J.ldb + gj];
-      Bs[k][j] = v;
+      if (J.ta) As[e >> 6][e & 63] = ra[q];
+      else As[e & 15][e >> 4] = ra[q];
+      if (J.tb) Bs[e & 15][e >> 4] = rb[q];
+      else Bs[e >> 6][e & 63] = rb[q];
     }
     __syncthreads();
+    if (k0 + 16 < J.K) load(k0 + 16);
 #pragma unroll
     for (int kk = 0; kk < 16; kk++) {
       double a[4], b[4];

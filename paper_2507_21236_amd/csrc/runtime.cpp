@@ -1487,6 +1487,9 @@ attn_status attn_destroy(attn_handle* h) {
     (void)hipSetDevice(h->device);
     (void)hipDeviceSynchronize();
     for (void* p : h->owned) (void)hipFree(p);
+    h->xkeep.trim(0);
+    h->xtmp.trim(0);
+    h->xstage.release();
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     for (auto& g : h->sgraphs) (void)hipGraphExecDestroy(g.exec);
     if (h->gstream) (void)hipStreamDestroy(h->gstream);

@@ -38,6 +38,80 @@ struct StatusFail {
   std::string msg;
 };
 
+// Device memory handed out in order and taken back by marks, kept from one
+// call to the next (an allocation of the size a call needs costs up to
+// hundreds of milliseconds: 8 x 8 m = 32 correlation matrix, 90 to 600 ms a call,
+// 33 ms with it).  Every user runs in order on one stream.  After a call at
+// most kKeep bytes stay; the rest is freed, and all of it with the handle.
+struct Workspace {
+  static constexpr size_t kKeep = (size_t)256 << 20;
+  struct Block { char* p; size_t cap, used; };
+  struct Mark { size_t cur, used; };
+  std::vector<Block> blocks;
+  size_t cur = 0;   // block that serves the next request
+  void* get(size_t bytes) {
+    bytes = (bytes + 255) / 256 * 256;
+    while (cur < blocks.size() && blocks[cur].used + bytes > blocks[cur].cap) {
+      if (cur + 1 == blocks.size()) break;
+      blocks[++cur].used = 0;
+    }
+    if (blocks.empty() || blocks[cur].used + bytes > blocks[cur].cap) {
+      size_t total = 0;
+      for (auto& b : blocks) total += b.cap;
+      const size_t cap = std::max(bytes, std::min<size_t>(std::max<size_t>(total, (size_t)4 << 20), (size_t)128 << 20));
+      void* p = nullptr;
+      HIPCHK(hipMalloc(&p, cap));
+      blocks.push_back({(char*)p, cap, 0});
+      cur = blocks.size() - 1;
+    }
+    void* r = blocks[cur].p + blocks[cur].used;
+    blocks[cur].used += bytes;
+    return r;
+  }
+  Mark mark() const { return {cur, blocks.empty() ? 0 : blocks[cur].used}; }
+  void reset(Mark m) {
+    cur = m.cur;
+    if (cur < blocks.size()) blocks[cur].used = m.used;
+  }
+  // frees blocks from the last one until at most `keep` bytes are left (the device is idle)
+  void trim(size_t keep) {
+    size_t total = 0;
+    for (auto& b : blocks) total += b.cap;
+    while (!blocks.empty() && total > keep) {
+      total -= blocks.back().cap;
+      (void)hipFree(blocks.back().p);
+      blocks.pop_back();
+    }
+    if (cur >= blocks.size()) cur = blocks.empty() ? 0 : blocks.size() - 1;
+  }
+};
+
+// Uploads of work lists through pinned memory, asynchronous and in stream order.
+struct Stage {
+  static constexpr size_t kCap = (size_t)4 << 20;
+  char* p = nullptr;
+  size_t used = 0;
+  void upload(void* dst, const void* src, size_t bytes, hipStream_t s) {
+    if (bytes == 0) return;
+    if (!p) HIPCHK(hipHostMalloc((void**)&p, kCap, hipHostMallocDefault));
+    for (size_t at = 0; at < bytes;) {
+      if (used == kCap) {   // full: what was staged has to leave first
+        HIPCHK(hipStreamSynchronize(s));
+        used = 0;
+      }
+      const size_t n = std::min(bytes - at, kCap - used);
+      std::memcpy(p + used, (const char*)src + at, n);
+      HIPCHK(hipMemcpyAsync((char*)dst + at, p + used, n, hipMemcpyHostToDevice, s));
+      used += n;
+      at += n;
+    }
+  }
+  void release() {
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+  }
+};
+
 // A sandwich launch group: tasks with the same (ma, mb).
 struct SWGroup {
   int ma = 0, mb = 0;
@@ -280,6 +354,9 @@ struct attn_handle {
   };
   hipStream_t gstream = nullptr;
   std::vector<SweepGraph> sgraphs;   // at most two (the first sweep from a fresh state, then the steady one)
+  // observables: memory of a whole run, of its scopes, and the upload stage
+  Workspace xkeep, xtmp;
+  Stage xstage;
   // counters
   int64_t n_matvec = 0, n_env = 0, n_qr = 0;
   double mv_flops = 0;
