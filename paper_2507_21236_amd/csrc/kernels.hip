@@ -24,6 +24,25 @@ __device__ __forceinline__ void fail_status(KrylovState* st, int v) {
   atomicOr(&st->sticky, v);
 }
 
+// Sum of entry e (et in the transposed layout) of nsrc partial outputs, cut
+// into S groups of consecutive sources.
+template <typename TI>
+__device__ __forceinline__ double sum_sources(const RDSrc* __restrict__ srcs, int k0, int k1, int64_t e, int64_t et) {
+  double acc = 0;
+#pragma unroll 8
+  for (int k = k0; k < k1; k++) {
+    const TI* src = (const TI*)srcs[k].p;
+    acc += (double)(srcs[k].layout ? src[et] : src[e]);
+  }
+  return acc;
+}
+template <typename TI>
+__device__ __forceinline__ double sum_grouped(const RDSrc* __restrict__ srcs, int nsrc, int S, int64_t e, int64_t et) {
+  double acc = sum_sources<TI>(srcs, 0, nsrc / S, e, et);
+  for (int g = 1; g < S; g++) acc += sum_sources<TI>(srcs, nsrc * g / S, nsrc * (g + 1) / S, e, et);
+  return acc;
+}
+
 // ============================================================================ mode product
 // (device bodies: mode_body.hpp)
 template <typename T, int NI, int QS, int FT>
@@ -139,9 +158,8 @@ __global__ __launch_bounds__(256) void k_reduce_list(const RDTask* __restrict__ 
     const int64_t rem = e - l * t.mr * t.mp;
     const int64_t r = rem / t.mp, p = rem - r * t.mp;
     const int64_t et = p * t.ml * t.mr + l * t.mr + r;
-    double acc = 0;
-    for (int k = 0; k < t.nsrc; k++) acc += (double)((const TI*)t.srcs[k].p)[t.srcs[k].layout ? et : e];
-    ((TO*)t.y)[e] = (TO)acc;
+    // FP32 partial outputs are summed in one run, as the low-precision solves do
+    ((TO*)t.y)[e] = (TO)sum_grouped<TI>(t.srcs, t.nsrc, sizeof(TI) == 8 ? sum_groups(M) : 1, e, et);
   }
 }
 
@@ -393,23 +411,37 @@ __global__ __launch_bounds__(256) void k_combine(const CBTask* __restrict__ task
   ((double*)t.out)[e] = acc;
 }
 
+// Sum of the partial outputs of one entry by the S = 1024 / c threads that
+// share it (thread g c + i: group g of entry e0 + i of the block's c entries):
+// the total is returned in thread i < c.  part holds 1024 values.
+template <typename TI>
+__device__ __forceinline__ double sum_split(const RDSrc* __restrict__ srcs, int nsrc, int c, int64_t e, int64_t et,
+                                            bool on, double* part) {
+  const int S = 1024 / c, g = threadIdx.x / c;
+  double acc = on ? sum_sources<TI>(srcs, nsrc * g / S, nsrc * (g + 1) / S, e, et) : 0.0;
+  if (S == 1) return acc;
+  __syncthreads();
+  part[threadIdx.x] = acc;
+  __syncthreads();
+  if ((int)threadIdx.x < c)
+    for (int q = 1; q < S; q++) acc += part[q * c + threadIdx.x];
+  return acc;
+}
+
+// y = sum of the partial outputs, c entries per block of 1024 threads
 template <typename TI, typename TO>
-__global__ __launch_bounds__(256) void k_reduce_out(const RDSrc* __restrict__ srcs, int nsrc,
-                                                    TO* __restrict__ y, int ml, int mr, int mp) {
+__global__ __launch_bounds__(1024) void k_reduce_out(const RDSrc* __restrict__ srcs, int nsrc, int c,
+                                                     TO* __restrict__ y, int ml, int mr, int mp) {
+  __shared__ double part[1024];
   const int64_t M = (int64_t)ml * mr * mp;
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= M) return;
+  const int64_t e = (int64_t)blockIdx.x * c + threadIdx.x % c;
+  const bool on = e < M;
   const int64_t l = e / ((int64_t)mr * mp);
   const int64_t rem = e - l * mr * mp;
   const int64_t r = rem / mp, p = rem - r * mp;
   const int64_t et = p * ml * mr + l * mr + r;
-  double acc = 0;
-#pragma unroll 8
-  for (int k = 0; k < nsrc; k++) {
-    const TI* src = (const TI*)srcs[k].p;
-    acc += (double)(srcs[k].layout ? src[et] : src[e]);
-  }
-  y[e] = (TO)acc;
+  const double acc = sum_split<TI>(srcs, nsrc, c, e, et, on, part);
+  if (on && (int)threadIdx.x < c) y[e] = (TO)acc;
 }
 
 template <typename T>
@@ -632,15 +664,44 @@ __device__ __forceinline__ void block_dots_1k(const KJob& J, const double* __res
   }
 }
 
-// partial dots of V[i0, i0 + nv) with w into area pin (w as the product left it)
-__global__ __launch_bounds__(1024) void k_kdots(const KJob* __restrict__ jobs, int i0, int nv, int pin) {
-  const KJob& J = jobs[blockIdx.y];
-  if (J.st->stop) return;
-  __shared__ double red[16 * kDotChunk];
-  block_dots_1k(J, J.w, i0, nv, parea(J, pin), red);
+// The same dots for a vector of at most 256 c entries, c < 1024: block b holds
+// entries [b c, (b + 1) c), thread g c + i entry i of them, and the groups
+// share out the basis vectors.  we = this thread's entry of w (0 past the end).
+__device__ __forceinline__ void block_dots_split(const KJob& J, double we, int c, int i0, int nv, double* out,
+                                                 double* red) {
+  const int64_t n = J.n;
+  const int S = 1024 / c, g = threadIdx.x / c, i = threadIdx.x - g * c;
+  const int64_t e = (int64_t)blockIdx.x * c + i;
+  const int parts = c > 64 ? c / 64 : 1;   // wavefronts that share a group
+  for (int q = g; q < nv; q += S) {
+    double v = e < n ? J.V[(int64_t)(i0 + q) * n + e] * we : 0.0;
+    for (int off = (c < 64 ? c : 64) / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((i & 63) == 0) red[q * parts + (i >> 6)] = v;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < nv) {
+    double v = red[threadIdx.x * parts];
+    for (int k = 1; k < parts; k++) v += red[threadIdx.x * parts + k];
+    out[threadIdx.x * kRedBlocks + blockIdx.x] = v;
+  }
 }
 
-// w = the sum of the product's partial outputs (per element in the order of
+// partial dots of V[i0, i0 + nv) with w into area pin (w as the product left
+// it); split: entries dealt to the blocks by dot_chunk, else 1024 at a time
+__global__ __launch_bounds__(1024) void k_kdots(const KJob* __restrict__ jobs, int i0, int nv, int pin, int split) {
+  const KJob& J = jobs[blockIdx.y];
+  if (J.st->stop) return;
+  __shared__ double red[64 * kDotChunk];
+  const int c = split ? dot_chunk(J.n) : 1024;
+  if (c == 1024) {
+    block_dots_1k(J, J.w, i0, nv, parea(J, pin), red);
+  } else {
+    const int64_t e = (int64_t)blockIdx.x * c + threadIdx.x % c;
+    block_dots_split(J, e < J.n ? J.w[e] : 0.0, c, i0, nv, parea(J, pin), red);
+  }
+}
+
+// w = the sum of the product's partial outputs (per entry in the order of
 // k_reduce_out), then the partial dots of k_kdots: one launch instead of two
 // (single job; the same bits as k_reduce_out followed by k_kdots)
 __global__ __launch_bounds__(1024) void k_reduce_dots(const RDSrc* __restrict__ srcs, int nsrc,
@@ -648,22 +709,33 @@ __global__ __launch_bounds__(1024) void k_reduce_dots(const RDSrc* __restrict__ 
                                                       int i0, int nv, int pin) {
   const KJob& J = jobs[0];
   const int64_t M = (int64_t)ml * mr * mp;
+  const int c = dot_chunk(M);
   double* w = J.w;
+  __shared__ double red[64 * kDotChunk];
+  if (c < 1024) {
+    __shared__ double part[1024];
+    const int64_t e = (int64_t)blockIdx.x * c + threadIdx.x % c;
+    const int64_t l = e / ((int64_t)mr * mp);
+    const int64_t rem = e - l * mr * mp;
+    const int64_t r = rem / mp, p = rem - r * mp;
+    const double acc = sum_split<double>(srcs, nsrc, c, e, p * ml * mr + l * mr + r, e < M, part);
+    __syncthreads();
+    if ((int)threadIdx.x < c) {
+      part[threadIdx.x] = acc;
+      if (e < M) w[e] = acc;
+    }
+    __syncthreads();
+    if (J.st->stop) return;
+    block_dots_split(J, part[threadIdx.x % c], c, i0, nv, parea(J, pin), red);
+    return;
+  }
   for (int64_t e = (int64_t)blockIdx.x * kDotThreads + threadIdx.x; e < M; e += (int64_t)kRedBlocks * kDotThreads) {
     const int64_t l = e / ((int64_t)mr * mp);
     const int64_t rem = e - l * mr * mp;
     const int64_t r = rem / mp, p = rem - r * mp;
-    const int64_t et = p * ml * mr + l * mr + r;
-    double acc = 0;
-#pragma unroll 8
-    for (int k = 0; k < nsrc; k++) {
-      const double* src = (const double*)srcs[k].p;
-      acc += srcs[k].layout ? src[et] : src[e];
-    }
-    w[e] = acc;
+    w[e] = sum_sources<double>(srcs, 0, nsrc, e, p * ml * mr + l * mr + r);
   }
   if (J.st->stop) return;
-  __shared__ double red[16 * kDotChunk];
   block_dots_1k(J, w, i0, nv, parea(J, pin), red);
 }
 
@@ -2451,15 +2523,15 @@ hipError_t launch_combine(const CBTask* tasks, const CBTerm* terms, int ntask, i
 hipError_t launch_reduce_out(int dtype_in, const RDSrc* srcs, int nsrc, void* y, int dtype_out,
                              int ml, int mr, int mp, hipStream_t s) {
   const int64_t M = (int64_t)ml * mr * mp;
+  // FP32 partials into an FP64 vector (the low-precision solves): one run per entry
+  const int c = dtype_in == 1 && dtype_out == 0 ? 1024 : dot_chunk(M);
+  const dim3 grid((unsigned)((M + c - 1) / c));
   if (dtype_in == 0 && dtype_out == 0)
-    hipLaunchKernelGGL((k_reduce_out<double, double>), dim3(grid1(M)), dim3(256), 0, s, srcs, nsrc,
-                       (double*)y, ml, mr, mp);
+    hipLaunchKernelGGL((k_reduce_out<double, double>), grid, dim3(1024), 0, s, srcs, nsrc, c, (double*)y, ml, mr, mp);
   else if (dtype_in == 1 && dtype_out == 0)
-    hipLaunchKernelGGL((k_reduce_out<float, double>), dim3(grid1(M)), dim3(256), 0, s, srcs, nsrc,
-                       (double*)y, ml, mr, mp);
+    hipLaunchKernelGGL((k_reduce_out<float, double>), grid, dim3(1024), 0, s, srcs, nsrc, c, (double*)y, ml, mr, mp);
   else if (dtype_in == 1 && dtype_out == 1)
-    hipLaunchKernelGGL((k_reduce_out<float, float>), dim3(grid1(M)), dim3(256), 0, s, srcs, nsrc,
-                       (float*)y, ml, mr, mp);
+    hipLaunchKernelGGL((k_reduce_out<float, float>), grid, dim3(1024), 0, s, srcs, nsrc, c, (float*)y, ml, mr, mp);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -2528,8 +2600,8 @@ hipError_t launch_kalpha(const KJob* jobs, int nj, int j, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_kdots(const KJob* jobs, int nj, int i0, int nv, int pin, hipStream_t s) {
-  hipLaunchKernelGGL(k_kdots, dim3(kRedBlocks, nj), dim3(kDotThreads), 0, s, jobs, i0, nv, pin);
+hipError_t launch_kdots(const KJob* jobs, int nj, int i0, int nv, int pin, int split, hipStream_t s) {
+  hipLaunchKernelGGL(k_kdots, dim3(kRedBlocks, nj), dim3(kDotThreads), 0, s, jobs, i0, nv, pin, split);
   return hipGetLastError();
 }
 

@@ -129,6 +129,21 @@ constexpr size_t sw_mfma_lds(int ma, int mb, size_t esz) {
   return (size_t)((ma + 3) / 4 * 4) * (16 * sw_strips(mb) + 2) * esz;
 }
 
+// Elements of a vector of n entries that one block of the dot-product kernels
+// takes at a time (element e belongs to block (e / c) % 256), and the number of
+// groups a sum of partial outputs is cut into (each group in order, then the
+// groups in order).  Up to 2^18 entries a block of 1024 threads has 1024 / c
+// threads per entry, which take the groups: at 4096 entries four blocks held
+// every entry and each thread walked the whole list of sources (147 of them:
+// 36 us, 8 split 64 ways).
+// A function of n alone, so that every form of the sum gives the same bits.
+constexpr int dot_chunk(int64_t n) {
+  int c = 1024;
+  while (c > 16 && (int64_t)c * 128 >= n) c /= 2;
+  return c;
+}
+constexpr int sum_groups(int64_t n) { return 1024 / dot_chunk(n); }
+
 struct RDSrc {
   const void* p;
   int32_t layout;

@@ -37,8 +37,10 @@ hipError_t launch_kinit(const KJob* jobs, int nj, int kmax, hipStream_t s);
 hipError_t launch_knorm(const KJob* jobs, int nj, hipStream_t s);
 hipError_t launch_kscale(const KJob* jobs, int nj, int64_t nmax, int mode, hipStream_t s);
 hipError_t launch_kalpha(const KJob* jobs, int nj, int j, hipStream_t s);
-// partial dots of basis vectors [i0, i0 + nv) with w into partial-sum area pin
-hipError_t launch_kdots(const KJob* jobs, int nj, int i0, int nv, int pin, hipStream_t s);
+// partial dots of basis vectors [i0, i0 + nv) with w into partial-sum area pin;
+// split: entries dealt to the blocks by dot_chunk (FP64 solves), else 1024 at a
+// time (the low-precision solves)
+hipError_t launch_kdots(const KJob* jobs, int nj, int i0, int nv, int pin, int split, hipStream_t s);
 // w = sum of a product's partial outputs, then launch_kdots' partial dots (one job)
 hipError_t launch_reduce_dots(const RDSrc* srcs, int nsrc, const KJob* job, int ml, int mr, int mp, int i0,
                               int nv, int pin, hipStream_t s);

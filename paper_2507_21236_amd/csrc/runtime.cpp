@@ -627,7 +627,7 @@ void matvec_f64(attn_handle* h, int n, const double* x, double* y, hipStream_t s
   run_sw_mv(h, D.sw, 0, x, s);
   if (D.srcs.empty()) {
     HIPCHK(launch_zero(y, (int64_t)D.dims[0] * D.dims[1] * D.dims[2], s));
-    if (J) HIPCHK(launch_kdots(J, 1, i0, nv, pin, s));
+    if (J) HIPCHK(launch_kdots(J, 1, i0, nv, pin, 1, s));
   } else if (J) {
     HIPCHK(launch_reduce_dots(D.d_srcs, (int)D.srcs.size(), J, D.dims[0], D.dims[1], D.dims[2], i0, nv, pin, s));
   } else {
@@ -1131,7 +1131,7 @@ double lanczos(attn_handle* h, int n, int kreq, int precision, int* nmv, hipStre
       matvec_f64(h, n, V + (int64_t)j * Msz, h->d_w, s, J, i0, nv, pin);
     } else {
       matvec_lowp(h, n, precision, h->d_x32, h->d_w, 0, s);
-      HIPCHK(launch_kdots(J, 1, i0, nv, pin, s));
+      HIPCHK(launch_kdots(J, 1, i0, nv, pin, 0, s));
     }
     if (last) {
       HIPCHK(launch_kalpha(J, 1, j, s));

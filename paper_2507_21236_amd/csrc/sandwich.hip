@@ -1155,8 +1155,14 @@ __device__ __forceinline__ void pm_reduce(const RDTask& t, int64_t e0) {
     const int64_t r = rem / t.mp, p = rem - r * t.mp;
     const int64_t et = p * t.ml * t.mr + l * t.mr + r;
     double acc = 0;
+    const int S = sizeof(TI) == 8 ? sum_groups(M) : 1;
+    for (int g = 0; g < S; g++) {
+      double part = 0;
 #pragma unroll 8
-    for (int k = 0; k < t.nsrc; k++) acc += (double)((const TI*)t.srcs[k].p)[t.srcs[k].layout ? et : e];
+      for (int k = t.nsrc * g / S; k < t.nsrc * (g + 1) / S; k++)
+        part += (double)((const TI*)t.srcs[k].p)[t.srcs[k].layout ? et : e];
+      acc = g == 0 ? part : acc + part;
+    }
     ((double*)t.y)[e] = acc;
   }
 }
