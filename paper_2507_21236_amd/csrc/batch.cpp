@@ -126,6 +126,12 @@ int tile_for(const attn_batch* b, int ma, int mb) {
   return 1;
 }
 
+// whether node n of h is solved in one workgroup (as the single-handle path does)
+bool solved_tiny(const attn_batch* b, const attn_handle* h, int n) {
+  return h->mv[n].d_tiny &&
+         (b->precision != ATTN_F64 || tiny_in_lds((int)h->T_len[n], std::min(b->krylov_k, 64)));
+}
+
 // two-strip tiles apply to FP32 legs 64 x 64 in the staged launches
 bool w2_allowed(const attn_batch* b, int ma, int mb) {
   return b->precision == ATTN_F32 && ma == 64 && mb == 64 && b->persistent == 0;
@@ -401,7 +407,7 @@ void build_step(attn_batch* b, int t) {
     for (const CBTerm& c : D.comb.terms) S.cb_terms.push_back(c);
     const int64_t Msz = h->T_len[n];
     S.flops += (double)h->M.mv[n].flops;
-    if (D.d_tiny) {
+    if (solved_tiny(b, h, n)) {
       S.tj.push_back(h->h_tjobs[n]);
       S.tj_minM = std::min(S.tj_minM, (int)Msz);
       S.tj_maxM = std::max(S.tj_maxM, (int)Msz);
@@ -571,7 +577,7 @@ void autotune(attn_batch* b) {
   for (attn_handle* h : b->hs) {
     const Tree& tr = h->M.tree;
     for (int n = 0; n < (int)tr.nodes.size(); n++) {
-      if (h->mv[n].d_tiny) continue;
+      if (solved_tiny(b, h, n)) continue;
       const Node& nd = tr.nodes[n];
       for (const Item2& it : h->M.mv[n].items) {
         int ma, mb, ns;
@@ -599,7 +605,7 @@ void autotune(attn_batch* b) {
         for (int t = 0; t < nsteps && fits; t++) {
           for (int i = 0; i < (int)b->hs.size() && fits; i++) {
             attn_handle* h = b->hs[i];
-            if (t >= (int)h->M.tree.nodes.size() || h->mv[t].d_tiny) continue;
+            if (t >= (int)h->M.tree.nodes.size() || solved_tiny(b, h, t)) continue;
             std::vector<RDSrc> srcs;
             const void* x = b->precision == ATTN_F64 ? (const void*)b->x64[i] : (const void*)h->d_x32;
             add_sandwich(b, h, t, x, ms[t], srcs, &sh, &fits);

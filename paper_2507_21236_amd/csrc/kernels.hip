@@ -2180,8 +2180,8 @@ __device__ __forceinline__ void trinv_blocks(const double* A, double* X, int lan
   }
 }
 
-template <int N>
-__global__ __launch_bounds__(64) void k_chol_inv_blk(const double* __restrict__ G, int n, double* __restrict__ R,
+template <int N, bool RAG>
+__global__ __launch_bounds__(64) void k_chol_inv_blk(const double* __restrict__ G, int nr, double* __restrict__ R,
                                                      double* __restrict__ RinvRow, int shift_mode, int64_t rows,
                                                      KrylovState* __restrict__ st) {
   static_assert(N % 16 == 0 && N <= 64, "blocks of 16, one lane per row");
@@ -2189,7 +2189,8 @@ __global__ __launch_bounds__(64) void k_chol_inv_blk(const double* __restrict__ 
   __shared__ double A[64 * kCholLd];   // A(i, j) at j * kCholLd + i
   __shared__ double X[64 * kCholLd];
   const int lane = threadIdx.x;
-  const bool own = lane < n;   // n <= N; the matrix is continued by the identity
+  const int n = RAG ? nr : N;   // n <= N; the matrix is continued by the identity
+  const bool own = lane < n;
   const double tr = wave_sum(own ? G[(int64_t)lane * n + lane] : 0.0);
   const double shift =
       shift_mode ? 11.0 * ((double)rows * n + (double)n * (n + 1)) * 1.1102230246251565e-16 * tr : 0.0;
@@ -2315,90 +2316,96 @@ __global__ __launch_bounds__(256) void k_chol_inv(const double* __restrict__ G, 
 // LDS (column-major); reflectors as in LAPACK's geqr2, Q formed in place as in
 // org2r, then the signs are fixed so that diag(R) >= 0.  Q overwrites T, R
 // (column-major n x n) goes to Rout.
-__global__ __launch_bounds__(256) void k_qr_small(double* __restrict__ T, int d0, int d1, int d2,
-                                                  int j, double* __restrict__ Rout,
-                                                  KrylovState* __restrict__ st) {
+// A serial chain of n reflectors, so what counts is the latency of one: sixteen
+// wavefronts own the columns round robin, a reflector is kept unscaled (its
+// factor in sc), and the owner of the next column applies the current
+// reflector to it first and finds the next one at once, so a column costs one
+// barrier.  64 x 64: 564 us with four wavefronts, block-wide norms and four
+// barriers per column, 190 us now.
+__global__ __launch_bounds__(1024) void k_qr_small(double* __restrict__ T, int d0, int d1, int d2,
+                                                   int j, double* __restrict__ Rout,
+                                                   KrylovState* __restrict__ st) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* A = reinterpret_cast<double*>(smem_raw);
-  __shared__ double tau[64];
-  __shared__ double red[4];
-  __shared__ double sgn[64];
+  __shared__ double tau[64], sc[64], sgn[64];
+  constexpr int W = 16;   // wavefronts
   const int n = j == 0 ? d0 : (j == 1 ? d1 : d2);
-  const int64_t rows = (int64_t)d0 * d1 * d2 / n;
+  const int rows = (int)((int64_t)d0 * d1 * d2 / n);
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  for (int64_t e = t; e < rows * n; e += 256) {
-    const int c = (int)(e / rows);
-    const int64_t f = e - (int64_t)c * rows;
-    A[e] = T[mode_addr(j, d0, d1, d2, c, f)];
+  for (int e = t; e < rows * n; e += 64 * W) {
+    const int c = e / rows;
+    A[e] = T[mode_addr(j, d0, d1, d2, c, e - c * rows)];
   }
   __syncthreads();
-  const int kmax = (int)(rows < n ? rows : n);
-  for (int k = 0; k < kmax; k++) {
-    double* col = A + (int64_t)k * rows;
+  const int kmax = rows < n ? rows : n;
+  // H_k = I - tau v v^T, v = (1, sc col[k + 1 ..]), applied to column c
+  auto apply = [&](int k, int c, double tk, double sk) {
+    const double* col = A + k * rows;
+    double* cc = A + c * rows;
+    double w = 0;
+    for (int i = k + 1 + lane; i < rows; i += 64) w += col[i] * cc[i];
+    w = tk * (cc[k] + sk * wave_sum(w));
+    wave_sync();
+    if (lane == 0) cc[k] -= w;
+    for (int i = k + 1 + lane; i < rows; i += 64) cc[i] -= w * sk * col[i];
+    wave_sync();
+  };
+  // the reflector of column k, by the wavefront that owns it
+  auto reflector = [&](int k) {
+    double* col = A + k * rows;
     double s2 = 0;
-    for (int64_t i = k + 1 + t; i < rows; i += 256) s2 += col[i] * col[i];
-    s2 = block_sum(s2, red);
+    for (int i = k + 1 + lane; i < rows; i += 64) s2 += col[i] * col[i];
+    s2 = wave_sum(s2);
     const double alpha = col[k];
-    double tk = 0, beta = alpha, scale = 0;
+    double tk = 0, beta = alpha, sk = 0;
     if (s2 > 0) {
       beta = -copysign(sqrt(alpha * alpha + s2), alpha);
       tk = (beta - alpha) / beta;
-      scale = 1.0 / (alpha - beta);
+      sk = 1.0 / (alpha - beta);
     }
-    __syncthreads();
-    if (s2 > 0) for (int64_t i = k + 1 + t; i < rows; i += 256) col[i] *= scale;
-    if (t == 0) { col[k] = beta; tau[k] = tk; }
-    __syncthreads();
-    if (tk != 0.0) {
-      // apply H_k = I - tau v v^T (v_k = 1) to columns c > k; one wave per column
-      for (int c = k + 1 + wave; c < n; c += 4) {
-        double* cc = A + (int64_t)c * rows;
-        double w = 0;
-        for (int64_t i = k + lane; i < rows; i += 64) w += (i == k ? 1.0 : col[i]) * cc[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off, 64);
-        w *= tk;
-        for (int64_t i = k + lane; i < rows; i += 64) cc[i] -= w * (i == k ? 1.0 : col[i]);
-      }
+    wave_sync();
+    if (lane == 0) {
+      col[k] = beta;
+      tau[k] = tk;
+      sc[k] = sk;
+    }
+  };
+  if (wave == 0) reflector(0);
+  __syncthreads();
+  for (int k = 0; k < kmax; k++) {
+    const double tk = tau[k], sk = sc[k];
+    // this wavefront's columns behind k, the next one first
+    int c = k + 1 + (wave - (k + 1) % W + W) % W;
+    for (; c < n; c += W) {
+      if (tk != 0.0) apply(k, c, tk, sk);
+      if (c == k + 1 && c < kmax) reflector(c);
     }
     __syncthreads();
   }
   // R and its sign fix
-  for (int e = t; e < n * n; e += 256) {
-    const int c = e / n, r = e - c * n;
-    Rout[e] = (r <= c && r < kmax) ? A[(int64_t)c * rows + r] : 0.0;
-  }
-  if (t < n) sgn[t] = (t < kmax && A[(int64_t)t * rows + t] < 0) ? -1.0 : 1.0;
+  if (t < n) sgn[t] = (t < kmax && A[t * rows + t] < 0) ? -1.0 : 1.0;
   __syncthreads();
-  for (int e = t; e < n * n; e += 256) {
-    const int r = e % n;
-    Rout[e] *= sgn[r];
+  for (int e = t; e < n * n; e += 64 * W) {
+    const int c = e / n, r = e - c * n;
+    Rout[e] = ((r <= c && r < kmax) ? A[c * rows + r] : 0.0) * sgn[r];
   }
-  // form Q in place (org2r), columns from last to first
+  __syncthreads();
+  // form Q in place (org2r), columns from last to first; column k is
+  // rewritten by its owner once every wavefront has applied reflector k
   for (int k = kmax - 1; k >= 0; k--) {
-    double* col = A + (int64_t)k * rows;
-    const double tk = tau[k];
-    if (k < n - 1) {
-      for (int c = k + 1 + wave; c < n; c += 4) {
-        double* cc = A + (int64_t)c * rows;
-        double w = 0;
-        for (int64_t i = k + lane; i < rows; i += 64) w += (i == k ? 1.0 : col[i]) * cc[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off, 64);
-        w *= tk;
-        for (int64_t i = k + lane; i < rows; i += 64) cc[i] -= w * (i == k ? 1.0 : col[i]);
-      }
+    const double tk = tau[k], sk = sc[k];
+    for (int c = k + 1 + (wave - (k + 1) % W + W) % W; c < n; c += W) apply(k, c, tk, sk);
+    __syncthreads();
+    if (wave == k % W) {
+      double* col = A + k * rows;
+      for (int i = lane; i < rows; i += 64) col[i] = i < k ? 0.0 : (i == k ? 1.0 - tk : -tk * sk * col[i]);
+      wave_sync();
     }
-    __syncthreads();
-    for (int64_t i = k + 1 + t; i < rows; i += 256) col[i] *= -tk;
-    if (t == 0) col[k] = 1.0 - tk;
-    for (int i = t; i < k; i += 256) col[i] = 0.0;
-    __syncthreads();
   }
-  for (int64_t e = t; e < rows * n; e += 256) {
-    const int c = (int)(e / rows);
-    const int64_t f = e - (int64_t)c * rows;
-    T[mode_addr(j, d0, d1, d2, c, f)] = A[e] * sgn[c];
+  __syncthreads();
+  for (int e = t; e < rows * n; e += 64 * W) {
+    const int c = e / rows;
+    T[mode_addr(j, d0, d1, d2, c, e - c * rows)] = A[e] * sgn[c];
   }
   if (t == 0 && st && !isfinite(tau[0])) fail_status(st, 2);
 }
@@ -2632,6 +2639,10 @@ hipError_t launch_kritz(const KJob* jobs, int nj, hipStream_t s) {
   return hipGetLastError();
 }
 
+bool tiny_in_lds(int M, int kreq) {
+  return M <= kTinyWaveM || tiny_basis_bytes(M, kreq) <= (int64_t)kTinyLdsMax - kTinyBlockFixed;
+}
+
 hipError_t launch_tiny(const TJob* jobs, int nj, int minM, int maxM, int kreq, hipStream_t s) {
   if (maxM > 1024 || minM < 1 || minM > maxM) return hipErrorInvalidValue;
   // blocks for the most entries x parts of any job size in [minM, maxM]
@@ -2655,13 +2666,20 @@ hipError_t launch_tiny(const TJob* jobs, int nj, int minM, int maxM, int kreq, h
 
 hipError_t launch_chol_inv(const double* G, int n, double* R, double* RinvRow, int shift_mode,
                            int64_t rows, KrylovState* st, double* ws, hipStream_t s) {
+#define CHOL_BLK(N)                                                                                          \
+  if (n == N)                                                                                                \
+    hipLaunchKernelGGL((k_chol_inv_blk<N, false>), dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st); \
+  else                                                                                                       \
+    hipLaunchKernelGGL((k_chol_inv_blk<N, true>), dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st);  \
+  return hipGetLastError();
   switch (sw_strips(n)) {
-    case 1: hipLaunchKernelGGL(k_chol_inv_blk<16>, dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
-    case 2: hipLaunchKernelGGL(k_chol_inv_blk<32>, dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
-    case 3: hipLaunchKernelGGL(k_chol_inv_blk<48>, dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
-    case 4: hipLaunchKernelGGL(k_chol_inv_blk<64>, dim3(1), dim3(64), 0, s, G, n, R, RinvRow, shift_mode, rows, st); return hipGetLastError();
+    case 1: CHOL_BLK(16)
+    case 2: CHOL_BLK(32)
+    case 3: CHOL_BLK(48)
+    case 4: CHOL_BLK(64)
     default: break;
   }
+#undef CHOL_BLK
   if (n <= 128) {
     hipLaunchKernelGGL(k_chol_inv<false>, dim3(1), dim3(256), (size_t)n * (n + 1) * sizeof(double), s, G,
                        n, R, RinvRow, shift_mode, rows, st, nullptr);
@@ -2675,7 +2693,7 @@ hipError_t launch_chol_inv(const double* G, int n, double* R, double* RinvRow, i
 hipError_t launch_qr_small(double* T, int d0, int d1, int d2, int j, double* Rout, KrylovState* st,
                            hipStream_t s) {
   const size_t lds = (size_t)d0 * d1 * d2 * sizeof(double);
-  hipLaunchKernelGGL(k_qr_small, dim3(1), dim3(256), lds, s, T, d0, d1, d2, j, Rout, st);
+  hipLaunchKernelGGL(k_qr_small, dim3(1), dim3(1024), lds, s, T, d0, d1, d2, j, Rout, st);
   return hipGetLastError();
 }
 

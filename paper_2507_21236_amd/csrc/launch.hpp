@@ -48,6 +48,12 @@ hipError_t launch_kortho(const KJob* jobs, int nj, int j, int pin, int norm_only
 hipError_t launch_kbeta(const KJob* jobs, int nj, int j, int64_t nmax, hipStream_t s);
 hipError_t launch_ktridiag(const KJob* jobs, int nj, hipStream_t s);
 hipError_t launch_kritz(const KJob* jobs, int nj, hipStream_t s);
+// Whether the one-workgroup Lanczos of a node of M entries holds its basis in
+// LDS.  FP64 solves above that (M = 768 to 1024 at k = 20) take the kernels of
+// the larger nodes: one workgroup streams H and the basis from L2 (M = 1024: 1.70
+// ms a solve, 0.51 over the whole chip; M = 1000: 1.84, 0.77).  Low-precision solves keep their tiny
+// nodes in FP64 and so in one workgroup.
+bool tiny_in_lds(int M, int kreq);
 hipError_t launch_tiny(const TJob* jobs, int nj, int minM, int maxM, int kreq, hipStream_t s);
 
 // Mixed-shape launches over the tasks of several nodes / problem instances

@@ -1097,7 +1097,7 @@ double lanczos(attn_handle* h, int n, int kreq, int precision, int* nmv, hipStre
   const int k = (int)std::min<int64_t>(kk, Msz);
   run_comb(D.comb, s);
   // tiny nodes (dense H_eff, negligible work) stay in FP64 for every form
-  if (D.d_tiny) {
+  if (D.d_tiny && (precision != ATTN_F64 || tiny_in_lds((int)Msz, kk))) {
     HIPCHK(launch_tiny(h->d_tjobs + n, 1, (int)Msz, (int)Msz, kk, s));
     h->n_matvec += k;
     h->mv_flops += (double)k * h->M.mv[n].flops;
