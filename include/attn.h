@@ -346,7 +346,7 @@ attn_status attn_mlp_eval(const float* params, const float* feats, float* out, i
  * every Krylov vector step in one launch); the centre moves of different
  * instances run concurrently on four streams.  With persistent, each matvec
  * of a step is instead ONE launch: a resident grid takes the units of all
- * instances (transposes, chain stages, two-leg tiles, reduction tiles) from
+ * instances (chain stages, two-leg tiles, reduction tiles) from
  * one ordered work list by ticket, and a unit that needs earlier results waits
  * on a per-instance counter of the units it depends on, which always come
  * earlier in the list (persistent = 2: each step takes whichever of the two

@@ -39,15 +39,13 @@ struct attn_batch {
     std::vector<MPJob> mp_jobs[3];
     std::vector<int2> mp_wus[3];
     size_t mp_lds[3] = {0, 0, 0};
-    std::vector<TRTask> tr;
-    int64_t tr_max = 0;
     std::vector<RDSrc> rd_srcs;
     std::vector<RDTask> rd;
     int64_t rd_max = 0;
     std::vector<int4> sw_wus2;   // two-strip units (task, first slice, 0, slices)
     int4* d_sw_wus2 = nullptr;
     // instance of every task (persistent form)
-    std::vector<int> sw_inst, mp_inst[3], tr_inst, rd_inst;
+    std::vector<int> sw_inst, mp_inst[3], rd_inst;
     std::vector<PUnit> pu;
     std::vector<int32_t> tickets;
     int pm_grid = 0;
@@ -61,7 +59,6 @@ struct attn_batch {
     MPTask* d_mp_tasks[3] = {nullptr, nullptr, nullptr};
     MPJob* d_mp_jobs[3] = {nullptr, nullptr, nullptr};
     int2* d_mp_wus[3] = {nullptr, nullptr, nullptr};
-    TRTask* d_tr = nullptr;
     RDSrc* d_rd_srcs = nullptr;
     RDTask* d_rd = nullptr;
     PUnit* d_pu = nullptr;
@@ -269,7 +266,6 @@ void upload_merged(attn_batch* b, attn_batch::Merged& m) {
     m.d_mp_jobs[k] = bupload(b, m.mp_jobs[k]);
     m.d_mp_wus[k] = bupload(b, m.mp_wus[k]);
   }
-  m.d_tr = bupload(b, m.tr);
   m.d_rd_srcs = bupload(b, m.rd_srcs);
   for (RDTask& t : m.rd) t.srcs = m.d_rd_srcs + (size_t)(uintptr_t)t.srcs;   // offsets -> pointers
   m.d_rd = bupload(b, m.rd);
@@ -289,13 +285,12 @@ void upload_merged(attn_batch* b, attn_batch::Merged& m) {
     m.pm.mp_tasks[k] = m.d_mp_tasks[k];
     m.pm.mp_jobs[k] = m.d_mp_jobs[k];
   }
-  m.pm.tr = m.d_tr;
   m.pm.rd = m.d_rd;
 }
 
 // Ordered work list of the persistent matvec.  Counters per instance i:
-// kPmFirst + 4 i + {0: transposes, 1: chain stage 1, 2: chain stage 2,
-// 3: partial and chain outputs}.  Order: transposes, chain stage 1, the first
+// kPmFirst + 4 i + {1: chain stage 1, 2: chain stage 2, 3: partial and chain
+// outputs}.  Order: chain stage 1, the first
 // third of the sandwich tiles, stage 2, the second third, stage 3, the last
 // third, reductions.  Every wait points at units earlier in the list, and the
 // sandwich thirds give the chain stages independent work to overlap with, so
@@ -314,13 +309,6 @@ void build_units(attn_batch* b, attn_batch::Merged& m) {
     m.pu.push_back(u);
     if (sig >= 0) n[sig - kPmFirst]++;
   };
-  std::vector<char> has_tr(ni, 0);
-  for (size_t r = 0; r < m.tr.size(); r++) {
-    const int i = m.tr_inst[r];
-    const int64_t M = (int64_t)m.tr[r].ml * m.tr[r].mr * m.tr[r].mp;
-    for (int64_t e = 0; e < M; e += kPmTileT) push(PU_TRANSPOSE, (int)r, (int)e, 0, 0, -1, ctr(i, 0));
-    has_tr[i] = 1;
-  }
   for (const int2& wu : m.mp_wus[0]) push(PU_MODE, 0, wu.x, wu.y, 0, -1, ctr(m.mp_inst[0][wu.x], 1));
   const bool chains = !m.mp_wus[1].empty() || !m.mp_wus[2].empty();
   const size_t nsw = m.sw_wus.size();
@@ -328,9 +316,7 @@ void build_units(attn_batch* b, attn_batch::Merged& m) {
     for (size_t w = w0; w < w1; w++) {
       const int4& wu = m.sw_wus[w];
       const int i = m.sw_inst[wu.x];
-      const bool tr = m.sw_tasks[wu.x].x == (const void*)b->hs[i]->d_xt;
-      if (tr && !has_tr[i]) throw BatchFail{ATTN_ERR_STATE, "internal: transposed input without its transpose"};
-      push(PU_SANDWICH, wu.x, wu.y, wu.z, wu.w, tr ? ctr(i, 0) : -1, ctr(i, 3));
+      push(PU_SANDWICH, wu.x, wu.y, wu.z, wu.w, -1, ctr(i, 3));
     }
   };
   sandwiches(0, chains ? nsw / 3 : nsw);
@@ -363,7 +349,7 @@ void build_units(attn_batch* b, attn_batch::Merged& m) {
   if (per_cu < 1) throw BatchFail{ATTN_ERR_UNSUPPORTED, "persistent matvec does not fit a CU"};
   const int64_t slots = (int64_t)per_cu * b->n_cu;
   // tickets: runs of up to K consecutive units with the same kind, wait and
-  // signal.  Chain-stage, transpose and reduction units go one per ticket:
+  // signal.  Chain-stage and reduction units go one per ticket:
   // the chain stages are on the dependency path, and the reductions end the
   // launch, so neither may pile up in one workgroup.  Sandwich tiles are many
   // and alike; they go in runs sized for about eight tickets per workgroup.
@@ -421,7 +407,12 @@ void build_step(attn_batch* b, int t) {
     }
     KJob J = h->h_kjobs[n];
     const void* x;
-    if (fmt) { J.x32 = h->d_x32; x = h->d_x32; }
+    if (fmt) {
+      J.x32 = h->d_x32;
+      x = h->d_x32;
+      J.xt32 = (float*)J.xt64;   // the transposed copy in FP32 instead
+      J.xt64 = nullptr;
+    }
     else { J.x64 = b->x64[i]; x = b->x64[i]; }
     S.kj.push_back(J);
     S.kj_inst.push_back(i);
@@ -432,13 +423,8 @@ void build_step(attn_batch* b, int t) {
     add_sandwich(b, h, n, x, S.mv, srcs, nullptr, &fits);
     if (!fits) throw BatchFail{ATTN_ERR_STATE, "batched form: partial-output scratch too small"};
     add_chains(b, h, n, x, S.mv, srcs);
-    if (D.need_xt) {
-      S.mv.tr.push_back({x, h->d_xt, D.dims[0], D.dims[1], D.dims[2], 0});
-      S.mv.tr_max = std::max(S.mv.tr_max, Msz);
-    }
     S.mv.sw_inst.resize(S.mv.sw_tasks.size(), i);
     for (int k = 0; k < 3; k++) S.mv.mp_inst[k].resize(S.mv.mp_tasks[k].size(), i);
-    S.mv.tr_inst.resize(S.mv.tr.size(), i);
     S.mv.rd_inst.push_back(i);
     RDTask rt;
     rt.srcs = (const RDSrc*)(uintptr_t)S.mv.rd_srcs.size();   // offset, made a pointer at upload
@@ -467,7 +453,6 @@ void run_matvec(attn_batch* b, attn_batch::Merged& m, hipStream_t s) {
     HIPCHK(launch_batch_matvec(dt, m.pm, m.pm_grid, m.pm_lds, s));
     return;
   }
-  HIPCHK(launch_transpose_list(dt, m.d_tr, (int)m.tr.size(), m.tr_max, s));
   for (int k = 0; k < 3; k++)
     HIPCHK(launch_batch_mode(dt, m.d_mp_tasks[k], m.d_mp_jobs[k], m.d_mp_wus[k], (int)m.mp_wus[k].size(),
                              m.mp_lds[k], s));
@@ -521,8 +506,8 @@ void enqueue_step(attn_batch* b, int t, hipStream_t s0) {
       break;
     }
     HIPCHK(launch_kdots(J, nj, 0, j + 1, 1, b->precision == ATTN_F64, s0));
-    HIPCHK(launch_kortho(J, nj, j, 1, 0, 1, s0));
-    HIPCHK(launch_kortho(J, nj, j, 2, 1, 0, s0));
+    HIPCHK(launch_kortho(J, nj, j, 1, 0, 1, b->precision == ATTN_F64, s0));
+    HIPCHK(launch_kortho(J, nj, j, 2, 1, 0, b->precision == ATTN_F64, s0));
     HIPCHK(launch_kbeta(J, nj, j, S.kj_max, s0));
   }
   HIPCHK(launch_ktridiag(J, nj, s0));

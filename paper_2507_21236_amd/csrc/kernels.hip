@@ -135,19 +135,6 @@ __global__ __launch_bounds__(256) void k_batch_mode(const MPTask* __restrict__ t
   }
 }
 
-// [l][r][p] -> [p][l][r] for a list of tensors (task blockIdx.y)
-template <typename T>
-__global__ __launch_bounds__(256) void k_transpose_list(const TRTask* __restrict__ tasks) {
-  const TRTask& t = tasks[blockIdx.y];
-  const int64_t M = (int64_t)t.ml * t.mr * t.mp;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < M; e += (int64_t)gridDim.x * 256) {
-    const int64_t l = e / ((int64_t)t.mr * t.mp);
-    const int64_t rem = e - l * t.mr * t.mp;
-    const int64_t r = rem / t.mp, p = rem - r * t.mp;
-    ((T*)t.xt)[p * t.ml * t.mr + l * t.mr + r] = ((const T*)t.x)[e];
-  }
-}
-
 // y = sum of the partial outputs of each task (fixed order), as k_reduce_out
 template <typename TI, typename TO>
 __global__ __launch_bounds__(256) void k_reduce_list(const RDTask* __restrict__ tasks) {
@@ -485,6 +472,39 @@ __global__ __launch_bounds__(256) void k_cast(const TS* __restrict__ s, TD* __re
 }
 
 // ============================================================================ Krylov (FP64)
+// ---- wavefront-wide reductions.  Every step combines a lane with a partner
+// holding the same partial (the operations are commutative), and the result
+// is read from lane 0, so every lane gets the same bits.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double readlane_d(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+template <typename Op>
+__device__ __forceinline__ double wave_reduce(double v, Op op) {
+  v = op(v, dpp_d<0xB1>(v));    // quad_perm(1, 0, 3, 2)
+  v = op(v, dpp_d<0x4E>(v));    // quad_perm(2, 3, 0, 1)
+  v = op(v, dpp_d<0x141>(v));   // row_half_mirror
+  v = op(v, dpp_d<0x140>(v));   // row_mirror
+  v = op(v, __shfl_xor(v, 16, 64));
+  v = op(v, __shfl_xor(v, 32, 64));
+  return readlane_d(v, 0);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  return wave_reduce(v, [](double x, double y) { return x + y; });
+}
+__device__ __forceinline__ double wave_max(double v) {
+  return wave_reduce(v, [](double x, double y) { return fmax(x, y); });
+}
+__device__ __forceinline__ double wave_min(double v) {
+  return wave_reduce(v, [](double x, double y) { return fmin(x, y); });
+}
+
 __device__ __forceinline__ double block_sum(double v, double* red) {
   // deterministic: wave shuffle tree, then fixed-order sum of the 4 waves
 #pragma unroll
@@ -512,6 +532,14 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ p, dou
 __device__ __forceinline__ void write_copies(const KJob& J, int64_t e, double v) {
   if (J.x64) J.x64[e] = v;
   if (J.x32) J.x32[e] = (float)v;
+  // the product contracts (l, r) slices from a copy with p first: written here,
+  // a launch of its own per product otherwise
+  if (J.xt64 || J.xt32) {
+    const uint32_t q = (uint32_t)e / J.mp, c = (uint32_t)e - q * J.mp;   // (l, r) and p
+    const int64_t et = (int64_t)c * J.ml * J.mr + q;
+    if (J.xt64) J.xt64[et] = v;
+    if (J.xt32) J.xt32[et] = (float)v;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_kinit(const KJob* __restrict__ jobs, int kmax) {
@@ -814,6 +842,80 @@ __global__ __launch_bounds__(256) void k_kortho(const KJob* __restrict__ jobs, i
   block_dots(J, w, nv, po, red8);
 }
 
+// The same pass for FP64 solves, with the entries dealt to blocks of 1024
+// threads as in k_kdots: wavefronts share out the sums of partials, and the
+// 1024 / c threads of an entry share out the basis vectors.  What bounds it at
+// the small nodes is the chain partials -> coefficients -> update -> dots; four
+// wavefronts walking all vectors took 6.1 us a pass over the solves of an 8 x 8
+// m = 32 sweep, 5.1 this way.
+__global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ jobs, int j, int pin,
+                                                       int norm_only, int set_alpha) {
+  const KJob& J = jobs[blockIdx.y];
+  if (J.st->stop) return;
+  __shared__ double hs[64], part[1024], red[64 * kDotChunk];
+  const int nv = j + 1, t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  const int64_t n = J.n;
+  const double* P = parea(J, pin);
+  for (int q = wave; q < nv; q += 16) {
+    double v = 0;
+#pragma unroll
+    for (int u = 0; u < kRedBlocks / 64; u++) v += P[q * kRedBlocks + lane + 64 * u];
+    v = wave_sum(v);
+    if (lane == 0) hs[q] = v;
+  }
+  __syncthreads();
+  if (set_alpha && blockIdx.x == 0 && t == 0) {
+    J.st->alpha[j] = hs[j];
+    if (!isfinite(hs[j])) fail_status(J.st, 1);
+  }
+  const int c = dot_chunk(n), S = 1024 / c, g = t / c, i = t - g * c;
+  double* w = J.w;
+  double* po = parea(J, pin + 1);
+  double nrm = 0;
+  for (int64_t e0 = (int64_t)blockIdx.x * c; e0 < n; e0 += (int64_t)kRedBlocks * c) {   // once when c < 1024
+    const int64_t e = e0 + i;
+    double a = 0;
+    if (e < n) {
+      const double* V = J.V + e;
+#pragma unroll 8
+      for (int q = g; q < nv; q += S) a += hs[q] * V[(int64_t)q * n];
+    }
+    if (S > 1) {
+      part[t] = a;
+      __syncthreads();
+      if (g == 0)
+        for (int q = 1; q < S; q++) a += part[q * c + i];
+      __syncthreads();
+    }
+    if (g == 0 && e < n) {
+      const double x = w[e] - a;
+      w[e] = x;
+      part[i] = x;
+      nrm += x * x;
+    } else if (g == 0) {
+      part[i] = 0.0;
+    }
+  }
+  if (norm_only) {
+    const double s = wave_sum(nrm);
+    if (lane == 0) red[wave] = s;
+    __syncthreads();
+    if (t == 0) {
+      double v = 0;
+      for (int q = 0; q < 16; q++) v += red[q];
+      po[blockIdx.x] = v;
+    }
+    return;
+  }
+  __syncthreads();
+  if (S > 1) {
+    const bool mine = (int64_t)blockIdx.x * c < n;   // part holds this block's entries
+    block_dots_split(J, mine ? part[i] : 0.0, c, 0, nv, po, red);
+  } else {
+    block_dots_1k(J, w, 0, nv, po, red);
+  }
+}
+
 // beta_j = sqrt(sum P3); breakdown test; V_{j+1} = w / beta_j (and the copies)
 __global__ __launch_bounds__(256) void k_kbeta(const KJob* __restrict__ jobs, int j) {
   __shared__ double red[4];
@@ -838,39 +940,6 @@ __global__ __launch_bounds__(256) void k_kbeta(const KJob* __restrict__ jobs, in
     out[e] = v;
     write_copies(J, e, v);
   }
-}
-
-// ---- wavefront-wide reductions.  Every step combines a lane with a partner
-// holding the same partial (the operations are commutative), and the result
-// is read from lane 0, so every lane gets the same bits.
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double readlane_d(double v, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                          __builtin_amdgcn_readlane(__double2loint(v), l));
-}
-template <typename Op>
-__device__ __forceinline__ double wave_reduce(double v, Op op) {
-  v = op(v, dpp_d<0xB1>(v));    // quad_perm(1, 0, 3, 2)
-  v = op(v, dpp_d<0x4E>(v));    // quad_perm(2, 3, 0, 1)
-  v = op(v, dpp_d<0x141>(v));   // row_half_mirror
-  v = op(v, dpp_d<0x140>(v));   // row_mirror
-  v = op(v, __shfl_xor(v, 16, 64));
-  v = op(v, __shfl_xor(v, 32, 64));
-  return readlane_d(v, 0);
-}
-__device__ __forceinline__ double wave_sum(double v) {
-  return wave_reduce(v, [](double x, double y) { return x + y; });
-}
-__device__ __forceinline__ double wave_max(double v) {
-  return wave_reduce(v, [](double x, double y) { return fmax(x, y); });
-}
-__device__ __forceinline__ double wave_min(double v) {
-  return wave_reduce(v, [](double x, double y) { return fmin(x, y); });
 }
 
 // Lowest eigenpair of the keff x keff symmetric tridiagonal matrix
@@ -2619,8 +2688,12 @@ hipError_t launch_reduce_dots(const RDSrc* srcs, int nsrc, const KJob* job, int 
   return hipGetLastError();
 }
 
-hipError_t launch_kortho(const KJob* jobs, int nj, int j, int pin, int norm_only, int set_alpha, hipStream_t s) {
-  hipLaunchKernelGGL(k_kortho, dim3(kRedBlocks, nj), dim3(256), 0, s, jobs, j, pin, norm_only, set_alpha);
+hipError_t launch_kortho(const KJob* jobs, int nj, int j, int pin, int norm_only, int set_alpha, int split,
+                         hipStream_t s) {
+  if (split)
+    hipLaunchKernelGGL(k_kortho_split, dim3(kRedBlocks, nj), dim3(1024), 0, s, jobs, j, pin, norm_only, set_alpha);
+  else
+    hipLaunchKernelGGL(k_kortho, dim3(kRedBlocks, nj), dim3(256), 0, s, jobs, j, pin, norm_only, set_alpha);
   return hipGetLastError();
 }
 
@@ -2710,15 +2783,6 @@ hipError_t launch_batch_mode(int dtype, const MPTask* tasks, const MPJob* jobs, 
     hipLaunchKernelGGL(k_batch_mode<double>, dim3(nwu), dim3(256), lds, s, tasks, jobs, wus);
   else
     hipLaunchKernelGGL(k_batch_mode<float>, dim3(nwu), dim3(256), lds, s, tasks, jobs, wus);
-  return hipGetLastError();
-}
-
-hipError_t launch_transpose_list(int dtype, const TRTask* tasks, int ntask, int64_t maxM, hipStream_t s) {
-  if (ntask == 0) return hipSuccess;
-  if (dtype == 0)
-    hipLaunchKernelGGL(k_transpose_list<double>, dim3(gridv(maxM), ntask), dim3(256), 0, s, tasks);
-  else
-    hipLaunchKernelGGL(k_transpose_list<float>, dim3(gridv(maxM), ntask), dim3(256), 0, s, tasks);
   return hipGetLastError();
 }
 

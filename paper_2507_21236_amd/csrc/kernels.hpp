@@ -156,11 +156,6 @@ struct RDTask {
   void* y;             // FP64
   int32_t nsrc, ml, mr, mp;
 };
-struct TRTask {        // [l][r][p] -> [p][l][r]
-  const void* x;
-  void* xt;
-  int32_t ml, mr, mp, pad;
-};
 
 // ---------------------------------------------------------------- persistent batched matvec
 // One launch runs a whole matvec of several problem instances: a resident
@@ -168,8 +163,7 @@ struct TRTask {        // [l][r][p] -> [p][l][r]
 // tickets are dealt to kPmQueues queues (ticket t to queue t mod kPmQueues,
 // workgroup b takes from queue b mod kPmQueues, one atomic counter per queue),
 // so that no single counter serialises every grab.  A unit may wait for a
-// counter of units that come before it in the list (per instance:
-// transposes before the sandwiches that read the transposed input, each chain
+// counter of units that come before it in the list (per instance: each chain
 // stage before the next, every partial output before the reduction).  The
 // launch cannot deadlock: each queue hands out its tickets in list order, so
 // the earliest unfinished unit is either held by a running workgroup (and
@@ -177,12 +171,12 @@ struct TRTask {        // [l][r][p] -> [p][l][r]
 // queue, whose workgroups are then all free to take it.  One ticket covers a
 // run of consecutive units with the same wait and signal, so that the ticket
 // atomic and the device-scope release and acquire are paid once per run.
-enum { PU_TRANSPOSE = 0, PU_MODE = 1, PU_SANDWICH = 2, PU_REDUCE = 3 };
+enum { PU_MODE = 1, PU_SANDWICH = 2, PU_REDUCE = 3 };
 
 struct PUnit {
   int32_t kind;     // PU_*
   int32_t a, b, c, d;
-  // transpose / reduce: a = task, b = first element (kPmTileT / kPmTileR elements)
+  // reduce: a = task, b = first element (kPmTileR elements)
   // mode: a = chain stage, b = task of that stage, c = free tile or first element
   // sandwich: (a, b, c, d) = (task, slice, first 16-row strip, body)
   int32_t wait;     // counter that must reach `need` before the unit runs, or -1
@@ -194,7 +188,6 @@ constexpr int kPmQueues = 8;              // ticket queues (counters 0 .. 7)
 constexpr int kPmExit = kPmQueues;        // counter: workgroups that have left the loop
 constexpr int kPmFirst = kPmQueues + 1;   // first dependency counter
 constexpr int kPmStride = 32;             // ints between counters: one 128-byte line each
-constexpr int kPmTileT = 2048;            // elements per transpose unit
 constexpr int kPmTileR = 256;             // elements per reduction unit (one per lane: each sums every source)
 // Spin limit of one wait: about a second; past it the launch sets its abort
 // word, skips every unit that still has to wait, and ends.
@@ -214,7 +207,6 @@ struct PMArgs {
   const SWItem* sw_items;
   const MPTask* mp_tasks[3];
   const MPJob* mp_jobs[3];
-  const TRTask* tr;
   const RDTask* rd;
 };
 
@@ -258,6 +250,9 @@ struct KJob {
   double* x64;        // optional copy of the newest basis vector (FP64)
   float* x32;         // optional copy of the newest basis vector (FP32)
   int64_t n;
+  double* xt64;       // optional copies with the parent leg first, [p][l][r]
+  float* xt32;
+  int32_t ml, mr, mp, pad;
 };
 
 // ---------------------------------------------------------------- tiny nodes

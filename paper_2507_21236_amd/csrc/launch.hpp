@@ -44,7 +44,8 @@ hipError_t launch_kdots(const KJob* jobs, int nj, int i0, int nv, int pin, int s
 // w = sum of a product's partial outputs, then launch_kdots' partial dots (one job)
 hipError_t launch_reduce_dots(const RDSrc* srcs, int nsrc, const KJob* job, int ml, int mr, int mp, int i0,
                               int nv, int pin, hipStream_t s);
-hipError_t launch_kortho(const KJob* jobs, int nj, int j, int pin, int norm_only, int set_alpha, hipStream_t s);
+hipError_t launch_kortho(const KJob* jobs, int nj, int j, int pin, int norm_only, int set_alpha, int split,
+                         hipStream_t s);
 hipError_t launch_kbeta(const KJob* jobs, int nj, int j, int64_t nmax, hipStream_t s);
 hipError_t launch_ktridiag(const KJob* jobs, int nj, hipStream_t s);
 hipError_t launch_kritz(const KJob* jobs, int nj, hipStream_t s);
@@ -66,7 +67,6 @@ hipError_t launch_batch_matvec(int dtype, const PMArgs& a, int grid, size_t lds,
 hipError_t batch_matvec_occupancy(int dtype, size_t lds, int* per_cu);
 hipError_t launch_batch_mode(int dtype, const MPTask* tasks, const MPJob* jobs, const int2* wus, int nwu,
                              size_t lds, hipStream_t s);
-hipError_t launch_transpose_list(int dtype, const TRTask* tasks, int ntask, int64_t maxM, hipStream_t s);
 hipError_t launch_reduce_list(int dtype_in, const RDTask* tasks, int ntask, int64_t maxM, hipStream_t s);
 hipError_t launch_zero(double* p, int64_t n, hipStream_t s);
 // dst = src (n doubles; the ranges do not overlap)

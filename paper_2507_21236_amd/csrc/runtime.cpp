@@ -615,12 +615,13 @@ void run_mp(std::vector<MPGroup>& gs, int dtype, const void* xbase, hipStream_t 
 }
 
 // y <- H_eff(n) x (FP64), combines must be current.  With a Krylov job J
-// (y = J's w), the partial dots of basis vectors [i0, i0 + nv) with y go to
-// area pin in the same launch as the sum of the partial outputs.
+// (y = J's w), x is J's newest basis vector (whose transposed copy is current)
+// and the partial dots of basis vectors [i0, i0 + nv) with y go to area pin in
+// the same launch as the sum of the partial outputs.
 void matvec_f64(attn_handle* h, int n, const double* x, double* y, hipStream_t s, const KJob* J = nullptr,
                 int i0 = 0, int nv = 0, int pin = 0) {
   MVDev& D = h->mv[n];
-  if (D.need_xt) HIPCHK(launch_transpose_plr(0, x, h->d_xt, D.dims[0], D.dims[1], D.dims[2], s));
+  if (D.need_xt && !J) HIPCHK(launch_transpose_plr(0, x, h->d_xt, D.dims[0], D.dims[1], D.dims[2], s));
   run_mp(D.chainA, 0, x, s);
   run_mp(D.chainB, 0, x, s);
   run_mp(D.chainC, 0, x, s);
@@ -866,10 +867,11 @@ void prepare_lowp(attn_handle* h, int n, int dtype, hipStream_t s) {
 }
 
 // y <- H_eff(n) x in form `dtype` (mirrors current); x is FP32, y FP64
-// (out_dtype 0) or FP32 (out_dtype 1).
-void matvec_lowp(attn_handle* h, int n, int dtype, const float* x, void* y, int out_dtype, hipStream_t s) {
+// (out_dtype 0) or FP32 (out_dtype 1).  have_xt: the transposed copy of x is current.
+void matvec_lowp(attn_handle* h, int n, int dtype, const float* x, void* y, int out_dtype, hipStream_t s,
+                 bool have_xt = false) {
   MVDev& D = h->mvlp[dtype - 1][n];
-  if (D.need_xt) HIPCHK(launch_transpose_plr(1, x, h->d_xt, D.dims[0], D.dims[1], D.dims[2], s));
+  if (D.need_xt && !have_xt) HIPCHK(launch_transpose_plr(1, x, h->d_xt, D.dims[0], D.dims[1], D.dims[2], s));
   run_mp(D.chainA, 1, x, s);
   run_mp(D.chainB, 1, x, s);
   run_mp(D.chainC, 1, x, s);
@@ -1130,15 +1132,16 @@ double lanczos(attn_handle* h, int n, int kreq, int precision, int* nmv, hipStre
     if (precision == ATTN_F64) {
       matvec_f64(h, n, V + (int64_t)j * Msz, h->d_w, s, J, i0, nv, pin);
     } else {
-      matvec_lowp(h, n, precision, h->d_x32, h->d_w, 0, s);
+      matvec_lowp(h, n, precision, h->d_x32, h->d_w, 0, s, true);
       HIPCHK(launch_kdots(J, 1, i0, nv, pin, 0, s));
     }
     if (last) {
       HIPCHK(launch_kalpha(J, 1, j, s));
       break;
     }
-    HIPCHK(launch_kortho(J, 1, j, 1, 0, 1, s));
-    HIPCHK(launch_kortho(J, 1, j, 2, 1, 0, s));
+    const int split = precision == ATTN_F64;
+    HIPCHK(launch_kortho(J, 1, j, 1, 0, 1, split, s));
+    HIPCHK(launch_kortho(J, 1, j, 2, 1, 0, split, s));
     HIPCHK(launch_kbeta(J, 1, j, Msz, s));
   }
   HIPCHK(launch_ktridiag(J, 1, s));
@@ -1458,8 +1461,15 @@ attn_status attn_build_tpo(const attn_problem* p, attn_handle** out) {
       const int64_t Msz = h->T_len[n];
       double* T = h->d_T + h->T_off[n];
       kj64[n] = KJob{h->d_V, h->d_w, T, h->d_red, h->d_st, nullptr, nullptr, Msz};
+      kj64[n].ml = tr.nodes[n].dims[0];
+      kj64[n].mr = tr.nodes[n].dims[1];
+      kj64[n].mp = tr.nodes[n].dims[2];
       kj32[n] = kj64[n];
       kj32[n].x32 = h->d_x32;
+      if (h->mv[n].need_xt) {
+        kj64[n].xt64 = h->d_xt;
+        kj32[n].xt32 = (float*)h->d_xt;
+      }
       tj[n] = TJob{h->mv[n].d_tiny, h->d_tmp2, T, h->d_V, h->d_w, h->d_st, (int32_t)Msz, 0};
     }
     h->h_kjobs = kj64;
@@ -2264,7 +2274,8 @@ extern "C" attn_status attn_validate(const attn_handle* h) {
     if (D.need_xt) c.span(h->d_xt, M * 8, "transposed input");
     {
       const KJob& J = h->h_kjobs[n];
-      if (J.n != M) c.fail("eigensolve job size");
+      if (J.n != M || (int64_t)J.ml * J.mr * J.mp != M || M > UINT32_MAX) c.fail("eigensolve job size");
+      if ((J.xt64 != nullptr) != D.need_xt) c.fail("eigensolve job: transposed copy");
       c.span(J.T, M * 8, "job tensor");
       c.span(J.V, (int64_t)h->kcap * M * 8, "job basis");
       c.span(J.w, M * 8, "job residual");

@@ -1113,7 +1113,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 }
 
 // ============================================================================ persistent batched matvec
-// The staged batched matvec is six launches (transposes, three chain stages,
+// The staged batched matvec is five launches (three chain stages,
 // sandwiches, reduction); here one launch of a resident grid runs them all
 // from one ordered work list (PUnit), so later stages start while earlier
 // units of other instances still run.  Every unit runs the same body as in
@@ -1132,18 +1132,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // per-unit timestamp trace put the remaining gap in per-ticket latency
 // (ticket atomic, descriptor loads, publish: about 5 us between units) and in
 // the reduction tail; the staged launches stay the default.
-template <typename T>
-__device__ __forceinline__ void pm_transpose(const TRTask& t, int64_t e0) {
-  const int64_t M = (int64_t)t.ml * t.mr * t.mp;
-  const int64_t e1 = e0 + kPmTileT < M ? e0 + kPmTileT : M;
-  for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
-    const int64_t l = e / ((int64_t)t.mr * t.mp);
-    const int64_t rem = e - l * t.mr * t.mp;
-    const int64_t r = rem / t.mp, p = rem - r * t.mp;
-    ((T*)t.xt)[p * t.ml * t.mr + l * t.mr + r] = ((const T*)t.x)[e];
-  }
-}
-
 // same per-element sum as k_reduce_list
 template <typename TI>
 __device__ __forceinline__ void pm_reduce(const RDTask& t, int64_t e0) {
@@ -1298,7 +1286,6 @@ void k_batch_matvec(const PMArgs a) {
       const PUnit u = units[ui];
       if (ui > u0) __syncthreads();   // LDS of the previous unit
       switch (u.kind) {
-        case PU_TRANSPOSE: pm_transpose<T>(a.tr[u.a], u.b); break;
         case PU_REDUCE: pm_reduce<T>(a.rd[u.a], u.b); break;
         case PU_MODE: pm_mode<T>(a.mp_tasks[u.a] + u.b, a.mp_jobs[u.a], u.b, u.c); break;
         case PU_SANDWICH: pm_sandwich<T>(a.sw_tasks + u.a, a.sw_items, u.a, u.b, u.c, u.d); break;
