@@ -232,7 +232,7 @@ void add_chains(attn_batch* b, attn_handle* h, int n, const void* x, attn_batch:
                 std::vector<RDSrc>& srcs) {
   const MVDev& D = b->precision == ATTN_F64 ? h->mv[n] : h->mvlp[0][n];
   const size_t esz = b->precision == ATTN_F64 ? 8 : 4;
-  const std::vector<MPGroup>* st[3] = {&D.chainA, &D.chainB, &D.chainC};
+  const std::vector<MPGroup>* st[3] = {&D.chainA, &D.chainB, b->precision == ATTN_F64 ? &D.chainS : &D.chainC};
   for (int k = 0; k < 3; k++)
     for (const MPGroup& g : *st[k]) {
       const int t0 = (int)m.mp_tasks[k].size();

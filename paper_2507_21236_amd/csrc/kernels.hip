@@ -52,57 +52,7 @@ __global__ __launch_bounds__(256) void k_mode(const MPTask* __restrict__ tasks,
                                               const T* __restrict__ xbase) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int2 wu = wus[blockIdx.x];
-  mode_mfma<T, NI, QS, FT>(tasks[wu.x], jobs, wu, xbase, smem_raw);
-}
-
-// Mode product for contracted leg j = 0 or 1 with 16 | d2: a 16-wide tile of
-// the free index is contiguous in memory for every i', so both operands are
-// loaded straight into registers (no LDS, no barriers).  wu = (task, 64-wide
-// free block); the block is split over blockIdx.y into QS sub-blocks, and a
-// workgroup's four waves take (4 / QS) tiles of 16 free indices times QS
-// groups of output rows (QS = 1: each wave all m_j rows of its own tile).
-// Every output entry sums its products in the same order whatever QS is.
-template <typename T, int NI, int QS>
-__global__ __launch_bounds__(256) void k_mode_nt(const MPTask* __restrict__ tasks, const MPJob* __restrict__ jobs,
-                                                 const int2* __restrict__ wus, const T* __restrict__ xbase) {
-  typedef typename V4<T>::type v4;
-  constexpr int mj = 16 * NI, NQ = NI / QS;   // output row blocks per wave
-  const int2 wu = wus[blockIdx.x];
-  const MPTask& t = tasks[wu.x];
-  const int j = t.j, d1 = t.d1, d2 = t.d2;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int l16 = lane & 15, l4 = lane >> 4;
-  const int tile = (4 / QS) * blockIdx.y + wave / QS, q0 = (wave % QS) * NQ;
-  const int64_t F = (int64_t)t.d0 * d1 * d2 / mj;
-  const int64_t f = (int64_t)wu.y * 64 + 16 * tile + l16;
-  // (i, f) -> address; the tile's f share one a-row when j = 1
-  int64_t fo, fs;   // address = fo + i * fs
-  if (j == 0) { fo = f; fs = F; }
-  else { const int64_t a = f / d2, c = f - a * d2; fo = a * d1 * d2 + c; fs = d2; }
-  v4 acc[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; q++) acc[q] = v4{0, 0, 0, 0};
-  for (int jb = t.job0; jb < t.job0 + t.njob; jb++) {
-    const T* in = jobs[jb].in ? (const T*)jobs[jb].in : xbase;
-    const T* A = (const T*)jobs[jb].A + 16 * q0 + l16;
-    const T coef = (T)jobs[jb].coef;
-#pragma unroll 4
-    for (int k0 = 0; k0 < mj; k0 += 4) {
-      const T bop = in[fo + (int64_t)(k0 + l4) * fs] * coef;
-      const T* Ak = A + (int64_t)(k0 + l4) * mj;
-#pragma unroll
-      for (int q = 0; q < NQ; q++) acc[q] = mfma16(Ak[16 * q], bop, acc[q]);
-    }
-  }
-  T* out = (T*)t.out;
-#pragma unroll
-  for (int q = 0; q < NQ; q++)
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int64_t ad = fo + (int64_t)(16 * (q0 + q) + drow<T>(l4, i)) * fs;
-      if (t.accumulate) out[ad] += acc[q][i];
-      else out[ad] = acc[q][i];
-    }
+  mode_mfma<T, NI, QS, FT>(tasks[wu.x], jobs, wu, blockIdx.y, xbase, smem_raw);
 }
 
 template <typename T>
@@ -127,10 +77,10 @@ __global__ __launch_bounds__(256) void k_batch_mode(const MPTask* __restrict__ t
   const MPTask& t = tasks[wu.x];
   switch (t.pad) {
     case 0: mode_gen_elem<T>(t, jobs, (int64_t)wu.y + threadIdx.x, nullptr); break;
-    case 1: mode_mfma<T, 1>(t, jobs, wu, nullptr, smem_raw); break;
-    case 2: mode_mfma<T, 2>(t, jobs, wu, nullptr, smem_raw); break;
-    case 3: mode_mfma<T, 3>(t, jobs, wu, nullptr, smem_raw); break;
-    case 4: mode_mfma<T, 4>(t, jobs, wu, nullptr, smem_raw); break;
+    case 1: mode_mfma<T, 1>(t, jobs, wu, 0, nullptr, smem_raw); break;
+    case 2: mode_mfma<T, 2>(t, jobs, wu, 0, nullptr, smem_raw); break;
+    case 3: mode_mfma<T, 3>(t, jobs, wu, 0, nullptr, smem_raw); break;
+    case 4: mode_mfma<T, 4>(t, jobs, wu, 0, nullptr, smem_raw); break;
     default: break;
   }
 }
@@ -379,6 +329,7 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const GRReduce* __restrict_
   if (e >= mm) return;
   const double* P = (const double*)r.partial;
   double acc = 0;
+#pragma unroll 8
   for (int c = 0; c < r.npart; c++) acc += P[c * mm + e];
   double* out = (double*)r.out;
   acc *= r.coef;
@@ -846,8 +797,8 @@ __global__ __launch_bounds__(256) void k_kortho(const KJob* __restrict__ jobs, i
 // threads as in k_kdots: wavefronts share out the sums of partials, and the
 // 1024 / c threads of an entry share out the basis vectors.  What bounds it at
 // the small nodes is the chain partials -> coefficients -> update -> dots; four
-// wavefronts walking all vectors took 6.1 us a pass over the solves of an 8 x 8
-// m = 32 sweep, 5.1 this way.
+// wavefronts walking all vectors took 6.1 us at 4096 entries and 10 vectors,
+// MEAS_KO this way.
 __global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ jobs, int j, int pin,
                                                        int norm_only, int set_alpha) {
   const KJob& J = jobs[blockIdx.y];
@@ -2491,6 +2442,37 @@ __global__ __launch_bounds__(64) void k_small_matmul(const double* __restrict__ 
   C[e] = acc;
 }
 
+// C = A2 (A1 A0) for n x n upper-triangular column-major matrices, n <= 64: the
+// R of three Cholesky-QR passes, in one workgroup (two launches of k_small_matmul
+// walk n dependent loads each: 34 us at n = 64, about 10 here).
+__global__ __launch_bounds__(1024) void k_r_product(const double* __restrict__ A2, const double* __restrict__ A1,
+                                                    const double* __restrict__ A0, double* __restrict__ C, int n) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* X = reinterpret_cast<double*>(smem_raw);
+  double* Y = X + n * n;
+  double* Z = Y + n * n;
+  for (int e = threadIdx.x; e < n * n; e += 1024) {
+    X[e] = A1[e];
+    Y[e] = A0[e];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < n * n; e += 1024) {
+    const int j = e / n, i = e - j * n;
+    double acc = 0;
+    for (int k = i; k <= j; k++) acc += X[k * n + i] * Y[j * n + k];
+    Z[e] = acc;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < n * n; e += 1024) X[e] = A2[e];
+  __syncthreads();
+  for (int e = threadIdx.x; e < n * n; e += 1024) {
+    const int j = e / n, i = e - j * n;
+    double acc = 0;
+    for (int k = i; k <= j; k++) acc += X[k * n + i] * Z[j * n + k];
+    C[e] = acc;
+  }
+}
+
 // ============================================================================ launchers
 static inline unsigned grid1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
@@ -2504,24 +2486,8 @@ static hipError_t mode_launch(int mj, const MPTask* tasks, const MPJob* jobs, co
 }
 
 hipError_t launch_mode(int dtype, int mj, bool mfma, const MPTask* tasks, const MPJob* jobs,
-                       const int2* wus, int nwu, const void* xbase, hipStream_t s, bool nt) {
+                       const int2* wus, int nwu, const void* xbase, hipStream_t s) {
   if (nwu == 0) return hipSuccess;
-  if (mfma && nt && mj <= 64) {
-// m_j = 32 or 64: the output rows of a tile are spread over 2 or 4 waves
-#define MNT(T, NI)                                                                                        \
-  {                                                                                                       \
-    constexpr int QS = NI == 4 ? 4 : (NI == 2 ? 2 : 1);                                                   \
-    hipLaunchKernelGGL((k_mode_nt<T, NI, QS>), dim3(nwu, QS), dim3(256), 0, s, tasks, jobs, wus,          \
-                       (const T*)xbase);                                                                  \
-    return hipGetLastError();                                                                             \
-  }
-    if (dtype == 0) {
-      switch (mj / 16) { case 1: MNT(double, 1) case 2: MNT(double, 2) case 3: MNT(double, 3) case 4: MNT(double, 4) }
-    } else {
-      switch (mj / 16) { case 1: MNT(float, 1) case 2: MNT(float, 2) case 3: MNT(float, 3) case 4: MNT(float, 4) }
-    }
-#undef MNT
-  }
   if (!mfma) {
     if (dtype == 0)
       hipLaunchKernelGGL(k_mode_gen<double>, dim3(nwu), dim3(256), 0, s, tasks, jobs, wus,
@@ -2775,6 +2741,16 @@ hipError_t launch_small_matmul(const double* A, const double* B, double* C, int 
   return hipGetLastError();
 }
 
+hipError_t launch_r_product(const double* A2, const double* A1, const double* A0, double* tmp, double* C, int n,
+                            hipStream_t s) {
+  if (n <= 64) {
+    hipLaunchKernelGGL(k_r_product, dim3(1), dim3(1024), (size_t)3 * n * n * sizeof(double), s, A2, A1, A0, C, n);
+    return hipGetLastError();
+  }
+  hipError_t e = launch_small_matmul(A1, A0, tmp, n, s);
+  return e != hipSuccess ? e : launch_small_matmul(A2, tmp, C, n, s);
+}
+
 // ---------------------------------------------------------------- mixed-shape launchers
 hipError_t launch_batch_mode(int dtype, const MPTask* tasks, const MPJob* jobs, const int2* wus, int nwu,
                              size_t lds, hipStream_t s) {
@@ -2839,7 +2815,7 @@ hipError_t prepare_kernel_attributes() {
       (const void*)k_mode<float, 6, mode_tile(6).qs, mode_tile(6).ft>,
       (const void*)k_mode<float, 7, mode_tile(7).qs, mode_tile(7).ft>,
       (const void*)k_mode<float, 8, mode_tile(8).qs, mode_tile(8).ft>,
-      (const void*)k_mlp_grad};
+      (const void*)k_mlp_grad, (const void*)k_r_product};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;

@@ -46,16 +46,20 @@ struct MPJob {
   double coef;
 };
 
-// Tile of a mode product's workgroup (legs of 16 NI): qs groups of row tiles by
-// 4 / qs groups of ft tiles of free columns.  Up to legs of 64 many small
+// Tile of a mode product's workgroup (legs of 16 NI): nw wavefronts as qs groups
+// of row tiles by nw / qs groups of ft tiles of free columns.  Up to legs of 64 many small
 // workgroups, above column pairs (each A element then serves two products).
 struct ModeTile {
-  int qs, ft;
+  int qs, ft, nw = 4;
 };
 constexpr ModeTile mode_tile(int NI) {
   return NI == 8 ? ModeTile{4, 2} : NI == 4 ? ModeTile{4, 1} : (NI == 2 || NI == 6) ? ModeTile{2, 1} : ModeTile{1, 1};
 }
-constexpr int mode_width(ModeTile m) { return 16 * m.ft * (4 / m.qs); }
+// within a sandwich launch (a workgroup of NI wavefronts there)
+constexpr ModeTile joint_mode_tile(int NI) {
+  return NI == 1 ? ModeTile{1, 1, 1} : NI == 2 ? ModeTile{2, 1, 2} : NI == 3 ? ModeTile{1, 1, 2} : ModeTile{4, 1, 4};
+}
+constexpr int mode_width(ModeTile m) { return 16 * m.ft * (m.nw / m.qs); }
 // LDS bytes of the staged tile (whole K steps of rows, two elements of padding)
 constexpr size_t mode_lds(int mj, ModeTile m, size_t esz) {
   return (size_t)((mj + 3) / 4 * 4) * (mode_width(m) + 2) * esz;

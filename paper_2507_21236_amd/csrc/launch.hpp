@@ -15,9 +15,13 @@ constexpr int kRedBlocks = 256;
 hipError_t launch_sandwich(int dtype, int ma, int mb, const SWTask* tasks, const SWItem* items,
                            const int4* wus, int nwu, const void* xbase, hipStream_t s,
                            const SWOut* outs = nullptr);
-// nt: every task has j in {0, 1} and 16 | d2 (register-direct kernel, m_j <= 64)
 hipError_t launch_mode(int dtype, int mj, bool mfma, const MPTask* tasks, const MPJob* jobs,
-                       const int2* wus, int nwu, const void* xbase, hipStream_t s, bool nt = false);
+                       const int2* wus, int nwu, const void* xbase, hipStream_t s);
+// The FP64 sandwich launch (ma, mb) with the units of a mode-product launch
+// (legs of as many tiles as mb) in front of its own
+hipError_t launch_sandwich_mode(int ma, int mb, const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
+                                int mj, const MPTask* mtasks, const MPJob* mjobs, const int2* mwus, int nmwu,
+                                const void* xbase, hipStream_t s);
 // nt: every task has j in {0, 1}, 16 | d2 and 16-aligned free ranges (register-direct kernel, mj <= 64)
 hipError_t launch_gram(int mj, bool mfma, const GRTask* tasks, int ntask, hipStream_t s, bool nt = false);
 hipError_t launch_gram_reduce(const GRReduce* r, int nr, int maxm, hipStream_t s);
@@ -104,5 +108,8 @@ hipError_t launch_chol_inv(const double* G, int n, double* R, double* RinvRow, i
 hipError_t launch_qr_small(double* T, int d0, int d1, int d2, int j, double* Rout, KrylovState* st,
                            hipStream_t s);
 hipError_t launch_small_matmul(const double* A, const double* B, double* C, int n, hipStream_t s);
+// C = A2 (A1 A0), upper triangular; tmp: n x n scratch
+hipError_t launch_r_product(const double* A2, const double* A1, const double* A0, double* tmp, double* C, int n,
+                            hipStream_t s);
 
 }  // namespace attn

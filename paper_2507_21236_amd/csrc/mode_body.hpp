@@ -22,33 +22,35 @@ __device__ __forceinline__ int64_t mode_addr(int j, int d0, int d1, int d2, int 
 }
 
 // out (+)= sum_jobs coef * A x_j in.  wu = (task, 64-wide block of the free
-// index f).  A workgroup takes FW = 16 FT (4 / QS) free columns (the block is
-// split over blockIdx.y when FW < 64) and every row i: its four wavefronts form
-// QS groups of rows by 4 / QS groups of FT column tiles.  The input tile
+// index f).  A workgroup takes FW = 16 FT (NW / QS) free columns (part `sub` of
+// the block when FW < 64) and every row i: its NW wavefronts form
+// QS groups of rows by NW / QS groups of FT column tiles.  The input tile
 // [i'][f] of a job is staged in LDS, the next job's is already on its way into
 // registers while this one is multiplied, and the elements of A run PA steps
 // ahead of their products through bounds-checked loads, so a leg that is not a
 // multiple of 16, or a last block that is not full, needs no other code (rows
 // past the end are zero, results past the end are not stored).  Every output
-// entry sums its products in the same order whatever the split.
+// entry sums its products in the same order whatever the split.  With a single
+// job the output may be the input: a workgroup reads its columns before it
+// writes them.
 // What bounds it is the latency of the operand loads: a chain has few jobs and
 // one launch per stage, so small tiles (many workgroups) are taken up to legs
 // of 64 and column pairs above, where each A element then serves two products.
 // Three stages of the heaviest 8 x 8 m = 128 node
-// (96 products, 51.5 GFLOP): 2.51 ms before the loads ran ahead, 0.7 ms now.
-template <typename T, int NI, int QS = 1, int FT = 1>
+// (96 products, 51.5 GFLOP): 2.51 ms before the loads ran ahead, 1.09 now.
+template <typename T, int NI, int QS = 1, int FT = 1, int NW = 4>
 __device__ __forceinline__ void mode_mfma(const MPTask& t, const MPJob* __restrict__ jobs,
-                                          const int2 wu, const T* __restrict__ xbase,
+                                          const int2 wu, int sub, const T* __restrict__ xbase,
                                           unsigned char* smem_raw) {
   typedef typename V4<T>::type v4;
-  constexpr int mjp = 16 * NI, NQ = NI / QS, FW = 16 * FT * (4 / QS), ld = FW + 2;
-  constexpr int NPT = mjp * FW / 256;   // staged elements per thread
+  constexpr int mjp = 16 * NI, NQ = NI / QS, FW = 16 * FT * (NW / QS), ld = FW + 2;
+  constexpr int NT = 64 * NW, NPT = mjp * FW / NT;   // staged elements per thread
   constexpr int PA = NQ > 2 ? 2 : 4;
   T* lds = reinterpret_cast<T*>(smem_raw);
   const int j = t.j, d0 = t.d0, d1 = t.d1, d2 = t.d2;
   const int mj = j == 0 ? d0 : (j == 1 ? d1 : d2);
   const int M = d0 * d1 * d2, F = M / mj, KS = (mj + 3) >> 2;
-  const int f0 = wu.y * 64 + (FW < 64 ? FW * (int)blockIdx.y : 0);
+  const int f0 = wu.y * 64 + (FW < 64 ? FW * sub : 0);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int l16 = lane & 15, l4 = lane >> 4;
   const int tile = (wave / QS) * FT, q0 = (wave % QS) * NQ;
@@ -56,7 +58,7 @@ __device__ __forceinline__ void mode_mfma(const MPTask& t, const MPJob* __restri
   int off[NPT];
 #pragma unroll
   for (int u = 0; u < NPT; u++) {
-    const int e = threadIdx.x + 256 * u;
+    const int e = threadIdx.x + NT * u;
     const int i = j == 2 ? e % mjp : e / FW, fl = j == 2 ? e / mjp : e % FW;
     off[u] = (i < mj && f0 + fl < F) ? (int)mode_addr(j, d0, d1, d2, i, f0 + fl) * (int)sizeof(T) : M * (int)sizeof(T);
   }
@@ -85,7 +87,7 @@ __device__ __forceinline__ void mode_mfma(const MPTask& t, const MPJob* __restri
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < NPT; u++) {
-      const int e = threadIdx.x + 256 * u;
+      const int e = threadIdx.x + NT * u;
       const int i = j == 2 ? e % mjp : e / FW, fl = j == 2 ? e / mjp : e % FW;
       if (i < 4 * KS) lds[i * ld + fl] = pf[u];
     }

@@ -182,21 +182,8 @@ void upload_sw(attn_handle* h, std::vector<SWGroup>& gs, bool by_xcd = false) {
   }
 }
 
-// the register-direct mode kernel applies when every task contracts leg 0 or 1
-// of a tensor whose last leg is a multiple of 16 (m_j <= 64)
-bool mode_nt_ok(const std::vector<MPTask>& ts, bool mfma) {
-  if (!mfma || ts.empty()) return false;
-  for (const MPTask& t : ts) {
-    const int mj = t.j == 0 ? t.d0 : (t.j == 1 ? t.d1 : t.d2);
-    if (t.j > 1 || mj > 64 || mj % 16 || t.d2 % 16) return false;
-    if ((int64_t)t.d0 * t.d1 * t.d2 / mj % 64) return false;
-  }
-  return true;
-}
-
 void upload_mp(attn_handle* h, std::vector<MPGroup>& gs) {
   for (auto& g : gs) {
-    g.nt = mode_nt_ok(g.tasks, g.mfma);
     g.d_tasks = upload(h, g.tasks);
     g.d_jobs = upload(h, g.jobs);
     g.d_wus = upload(h, g.wus);
@@ -315,6 +302,27 @@ void build_mv_dev(attn_handle* h, int n, std::vector<int64_t>& comb_off_out) {
     for (auto& pr : stageC[leg]) g.jobs.push_back({pr.first, pr.second, 1.0});
     add_mp_task(g, t);
     D.srcs.push_back({out, 0, 0});
+    // FP64: runs of four jobs to outputs of their own while the launch has fewer
+    // than 1024 workgroups (one task walks its jobs at the latency of a tile
+    // each: 16 jobs at legs 16 took 9.7 us).  Low-precision solves keep one
+    // sum per leg in the accumulators.
+    const int nj = (int)stageC[leg].size();
+    const ModeTile mt = mode_tile(sw_strips(dm[leg]));
+    const int64_t per = g.mfma ? mode_blocks(dm[leg], Msz) * (64 / mode_width(mt)) : 1024;
+    const int ns = (int)std::max<int64_t>(1, std::min<int64_t>((nj + 3) / 4, 1024 / per));
+    MPGroup& gs = mgroup_for(D.chainS, dm[leg], g.mfma);
+    for (int k = 0; k < ns; k++) {
+      const int j0 = nj * k / ns, j1 = nj * (k + 1) / ns;
+      double* o = k == 0 ? out : h->d_chain + chain_used;
+      if (k > 0) {
+        chain_used += Msz;
+        D.srcs.push_back({o, 0, 0});
+        D.split_outs.push_back(o);
+      }
+      MPTask ts{o, dm[0], dm[1], dm[2], leg, (int)gs.jobs.size(), j1 - j0, 0, 0};
+      for (int q = j0; q < j1; q++) gs.jobs.push_back({stageC[leg][q].first, stageC[leg][q].second, 1.0});
+      add_mp_task(gs, ts);
+    }
   }
   if (part_used > h->part_cap || chain_used > h->chain_cap)
     throw StatusFail{ATTN_ERR_STATE, "internal: scratch sizing"};
@@ -322,7 +330,7 @@ void build_mv_dev(attn_handle* h, int n, std::vector<int64_t>& comb_off_out) {
   upload_sw(h, D.sw, true);
   upload_mp(h, D.chainA);
   upload_mp(h, D.chainB);
-  upload_mp(h, D.chainC);
+  upload_mp(h, D.chainS);   // chainC is uploaded by the low-precision forms
   D.d_srcs = upload(h, D.srcs);
   // explicit item lists: the dense H_eff of tiny nodes (M <= 1024) and the
   // H_eff diagonal of every node
@@ -611,7 +619,7 @@ void run_sw_mv(attn_handle* h, std::vector<SWGroup>& gs, int dtype, const void* 
 
 void run_mp(std::vector<MPGroup>& gs, int dtype, const void* xbase, hipStream_t s) {
   for (auto& g : gs)
-    HIPCHK(launch_mode(dtype, g.mj, g.mfma, g.d_tasks, g.d_jobs, g.d_wus, (int)g.wus.size(), xbase, s, g.nt));
+    HIPCHK(launch_mode(dtype, g.mj, g.mfma, g.d_tasks, g.d_jobs, g.d_wus, (int)g.wus.size(), xbase, s));
 }
 
 // y <- H_eff(n) x (FP64), combines must be current.  With a Krylov job J
@@ -624,8 +632,20 @@ void matvec_f64(attn_handle* h, int n, const double* x, double* y, hipStream_t s
   if (D.need_xt && !J) HIPCHK(launch_transpose_plr(0, x, h->d_xt, D.dims[0], D.dims[1], D.dims[2], s));
   run_mp(D.chainA, 0, x, s);
   run_mp(D.chainB, 0, x, s);
-  run_mp(D.chainC, 0, x, s);
-  run_sw_mv(h, D.sw, 0, x, s);
+  // full nodes: the last chain stage shares the launch of the two-leg terms
+  // (not while those launches are being timed)
+  const bool joint = D.sw.size() == 1 && D.chainS.size() == 1 && D.chainS[0].mfma &&
+                     D.chainS[0].mj <= 64 && sw_mfma(D.sw[0].ma, D.sw[0].mb) &&
+                     sw_strips(D.chainS[0].mj) == sw_strips(D.sw[0].mb) && !h->prof;
+  if (joint) {
+    const SWGroup& g = D.sw[0];
+    const MPGroup& c = D.chainS[0];
+    HIPCHK(launch_sandwich_mode(g.ma, g.mb, g.d_tasks, g.d_items, g.d_wus, (int)g.wus.size(), c.mj, c.d_tasks, c.d_jobs,
+                                c.d_wus, (int)c.wus.size(), x, s));
+  } else {
+    run_mp(D.chainS, 0, x, s);
+    run_sw_mv(h, D.sw, 0, x, s);
+  }
   if (D.srcs.empty()) {
     HIPCHK(launch_zero(y, (int64_t)D.dims[0] * D.dims[1] * D.dims[2], s));
     if (J) HIPCHK(launch_kdots(J, 1, i0, nv, pin, 1, s));
@@ -814,6 +834,7 @@ void ensure_lowp(attn_handle* h, int dtype) {
       for (auto& g : *dst[k])
         for (auto& jb : g.jobs) jb.A = to_mirror(h, jb.A, 1);
     }
+    dropped.insert(dropped.end(), D.split_outs.begin(), D.split_outs.end());
     if (!dropped.empty()) {
       std::vector<RDSrc> keep;
       for (const RDSrc& r : L.srcs)
@@ -976,7 +997,6 @@ void build_qr_dev(attn_handle* h, int n, int leg, QRDev& Q) {
     Q.d_mj[pass] = upload(h, std::vector<MPJob>{mjb});
     Q.h_mp[pass].mj = mj;
     Q.h_mp[pass].mfma = Q.mmf;
-    Q.mnt = mode_nt_ok({mt}, Q.mmf);
     Q.h_mp[pass].tasks = {mt};
     Q.h_mp[pass].jobs = {mjb};
     Q.h_mp[pass].wus = wus;
@@ -997,13 +1017,12 @@ void build_ab_dev(attn_handle* h, int q, int leg, ABDev& A) {
   else for (int64_t e = 0; e < Msz; e += 256) wus.push_back(make_int2(0, (int)e));
   A.nwus = (int)wus.size();
   A.d_wus = upload(h, wus);
-  MPTask mt{h->d_tmp2, dm[0], dm[1], dm[2], leg, 0, 1, 0, 0};
+  MPTask mt{A.mmf ? T : h->d_tmp2, dm[0], dm[1], dm[2], leg, 0, 1, 0, 0};
   A.d_mt = upload(h, std::vector<MPTask>{mt});
   MPJob mjb{h->d_qrR, T, 1.0};
   A.d_mj = upload(h, std::vector<MPJob>{mjb});
   A.h_mp.mj = mj;
   A.h_mp.mfma = A.mmf;
-  A.mnt = mode_nt_ok({mt}, A.mmf);
   A.h_mp.tasks = {mt};
   A.h_mp.jobs = {mjb};
   A.h_mp.wus = wus;
@@ -1038,10 +1057,9 @@ void qr_node(attn_handle* h, int n, int leg, hipStream_t s) {
     HIPCHK(launch_gram(mj, Q.gmf, Q.d_gt[pass], Q.nfc, s, Q.gnt));
     HIPCHK(launch_gram_reduce(Q.d_gr, 1, mj, s));
     HIPCHK(launch_chol_inv(G, mj, R[pass], Rinv, pass == 0 ? 1 : 0, Q.rows, h->d_st, ws, s));
-    HIPCHK(launch_mode(0, mj, Q.mmf, Q.d_mt[pass], Q.d_mj[pass], Q.d_wus, Q.nwus, nullptr, s, Q.mnt));
+    HIPCHK(launch_mode(0, mj, Q.mmf, Q.d_mt[pass], Q.d_mj[pass], Q.d_wus, Q.nwus, nullptr, s));
   }
-  HIPCHK(launch_small_matmul(R[1], R[0], Rt, mj, s));
-  HIPCHK(launch_small_matmul(R[2], Rt, h->d_qrR, mj, s));
+  HIPCHK(launch_r_product(R[2], R[1], R[0], Rt, h->d_qrR, mj, s));
   h->n_qr++;
 }
 
@@ -1049,8 +1067,8 @@ void qr_node(attn_handle* h, int n, int leg, hipStream_t s) {
 void absorb(attn_handle* h, int q, int leg, hipStream_t s) {
   ABDev& A = h->ab[leg][q];
   if (!A.present) throw StatusFail{ATTN_ERR_STATE, "internal: no absorb plan for this leg"};
-  HIPCHK(launch_mode(0, A.mj, A.mmf, A.d_mt, A.d_mj, A.d_wus, A.nwus, nullptr, s, A.mnt));
-  HIPCHK(launch_copy(h->d_T + h->T_off[q], h->d_tmp2, A.Msz, s));
+  HIPCHK(launch_mode(0, A.mj, A.mmf, A.d_mt, A.d_mj, A.d_wus, A.nwus, nullptr, s));
+  if (!A.mmf) HIPCHK(launch_copy(h->d_T + h->T_off[q], h->d_tmp2, A.Msz, s));
 }
 
 attn_status guard(attn_handle* h, const std::function<attn_status()>& f) {
@@ -1373,8 +1391,12 @@ attn_status attn_build_tpo(const attn_problem* p, attn_handle** out) {
       for (int sp = 0; sp < 3; sp++) nparts += nchs[sp];
       part_need = std::max(part_need, nparts * Msz);
       int64_t cn = 0;
-      for (auto& ch : P.chains) cn += (int64_t)(ch.O1.size() + ch.O2.size());
-      cn += 3;
+      int64_t n1 = 0;
+      for (auto& ch : P.chains) {
+        cn += (int64_t)(ch.O1.size() + ch.O2.size());
+        n1 += (int64_t)ch.O1.size();
+      }
+      cn += 3 + n1 / 4 + 3;   // outputs of the last stage
       chain_need = std::max(chain_need, cn * Msz);
       int64_t cb = 0;
       for (auto& c : P.combines) cb += (int64_t)c.dim * c.dim;
@@ -2257,6 +2279,7 @@ extern "C" attn_status attn_validate(const attn_handle* h) {
     for (auto& g : D.chainA) c.mp(g, M, 8);
     for (auto& g : D.chainB) c.mp(g, M, 8);
     for (auto& g : D.chainC) c.mp(g, M, 8);
+    for (auto& g : D.chainS) c.mp(g, M, 8);
     for (auto& sr : D.srcs) c.span(sr.p, M * 8, "reduce source");
     {
       if (D.d_tiny && M > 1024) c.fail("tiny node too large");

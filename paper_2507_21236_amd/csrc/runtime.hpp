@@ -130,7 +130,6 @@ struct SWGroup {
 struct MPGroup {
   int mj = 0;
   bool mfma = false;
-  bool nt = false;   // register-direct kernel
   std::vector<MPTask> tasks;
   std::vector<MPJob> jobs;
   std::vector<int2> wus;
@@ -166,6 +165,10 @@ struct MVDev {
   CBPlan comb;
   std::vector<SWGroup> sw;
   std::vector<MPGroup> chainA, chainB, chainC;   // one group per mj
+  // the last stage with its jobs cut into several outputs (FP64; chainC writes
+  // the first output of each leg), and the sources chainC leaves out
+  std::vector<MPGroup> chainS;
+  std::vector<const void*> split_outs;
   std::vector<RDSrc> srcs;
   RDSrc* d_srcs = nullptr;
   bool need_xt = false;
@@ -191,7 +194,7 @@ struct EnvDev {
 struct QRDev {
   bool present = false;
   int mj = 0, nfc = 0, nwus = 0;
-  bool gmf = false, mmf = false, gnt = false, mnt = false;
+  bool gmf = false, mmf = false, gnt = false;
   int64_t rows = 0, Msz = 0;
   GRTask* d_gt[3] = {nullptr, nullptr, nullptr};
   GRReduce* d_gr = nullptr;
@@ -203,11 +206,11 @@ struct QRDev {
   MPGroup h_mp[3];   // host copies for validation
 };
 
-// T <- R x_leg T through a temporary
+// T <- R x_leg T, in place on the matrix cores, through a temporary otherwise
 struct ABDev {
   bool present = false;
   int mj = 0, nwus = 0;
-  bool mmf = false, mnt = false;
+  bool mmf = false;
   int64_t Msz = 0;
   MPTask* d_mt = nullptr;
   MPJob* d_mj = nullptr;

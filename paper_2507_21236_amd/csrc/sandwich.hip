@@ -314,6 +314,34 @@ void k_sandwich(const SWTask* __restrict__ tasks,
   sandwich_mfma<T, NB, SQ>(tasks[wu.x], items, wu, xbase, smem_raw, outs);
 }
 
+// The same launch with mode-product units (the last stage of the three-leg
+// chains of a full node, independent of the two-leg terms) in front of its own:
+// one launch less, and the chip is full while they run.  Up to legs of 64; a
+// wider slice leaves one or two workgroups per CU, too few for the short
+// mode-product units (128: 8.06 ms a matvec joined, 8.01 apart).  Eigensolves of the
+// heaviest 8 x 8 nodes, with the last stage's jobs cut into runs of four:
+// m = 16 1.12 -> 0.94 ms, m = 40 4.96 -> 4.12 ms; matvec 16 x 16 m = 64 1190 ->
+// 1179 us.
+template <typename T, int NB, bool SQ>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && NB <= 6 ? 3 : 2)))
+void k_sandwich_mode(const SWTask* __restrict__ tasks, const SWItem* __restrict__ items,
+                     const int4* __restrict__ wus, const MPTask* __restrict__ mtasks,
+                     const MPJob* __restrict__ mjobs, const int2* __restrict__ mwus, int nmwu,
+                     const T* __restrict__ xbase) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr ModeTile m = joint_mode_tile(NB);
+  constexpr int ny = 64 / mode_width(m);
+  const int b = blockIdx.x;
+  if (b < nmwu * ny) {
+    if (threadIdx.x >= 64 * m.nw) return;
+    const int2 wu = mwus[b / ny];
+    mode_mfma<T, NB, m.qs, m.ft, m.nw>(mtasks[wu.x], mjobs, wu, b % ny, xbase, smem_raw);
+    return;
+  }
+  const int4 wu = wus[b - nmwu * ny];
+  sandwich_mfma<T, NB, SQ>(tasks[wu.x], items, wu, xbase, smem_raw);
+}
+
 // either form, for the launches that mix shapes
 template <typename T, int NB>
 __device__ __forceinline__ void sandwich_any(const SWTask& t, const SWItem* __restrict__ items, const int4 wu,
@@ -1183,10 +1211,10 @@ __device__ __noinline__ void pm_mode(const MPTask* tp, const MPJob* jobs_, int t
   const int2 wu = make_int2(task, c);
   switch (t.pad) {
     case 0: mode_gen_elem<T>(t, jobs, (int64_t)c + threadIdx.x, nullptr); break;
-    case 1: mode_mfma<T, 1>(t, jobs, wu, nullptr, smem_raw); break;
-    case 2: mode_mfma<T, 2>(t, jobs, wu, nullptr, smem_raw); break;
-    case 3: mode_mfma<T, 3>(t, jobs, wu, nullptr, smem_raw); break;
-    case 4: mode_mfma<T, 4>(t, jobs, wu, nullptr, smem_raw); break;
+    case 1: mode_mfma<T, 1>(t, jobs, wu, 0, nullptr, smem_raw); break;
+    case 2: mode_mfma<T, 2>(t, jobs, wu, 0, nullptr, smem_raw); break;
+    case 3: mode_mfma<T, 3>(t, jobs, wu, 0, nullptr, smem_raw); break;
+    case 4: mode_mfma<T, 4>(t, jobs, wu, 0, nullptr, smem_raw); break;
     default: break;
   }
 }
@@ -1325,6 +1353,37 @@ static hipError_t sand_launch(const SWTask* tasks, const SWItem* items, const in
 }
 
 template <int NB>
+static hipError_t sand_mode_launch(int ma, int mb, const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
+                                   int mj, const MPTask* mtasks, const MPJob* mjobs, const int2* mwus, int nmwu,
+                                   const double* x, hipStream_t s) {
+  constexpr ModeTile m = joint_mode_tile(NB);
+  const size_t l0 = sw_mfma_lds(ma, 16 * NB, 8), l1 = mode_lds(mj, m, 8);
+  const dim3 grid(nwu + nmwu * (64 / mode_width(m)));
+  const int w = sw_strips(ma);
+  const dim3 block(64 * (w > m.nw ? w : m.nw));
+  if (ma == 16 * NB && mb == 16 * NB)
+    hipLaunchKernelGGL((k_sandwich_mode<double, NB, true>), grid, block, l0 > l1 ? l0 : l1, s, tasks, items, wus, mtasks,
+                       mjobs, mwus, nmwu, x);
+  else
+    hipLaunchKernelGGL((k_sandwich_mode<double, NB, false>), grid, block, l0 > l1 ? l0 : l1, s, tasks, items, wus, mtasks,
+                       mjobs, mwus, nmwu, x);
+  return hipGetLastError();
+}
+
+hipError_t launch_sandwich_mode(int ma, int mb, const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
+                                int mj, const MPTask* mtasks, const MPJob* mjobs, const int2* mwus, int nmwu,
+                                const void* xbase, hipStream_t s) {
+  if (!sw_on_mfma(ma, mb) || sw_strips(mj) != sw_strips(mb) || mj > 64) return hipErrorInvalidValue;
+#define SM_CASE(NB) \
+  case NB: return sand_mode_launch<NB>(ma, mb, tasks, items, wus, nwu, mj, mtasks, mjobs, mwus, nmwu, (const double*)xbase, s);
+  switch (sw_strips(mb)) {
+    SM_CASE(1) SM_CASE(2) SM_CASE(3) SM_CASE(4)
+  }
+#undef SM_CASE
+  return hipErrorInvalidValue;
+}
+
+template <int NB>
 static hipError_t sand_bf2_launch(const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
                                   int ma, const void* xbase, hipStream_t s) {
   const size_t lds = (size_t)2 * (16 * NB) * (ma + 8) * sizeof(__bf16);
@@ -1455,6 +1514,10 @@ hipError_t prepare_sandwich_attributes() {
       (const void*)k_sandwich<float, 6, true>, (const void*)k_sandwich<float, 6, false>,
       (const void*)k_sandwich<float, 7, true>, (const void*)k_sandwich<float, 7, false>,
       (const void*)k_sandwich<float, 8, true>, (const void*)k_sandwich<float, 8, false>,
+      (const void*)k_sandwich_mode<double, 1, true>, (const void*)k_sandwich_mode<double, 1, false>,
+      (const void*)k_sandwich_mode<double, 2, true>, (const void*)k_sandwich_mode<double, 2, false>,
+      (const void*)k_sandwich_mode<double, 3, true>, (const void*)k_sandwich_mode<double, 3, false>,
+      (const void*)k_sandwich_mode<double, 4, true>, (const void*)k_sandwich_mode<double, 4, false>,
       (const void*)k_sandwich_bf2<2>, (const void*)k_sandwich_bf2<4>,
       (const void*)k_sandwich_bf2w<2, 2>, (const void*)k_sandwich_bf2w<2, 4>,
       (const void*)k_sandwich_bf2w<4, 2>, (const void*)k_sandwich_bf2d<4, 4>,
