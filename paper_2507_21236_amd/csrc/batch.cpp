@@ -447,10 +447,15 @@ void build_step(attn_batch* b, int t) {
   upload_merged(b, S.mv);
 }
 
-void run_matvec(attn_batch* b, attn_batch::Merged& m, hipStream_t s) {
+// One matvec of every job; with J also the partial dots of basis vectors
+// [i0, i0 + nv) with the products into area pin (FP64 staged launches: in the
+// launch that sums the partial outputs).
+void run_matvec(attn_batch* b, attn_batch::Merged& m, hipStream_t s, const KJob* J = nullptr, int i0 = 0, int nv = 0,
+                int pin = 0) {
   const int dt = b->precision == ATTN_F64 ? 0 : 1;
   if (m.use_pm) {
     HIPCHK(launch_batch_matvec(dt, m.pm, m.pm_grid, m.pm_lds, s));
+    if (J) HIPCHK(launch_kdots(J, (int)m.rd.size(), i0, nv, pin, dt == 0, s));
     return;
   }
   for (int k = 0; k < 3; k++)
@@ -460,7 +465,12 @@ void run_matvec(attn_batch* b, attn_batch::Merged& m, hipStream_t s) {
   if (!m.sw_wus2.empty())
     HIPCHK(launch_sandwich(4, 64, 64, m.d_sw_tasks, m.d_sw_items, m.d_sw_wus2, (int)m.sw_wus2.size(), nullptr, s,
                            nullptr));
+  if (J && dt == 0) {
+    HIPCHK(launch_reduce_dots_list(m.d_rd, J, (int)m.rd.size(), i0, nv, pin, s));
+    return;
+  }
   HIPCHK(launch_reduce_list(dt, m.d_rd, (int)m.rd.size(), m.rd_max, s));
+  if (J) HIPCHK(launch_kdots(J, (int)m.rd.size(), i0, nv, pin, dt == 0, s));
 }
 
 // Enqueue step t on stream s0; the centre moves of the instances are spread
@@ -499,13 +509,12 @@ void enqueue_step(attn_batch* b, int t, hipStream_t s0) {
   HIPCHK(launch_knorm(J, nj, s0));
   HIPCHK(launch_kscale(J, nj, S.kj_max, 0, s0));
   for (int j = 0; j < kk; j++) {
-    run_matvec(b, S.mv, s0);
     if (j == kk - 1) {   // last step: only alpha_j
-      HIPCHK(launch_kdots(J, nj, j, 1, 0, b->precision == ATTN_F64, s0));
+      run_matvec(b, S.mv, s0, J, j, 1, 0);
       HIPCHK(launch_kalpha(J, nj, j, s0));
       break;
     }
-    HIPCHK(launch_kdots(J, nj, 0, j + 1, 1, b->precision == ATTN_F64, s0));
+    run_matvec(b, S.mv, s0, J, 0, j + 1, 1);
     HIPCHK(launch_kortho(J, nj, j, 1, 0, 1, b->precision == ATTN_F64, s0));
     HIPCHK(launch_kortho(J, nj, j, 2, 1, 0, b->precision == ATTN_F64, s0));
     HIPCHK(launch_kbeta(J, nj, j, S.kj_max, s0));

@@ -680,13 +680,11 @@ __global__ __launch_bounds__(1024) void k_kdots(const KJob* __restrict__ jobs, i
   }
 }
 
-// w = the sum of the product's partial outputs (per entry in the order of
+// w = the sum of the product's partial outputs (per element in the order of
 // k_reduce_out), then the partial dots of k_kdots: one launch instead of two
-// (single job; the same bits as k_reduce_out followed by k_kdots)
-__global__ __launch_bounds__(1024) void k_reduce_dots(const RDSrc* __restrict__ srcs, int nsrc,
-                                                      const KJob* __restrict__ jobs, int ml, int mr, int mp,
-                                                      int i0, int nv, int pin) {
-  const KJob& J = jobs[0];
+// (the same bits as k_reduce_out followed by k_kdots)
+__device__ __forceinline__ void reduce_dots(const RDSrc* __restrict__ srcs, int nsrc, const KJob& J, int ml, int mr,
+                                            int mp, int i0, int nv, int pin) {
   const int64_t M = (int64_t)ml * mr * mp;
   const int c = dot_chunk(M);
   double* w = J.w;
@@ -716,6 +714,20 @@ __global__ __launch_bounds__(1024) void k_reduce_dots(const RDSrc* __restrict__ 
   }
   if (J.st->stop) return;
   block_dots_1k(J, w, i0, nv, parea(J, pin), red);
+}
+
+// one job, and one job per task (batched solves: summing a list with one thread
+// per entry and then the dots took 83 + 5 us a product over four 8 x 8 instances
+// of m = 8 to 32, 20 us this way)
+__global__ __launch_bounds__(1024) void k_reduce_dots(const RDSrc* __restrict__ srcs, int nsrc,
+                                                      const KJob* __restrict__ jobs, int ml, int mr, int mp,
+                                                      int i0, int nv, int pin) {
+  reduce_dots(srcs, nsrc, jobs[0], ml, mr, mp, i0, nv, pin);
+}
+__global__ __launch_bounds__(1024) void k_reduce_dots_list(const RDTask* __restrict__ tasks,
+                                                           const KJob* __restrict__ jobs, int i0, int nv, int pin) {
+  const RDTask& t = tasks[blockIdx.y];
+  reduce_dots(t.srcs, t.nsrc, jobs[blockIdx.y], t.ml, t.mr, t.mp, i0, nv, pin);
 }
 
 // classical Gram-Schmidt pass against V[0..j]: h = sums of P(pin); w -= sum h_i V_i;
@@ -2651,6 +2663,13 @@ hipError_t launch_reduce_dots(const RDSrc* srcs, int nsrc, const KJob* job, int 
                               int nv, int pin, hipStream_t s) {
   hipLaunchKernelGGL(k_reduce_dots, dim3(kRedBlocks), dim3(kDotThreads), 0, s, srcs, nsrc, job, ml, mr, mp, i0,
                      nv, pin);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_dots_list(const RDTask* tasks, const KJob* jobs, int nj, int i0, int nv, int pin,
+                                   hipStream_t s) {
+  if (nj == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_reduce_dots_list, dim3(kRedBlocks, nj), dim3(kDotThreads), 0, s, tasks, jobs, i0, nv, pin);
   return hipGetLastError();
 }
 

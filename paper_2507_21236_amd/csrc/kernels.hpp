@@ -127,6 +127,12 @@ constexpr int sw_strips(int m) { return (m + 15) / 16; }
 constexpr bool sw_on_mfma(int ma, int mb) {
   return ma <= 128 && mb <= 128 && ((ma % 16 == 0 && mb % 16 == 0) || gen_slice_lds(ma, mb, 8) == 0);
 }
+// Effective-operator updates take the matrix cores for every pair up to 128:
+// their tasks carry many items and outputs, and the slice form meets five
+// barriers an item (8 x 8 m = 32: 14.6 us a launch of the nodes next to the
+// leaves, 5.7 with one padded tile; a matvec of such a node, with a handful
+// of items per task, is 1 us slower that way).
+constexpr bool sw_env_mfma(int ma, int mb) { return ma <= 128 && mb <= 128; }
 // LDS bytes of its staged slice: whole K steps of rows, whole tiles of columns
 // (rows padded by two elements)
 constexpr size_t sw_mfma_lds(int ma, int mb, size_t esz) {

@@ -48,6 +48,9 @@ hipError_t launch_kdots(const KJob* jobs, int nj, int i0, int nv, int pin, int s
 // w = sum of a product's partial outputs, then launch_kdots' partial dots (one job)
 hipError_t launch_reduce_dots(const RDSrc* srcs, int nsrc, const KJob* job, int ml, int mr, int mp, int i0,
                               int nv, int pin, hipStream_t s);
+// the same over a list: job k sums task k's sources into its w
+hipError_t launch_reduce_dots_list(const RDTask* tasks, const KJob* jobs, int nj, int i0, int nv, int pin,
+                                   hipStream_t s);
 hipError_t launch_kortho(const KJob* jobs, int nj, int j, int pin, int norm_only, int set_alpha, int split,
                          hipStream_t s);
 hipError_t launch_kbeta(const KJob* jobs, int nj, int j, int64_t nmax, hipStream_t s);

@@ -94,7 +94,7 @@ void add_sw_task(SWGroup& g, SWTask t, int ns) {
   }
   for (int i = i0; i < i1; i++)
     g.flops += 2.0 * M * ((g.items[i].A ? t.ma : 0) + (g.items[i].B ? t.mb : 0));
-  if (sw_mfma(t.ma, t.mb)) {
+  if (t.pad || sw_mfma(t.ma, t.mb)) {
     for (int s = 0; s < ns; s++) g.wus.push_back(make_int4(ti, s, 0, 0));   // a wavefront per strip
   } else {
     for (int s = 0; s < ns; s++)
@@ -428,7 +428,7 @@ std::vector<int> env_pieces(const Model& M, const EnvPlan& P, int& cap_out) {
   for (size_t o = 0; o < P.outs.size(); o++) W += (int64_t)P.outs[o].items.size();
   const int64_t strips = (sw_strips(g.ma) + 3) / 4;
   const int64_t ntask = std::max<int64_t>(1, (kEnvWorkgroups + g.ns * strips - 1) / (g.ns * strips));
-  const int cap = sw_mfma(g.ma, g.mb) ? (int)std::max<int64_t>(4, (W + ntask - 1) / ntask) : 1 << 30;
+  const int cap = sw_env_mfma(g.ma, g.mb) ? (int)std::max<int64_t>(4, (W + ntask - 1) / ntask) : 1 << 30;
   for (size_t o = 0; o < P.outs.size(); o++) {
     const int w = (int)P.outs[o].items.size();
     pc[o] = w == 0 ? 0 : (w + cap - 1) / cap;
@@ -468,7 +468,7 @@ void build_env_dev(attn_handle* h, const EnvPlan& P, EnvDev& D) {
   const int nfc = (int)((F + fchunk - 1) / fchunk);
   int cap = 0;
   const std::vector<int> pieces = env_pieces(M, P, cap);
-  const bool multi = sw_mfma(ma, mb);
+  const bool multi = sw_env_mfma(ma, mb);
   const int64_t strips = (sw_strips(ma) + 3) / 4;
   size_t o0 = 0;
   while (o0 < P.outs.size()) {
@@ -2186,7 +2186,7 @@ struct Checker {
       if (wu.x < 0 || wu.x >= (int)g.tasks.size()) { fail("sandwich: task index"); return; }
       const SWTask& t = g.tasks[wu.x];
       if (t.ma != g.ma || t.mb != g.mb) { fail("sandwich: group dims"); return; }
-      const bool mf = sw_mfma(t.ma, t.mb);
+      const bool mf = t.pad ? sw_env_mfma(t.ma, t.mb) : sw_mfma(t.ma, t.mb);
       int64_t rows_hi;
       if (mf) {
         if (wu.z != 0) { fail("sandwich: strip"); return; }

@@ -1431,7 +1431,7 @@ hipError_t launch_sandwich(int dtype, int ma, int mb, const SWTask* tasks, const
     }
     return hipErrorInvalidValue;
   }
-  const bool mf = sw_on_mfma(ma, mb);
+  const bool mf = sw_on_mfma(ma, mb) || (outs && sw_env_mfma(ma, mb));
   if (dtype == 0) {
     if (!mf) {
       hipLaunchKernelGGL(k_sandwich_gen<double>, dim3(nwu), dim3(256), gen_slice_lds(ma, mb, 8), s, tasks, items,
