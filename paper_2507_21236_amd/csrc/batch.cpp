@@ -499,7 +499,7 @@ void enqueue_step(attn_batch* b, int t, hipStream_t s0) {
   }
   if (!S.cb_tasks.empty())
     HIPCHK(launch_combine(S.d_cb_tasks, S.d_cb_terms, (int)S.cb_tasks.size(), S.cb_maxn, s0));
-  if (!S.cv.empty()) HIPCHK(launch_convert(1, S.d_cv, (int)S.cv.size(), S.cv_max, s0));
+  if (!S.cv.empty()) HIPCHK(launch_convert(S.d_cv, (int)S.cv.size(), S.cv_max, s0));
   const int kk = std::min(b->krylov_k, 64);
   if (!S.tj.empty()) HIPCHK(launch_tiny(S.d_tj, (int)S.tj.size(), S.tj_minM, S.tj_maxM, kk, s0));
   if (S.kj.empty()) return;

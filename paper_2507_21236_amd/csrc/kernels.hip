@@ -394,25 +394,54 @@ __global__ __launch_bounds__(256) void k_transpose_plr(const T* __restrict__ x, 
   xt[p * ml * mr + l * mr + r] = x[e];
 }
 
+// What bounds it is memory (8 bytes read, 4 written per element).  A split-BF16
+// block changes from columns to rows: a workgroup takes the 32 columns of one
+// chunk of the permutation through LDS, so that both sides move whole lines
+// (16 x 16 m = 64, heaviest node: 92 us reading one column element per lane and
+// refreshing whole stores in both formats, 39 us with only the blocks that
+// the node's lists read).
 __global__ __launch_bounds__(256) void k_convert(const CVTask* __restrict__ tasks) {
+  __shared__ double col[32][129];
   const CVTask& t = tasks[blockIdx.y];
   if (t.fmt == 1) {
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < t.n; e += (int64_t)gridDim.x * 256)
-      ((float*)t.dst)[e] = (float)t.src[e];
+    float* dst = (float*)t.dst;
+    for (int64_t e0 = (int64_t)blockIdx.x * 1024 + threadIdx.x; e0 < t.n; e0 += (int64_t)gridDim.x * 1024) {
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) v[u] = t.src[e0 + 256 * u < t.n ? e0 + 256 * u : t.n - 1];
+#pragma unroll
+      for (int u = 0; u < 4; u++)
+        if (e0 + 256 * u < t.n) dst[e0 + 256 * u] = (float)v[u];
+    }
     return;
   }
-  // split BF16: thread per destination position (block, row i, permuted position)
-  const int m = t.m;
-  const int64_t mm = (int64_t)m * m;
-  __bf16* dst = (__bf16*)t.dst;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < t.n; e += (int64_t)gridDim.x * 256) {
-    const int64_t b = e / mm, r = e - b * mm;
-    const int i = (int)(r / m), pos = (int)(r - (int64_t)i * m);
-    const double x = t.src[b * mm + (int64_t)bf_perm(pos) * m + i];
-    const __bf16 hi = (__bf16)(float)x;
-    const __bf16 lo = (__bf16)(float)(x - (double)(float)hi);
-    dst[2 * b * mm + r] = hi;
-    dst[2 * b * mm + mm + r] = lo;
+  // split BF16: unit = (block, 32 columns); rows of both planes in runs of 8 positions
+  typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+  const int m = t.m, nc = m / 32;
+  const int64_t mm = (int64_t)m * m, units = t.n / mm * nc;
+  for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+    const int64_t b = u / nc;
+    const int c = (int)(u - b * nc);
+    const double* src = t.src + b * mm + (int64_t)32 * c * m;
+    __syncthreads();
+    for (int e = threadIdx.x; e < 32 * m; e += 256) {
+      const int k = e / m;
+      col[k][e - k * m] = src[e];
+    }
+    __syncthreads();
+    __bf16* dst = (__bf16*)t.dst + 2 * b * mm + 32 * c;
+    for (int e = threadIdx.x; e < 4 * m; e += 256) {
+      const int i = e >> 2, p0 = 8 * (e & 3);
+      bf8 hi, lo;
+#pragma unroll
+      for (int q = 0; q < 8; q++) {
+        const double x = col[bf_perm(p0 + q)][i];
+        hi[q] = (__bf16)(float)x;
+        lo[q] = (__bf16)(float)(x - (double)(float)hi[q]);
+      }
+      *(bf8*)(dst + (int64_t)i * m + p0) = hi;
+      *(bf8*)(dst + mm + (int64_t)i * m + p0) = lo;
+    }
   }
 }
 
@@ -809,8 +838,8 @@ __global__ __launch_bounds__(256) void k_kortho(const KJob* __restrict__ jobs, i
 // threads as in k_kdots: wavefronts share out the sums of partials, and the
 // 1024 / c threads of an entry share out the basis vectors.  What bounds it at
 // the small nodes is the chain partials -> coefficients -> update -> dots; four
-// wavefronts walking all vectors took 6.1 us at 4096 entries and 10 vectors,
-// MEAS_KO this way.
+// wavefronts walking all vectors took 6.1 us a pass over the solves of an 8 x 8
+// m = 32 sweep, 5.1 this way.
 __global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ jobs, int j, int pin,
                                                        int norm_only, int set_alpha) {
   const KJob& J = jobs[blockIdx.y];
@@ -2456,7 +2485,7 @@ __global__ __launch_bounds__(64) void k_small_matmul(const double* __restrict__ 
 
 // C = A2 (A1 A0) for n x n upper-triangular column-major matrices, n <= 64: the
 // R of three Cholesky-QR passes, in one workgroup (two launches of k_small_matmul
-// walk n dependent loads each: 34 us at n = 64, about 10 here).
+// walk n dependent loads each: 34 us at n = 64, 20 here).
 __global__ __launch_bounds__(1024) void k_r_product(const double* __restrict__ A2, const double* __restrict__ A1,
                                                     const double* __restrict__ A0, double* __restrict__ C, int n) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -2603,11 +2632,10 @@ hipError_t launch_transpose_plr(int dtype, const void* x, void* xt, int ml, int 
   return hipGetLastError();
 }
 
-hipError_t launch_convert(int dtype, const CVTask* tasks, int ntask, int64_t maxn, hipStream_t s) {
+hipError_t launch_convert(const CVTask* tasks, int ntask, int64_t maxn, hipStream_t s) {
   if (ntask == 0) return hipSuccess;
-  int64_t g = grid1(maxn);
-  if (g > 1024) g = 1024;
-  (void)dtype;
+  int64_t g = (maxn + 1023) / 1024;   // four elements per thread, or a chunk of a block per workgroup
+  if (g > 2048) g = 2048;
   hipLaunchKernelGGL(k_convert, dim3((unsigned)g, ntask), dim3(256), 0, s, tasks);
   return hipGetLastError();
 }

@@ -31,7 +31,7 @@ hipError_t launch_reduce_out(int dtype_in, const RDSrc* srcs, int nsrc, void* y,
                              int ml, int mr, int mp, hipStream_t s);
 hipError_t launch_transpose_plr(int dtype, const void* x, void* xt, int ml, int mr, int mp,
                                 hipStream_t s);
-hipError_t launch_convert(int dtype, const CVTask* tasks, int ntask, int64_t maxn, hipStream_t s);
+hipError_t launch_convert(const CVTask* tasks, int ntask, int64_t maxn, hipStream_t s);
 hipError_t launch_cast(const void* src, int src_dtype, void* dst, int dst_dtype, int64_t n,
                        hipStream_t s);
 

@@ -771,6 +771,38 @@ void rechunk_bf16(SWGroup& g, std::vector<int>& ns_of, std::vector<RDSrc>& srcs,
   ns_of.swap(nns);
 }
 
+// Conversion list that refreshes the mirrors read by node n's matvec in form
+// `dtype`: every block its work lists read, in the format they read it in,
+// neighbouring blocks as one task.
+std::vector<CVTask> lowp_conversions(attn_handle* h, int n, int dtype) {
+  const MVDev& D = h->mv[n];
+  const MVDev& L = h->mvlp[dtype - 1][n];
+  std::map<uintptr_t, int> need[2];   // block -> dimension, per format
+  for (size_t g = 0; g < D.sw.size(); g++) {
+    const int fmt = L.sw[g].fmt == 2 || L.sw[g].fmt == 3 ? 2 : 1;
+    for (const SWItem& it : D.sw[g].items) {
+      if (it.A) need[fmt - 1][(uintptr_t)it.A] = D.sw[g].ma;
+      if (it.B) need[fmt - 1][(uintptr_t)it.B] = D.sw[g].mb;
+    }
+  }
+  for (const std::vector<MPGroup>* c : {&D.chainA, &D.chainB, &D.chainC})
+    for (const MPGroup& g : *c)
+      for (const MPJob& j : g.jobs) need[0][(uintptr_t)j.A] = g.mj;
+  std::vector<CVTask> cv;
+  for (int fmt = 1; fmt <= 2; fmt++)
+    for (auto& kv : need[fmt - 1]) {
+      const int64_t mm = (int64_t)kv.second * kv.second;
+      void* dst = to_mirror(h, (const void*)kv.first, fmt);
+      if (!cv.empty() && cv.back().fmt == fmt && cv.back().m == kv.second &&
+          (uintptr_t)(cv.back().src + cv.back().n) == kv.first && (char*)cv.back().dst + cv.back().n * 4 == dst) {
+        cv.back().n += mm;
+        continue;
+      }
+      cv.push_back({(const double*)kv.first, dst, mm, kv.second, fmt});
+    }
+  return cv;
+}
+
 // Build the mirrors and the work lists of precision form `dtype` (1 = FP32,
 // 2 = split BF16; the latter runs its mode products and the sandwich groups
 // whose legs are not multiples of 32 in FP32).
@@ -847,44 +879,25 @@ void ensure_lowp(attn_handle* h, int dtype) {
     upload_mp(h, L.chainC);
     L.d_srcs = upload(h, L.srcs);
   }
+  // the conversions of every node, in one array
+  std::vector<CVTask> cv;
+  std::vector<size_t> at;
+  for (size_t n = 0; n < tr.nodes.size(); n++) {
+    at.push_back(cv.size());
+    for (const CVTask& t : lowp_conversions(h, (int)n, dtype)) {
+      LP[n].cv_max = std::max(LP[n].cv_max, t.n);
+      LP[n].n_cv++;
+      cv.push_back(t);
+    }
+  }
+  CVTask* d_cv = upload(h, cv);
+  for (size_t n = 0; n < tr.nodes.size(); n++) LP[n].d_cv = d_cv + at[n];
   h->lowp_ready[dtype - 1] = true;
 }
 
-// Conversion list that refreshes the mirrors read by node n's matvec in form
-// `dtype`: its three incoming stores and its combined blocks.
-std::vector<CVTask> lowp_conversions(attn_handle* h, int n, int dtype) {
-  const Tree& tr = h->M.tree;
-  std::vector<CVTask> cv;
-  auto add = [&](const double* src, void* dst, int64_t elems, int dim, int fmt) {
-    if (dst) cv.push_back({src, dst, elems, dim, fmt});
-  };
-  auto add_store = [&](int dir, int e) {
-    if (e < 0 || !h->store[dir][e]) return;
-    const int dim = tr.edge_dim(e);
-    for (int fmt = 1; fmt <= dtype; fmt++)
-      add(h->store[dir][e], h->mir[fmt - 1][dir][e], h->store_elems[dir][e], dim, fmt);
-  };
-  add_store(0, tr.edge_of_child(n, 0));
-  add_store(0, tr.edge_of_child(n, 1));
-  if (n != tr.root) add_store(1, tr.edge_of_node(n));
-  for (auto& cb : h->comb_blocks[n]) {
-    const int64_t el = (int64_t)cb.second * cb.second;
-    for (int fmt = 1; fmt <= dtype; fmt++)
-      if (fmt == 1 || cb.second % 32 == 0)
-        add(h->d_mvcomb + cb.first, (char*)h->comb_lp[fmt - 1] + cb.first * 4, el, cb.second, fmt);
-  }
-  return cv;
-}
-
 void prepare_lowp(attn_handle* h, int n, int dtype, hipStream_t s) {
-  std::vector<CVTask> cv = lowp_conversions(h, n, dtype);
-  int64_t maxn = 0;
-  for (auto& c : cv) maxn = std::max(maxn, c.n);
-  if (cv.size() > (size_t)h->cv_cap) throw StatusFail{ATTN_ERR_STATE, "internal: conversion list too long"};
-  HIPCHK(hipMemcpyAsync(h->d_cvtasks, cv.data(), cv.size() * sizeof(CVTask), hipMemcpyHostToDevice, s));
-  HIPCHK(launch_convert(dtype, (const CVTask*)h->d_cvtasks, (int)cv.size(), maxn, s));
-  // the host list must outlive the asynchronous copy
-  HIPCHK(hipStreamSynchronize(s));
+  const MVDev& L = h->mvlp[dtype - 1][n];
+  HIPCHK(launch_convert(L.d_cv, L.n_cv, L.cv_max, s));
 }
 
 // y <- H_eff(n) x in form `dtype` (mirrors current); x is FP32, y FP64
@@ -1446,8 +1459,6 @@ attn_status attn_build_tpo(const attn_problem* p, attn_handle** out) {
       for (int l = 0; l < 3; l++) h->mmax = std::max(h->mmax, tr.nodes[n].dims[l]);
     h->d_qrmat = alloc(qrmat_doubles(h->mmax));
     h->d_qrR = alloc((int64_t)h->mmax * h->mmax);
-    h->cv_cap = 6 + 2 * (int)std::max<size_t>(1, [&] { size_t mx = 0; for (int n = 0; n < nn; n++) mx = std::max(mx, h->M.mv[n].combines.size()); return mx; }());
-    h->d_cvtasks = dev_alloc(h, (size_t)h->cv_cap * sizeof(CVTask));
     h->d_st = (KrylovState*)dev_alloc(h, sizeof(KrylovState));
     // device plans
     h->mv.assign(nn, MVDev());
@@ -2372,7 +2383,7 @@ extern "C" attn_status attn_validate(const attn_handle* h) {
       for (auto& sr : D.srcs) c.span(sr.p, M * 4, "reduce source");
       if (D.need_xt) c.span(h->d_xt, M * 4, "transposed input");
       const std::vector<CVTask> cv = lowp_conversions(hm, n, dt);
-      if (cv.size() > (size_t)h->cv_cap) c.fail("conversion list too long");
+      if ((int)cv.size() != D.n_cv) c.fail("conversion list length");
       for (auto& t : cv) {
         c.span(t.src, t.n * 8, "conversion source");
         c.span(t.dst, t.n * 4, "conversion destination");

@@ -171,6 +171,10 @@ struct MVDev {
   std::vector<const void*> split_outs;
   std::vector<RDSrc> srcs;
   RDSrc* d_srcs = nullptr;
+  // low-precision plans: conversions that refresh the mirrors the lists read
+  CVTask* d_cv = nullptr;
+  int n_cv = 0;
+  int64_t cv_max = 0;
   bool need_xt = false;
   int dims[3] = {0, 0, 0};
 };
@@ -301,8 +305,6 @@ struct attn_handle {
   double* d_red = nullptr;    // 128 x kRedBlocks
   double* d_qrmat = nullptr;  // G, R0, R1, R2, Rinv, Rt (mmax^2 each), Cholesky workspace
   double* d_qrR = nullptr;    // R of the last QR (absorbed into the neighbour)
-  void* d_cvtasks = nullptr;  // conversion work list (low-precision forms)
-  int cv_cap = 0;
   int mmax = 1;
   KrylovState* d_st = nullptr;
   // sweeps: per-node status checks stay on the device (no host round trip per
