@@ -45,14 +45,14 @@ __device__ __forceinline__ double sum_grouped(const RDSrc* __restrict__ srcs, in
 
 // ============================================================================ mode product
 // (device bodies: mode_body.hpp)
-template <typename T, int NI, int QS, int FT>
-__global__ __launch_bounds__(256) void k_mode(const MPTask* __restrict__ tasks,
+template <typename T, int NI, int QS, int FT, int NW>
+__global__ __launch_bounds__(512) void k_mode(const MPTask* __restrict__ tasks,
                                               const MPJob* __restrict__ jobs,
                                               const int2* __restrict__ wus,
                                               const T* __restrict__ xbase) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int2 wu = wus[blockIdx.x];
-  mode_mfma<T, NI, QS, FT>(tasks[wu.x], jobs, wu, blockIdx.y, xbase, smem_raw);
+  mode_mfma<T, NI, QS, FT, NW>(tasks[wu.x], jobs, wu, blockIdx.y, xbase, smem_raw);
 }
 
 template <typename T>
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(256) void k_transpose_plr(const T* __restrict__ x, 
 // block changes from columns to rows: a workgroup takes the 32 columns of one
 // chunk of the permutation through LDS, so that both sides move whole lines
 // (16 x 16 m = 64, heaviest node: 92 us reading one column element per lane and
-// refreshing whole stores in both formats, 39 us with only the blocks that
+// refreshing whole stores in both formats, 31 us with only the blocks that
 // the node's lists read).
 __global__ __launch_bounds__(256) void k_convert(const CVTask* __restrict__ tasks) {
   __shared__ double col[32][129];
@@ -2521,7 +2521,7 @@ template <typename T, int NI>
 static hipError_t mode_launch(int mj, const MPTask* tasks, const MPJob* jobs, const int2* wus, int nwu,
                               const void* xbase, hipStream_t s) {
   constexpr ModeTile m = mode_tile(NI);
-  hipLaunchKernelGGL((k_mode<T, NI, m.qs, m.ft>), dim3(nwu, 64 / mode_width(m)), dim3(256), mode_lds(mj, m, sizeof(T)),
+  hipLaunchKernelGGL((k_mode<T, NI, m.qs, m.ft, m.nw>), dim3(nwu, 64 / mode_width(m)), dim3(64 * m.nw), mode_lds(mj, m, sizeof(T)),
                      s, tasks, jobs, wus, (const T*)xbase);
   return hipGetLastError();
 }
@@ -2846,22 +2846,22 @@ hipError_t prepare_kernel_attributes() {
   if (hipError_t e = prepare_sandwich_attributes()) return e;
   const void* fns[] = {
       (const void*)k_batch_mode<double>, (const void*)k_batch_mode<float>,
-      (const void*)k_mode<double, 1, mode_tile(1).qs, mode_tile(1).ft>,
-      (const void*)k_mode<double, 2, mode_tile(2).qs, mode_tile(2).ft>,
-      (const void*)k_mode<double, 3, mode_tile(3).qs, mode_tile(3).ft>,
-      (const void*)k_mode<double, 4, mode_tile(4).qs, mode_tile(4).ft>,
-      (const void*)k_mode<double, 5, mode_tile(5).qs, mode_tile(5).ft>,
-      (const void*)k_mode<double, 6, mode_tile(6).qs, mode_tile(6).ft>,
-      (const void*)k_mode<double, 7, mode_tile(7).qs, mode_tile(7).ft>,
-      (const void*)k_mode<double, 8, mode_tile(8).qs, mode_tile(8).ft>,
-      (const void*)k_mode<float, 1, mode_tile(1).qs, mode_tile(1).ft>,
-      (const void*)k_mode<float, 2, mode_tile(2).qs, mode_tile(2).ft>,
-      (const void*)k_mode<float, 3, mode_tile(3).qs, mode_tile(3).ft>,
-      (const void*)k_mode<float, 4, mode_tile(4).qs, mode_tile(4).ft>,
-      (const void*)k_mode<float, 5, mode_tile(5).qs, mode_tile(5).ft>,
-      (const void*)k_mode<float, 6, mode_tile(6).qs, mode_tile(6).ft>,
-      (const void*)k_mode<float, 7, mode_tile(7).qs, mode_tile(7).ft>,
-      (const void*)k_mode<float, 8, mode_tile(8).qs, mode_tile(8).ft>,
+      (const void*)k_mode<double, 1, mode_tile(1).qs, mode_tile(1).ft, mode_tile(1).nw>,
+      (const void*)k_mode<double, 2, mode_tile(2).qs, mode_tile(2).ft, mode_tile(2).nw>,
+      (const void*)k_mode<double, 3, mode_tile(3).qs, mode_tile(3).ft, mode_tile(3).nw>,
+      (const void*)k_mode<double, 4, mode_tile(4).qs, mode_tile(4).ft, mode_tile(4).nw>,
+      (const void*)k_mode<double, 5, mode_tile(5).qs, mode_tile(5).ft, mode_tile(5).nw>,
+      (const void*)k_mode<double, 6, mode_tile(6).qs, mode_tile(6).ft, mode_tile(6).nw>,
+      (const void*)k_mode<double, 7, mode_tile(7).qs, mode_tile(7).ft, mode_tile(7).nw>,
+      (const void*)k_mode<double, 8, mode_tile(8).qs, mode_tile(8).ft, mode_tile(8).nw>,
+      (const void*)k_mode<float, 1, mode_tile(1).qs, mode_tile(1).ft, mode_tile(1).nw>,
+      (const void*)k_mode<float, 2, mode_tile(2).qs, mode_tile(2).ft, mode_tile(2).nw>,
+      (const void*)k_mode<float, 3, mode_tile(3).qs, mode_tile(3).ft, mode_tile(3).nw>,
+      (const void*)k_mode<float, 4, mode_tile(4).qs, mode_tile(4).ft, mode_tile(4).nw>,
+      (const void*)k_mode<float, 5, mode_tile(5).qs, mode_tile(5).ft, mode_tile(5).nw>,
+      (const void*)k_mode<float, 6, mode_tile(6).qs, mode_tile(6).ft, mode_tile(6).nw>,
+      (const void*)k_mode<float, 7, mode_tile(7).qs, mode_tile(7).ft, mode_tile(7).nw>,
+      (const void*)k_mode<float, 8, mode_tile(8).qs, mode_tile(8).ft, mode_tile(8).nw>,
       (const void*)k_mlp_grad, (const void*)k_r_product};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);

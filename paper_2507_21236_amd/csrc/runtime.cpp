@@ -773,10 +773,12 @@ void rechunk_bf16(SWGroup& g, std::vector<int>& ns_of, std::vector<RDSrc>& srcs,
 
 // Conversion list that refreshes the mirrors read by node n's matvec in form
 // `dtype`: every block its work lists read, in the format they read it in,
-// neighbouring blocks as one task.
+// neighbouring blocks as one task of up to kConvertRun elements (a launch gives
+// every task the workgroups of the longest).
 std::vector<CVTask> lowp_conversions(attn_handle* h, int n, int dtype) {
   const MVDev& D = h->mv[n];
   const MVDev& L = h->mvlp[dtype - 1][n];
+  constexpr int64_t kConvertRun = (int64_t)1 << 16;
   std::map<uintptr_t, int> need[2];   // block -> dimension, per format
   for (size_t g = 0; g < D.sw.size(); g++) {
     const int fmt = L.sw[g].fmt == 2 || L.sw[g].fmt == 3 ? 2 : 1;
@@ -793,7 +795,7 @@ std::vector<CVTask> lowp_conversions(attn_handle* h, int n, int dtype) {
     for (auto& kv : need[fmt - 1]) {
       const int64_t mm = (int64_t)kv.second * kv.second;
       void* dst = to_mirror(h, (const void*)kv.first, fmt);
-      if (!cv.empty() && cv.back().fmt == fmt && cv.back().m == kv.second &&
+      if (!cv.empty() && cv.back().fmt == fmt && cv.back().m == kv.second && cv.back().n + mm <= kConvertRun &&
           (uintptr_t)(cv.back().src + cv.back().n) == kv.first && (char*)cv.back().dst + cv.back().n * 4 == dst) {
         cv.back().n += mm;
         continue;
