@@ -46,10 +46,13 @@ T* upload_tmp(attn_handle* h, Buf& b, const std::vector<T>& v, hipStream_t s) {
   return p;
 }
 
-// GEMM jobs of one launch.  A launch with few 64 x 64 tiles of a long
+// GEMM jobs of one list, launched by tile: 32 for results with a side of up to
+// 32, else 64 (correlation matrices of 8 x 8 lattices, ms: links of 32, 28.8 with
+// tiles of 32 and 32.6 of 64; of 80, 469 and 370; of 96, 631 and 553, where the
+// smaller tiles read A and B too often).  A list with few tiles of a long
 // contraction is cut along K into partial products (about 1024 work units, at
-// least 128 of K each), summed in order by a second launch: a single tile walks
-// K at the latency of its loads (K = 1024: 77 us).
+// least 128 of K each), summed in order by another launch: a single tile walks
+// K at the latency of its loads (K = 1024 in a 64 x 64 tile: 77 us).
 struct GemmList {
   std::vector<GMJob> jobs;
   std::vector<int> batches;
@@ -57,19 +60,22 @@ struct GemmList {
     jobs.push_back(j);
     batches.push_back(batch);
   }
+  static int tile(const GMJob& j) { return j.M <= 32 || j.N <= 32 ? 32 : 64; }
   void run(attn_handle* h, Buf& buf, hipStream_t s) {
     if (jobs.empty()) return;
     int64_t units = 0;
-    for (size_t i = 0; i < jobs.size(); i++)
-      units += (int64_t)batches[i] * ((jobs[i].M + 63) / 64) * ((jobs[i].N + 63) / 64);
+    for (size_t i = 0; i < jobs.size(); i++) {
+      const int t = tile(jobs[i]);
+      units += (int64_t)batches[i] * ((jobs[i].M + t - 1) / t) * ((jobs[i].N + t - 1) / t);
+    }
     const int64_t want = std::max<int64_t>(1, 1024 / units);
     std::vector<GMJob> out;
-    std::vector<int4> wus;
+    std::vector<int4> wus[2];   // tiles of 64, of 32
     std::vector<SPJob> sums;
     int64_t maxn = 0;
     for (size_t i = 0; i < jobs.size(); i++) {
       const GMJob& j = jobs[i];
-      const int nb = batches[i], tm = (j.M + 63) / 64, tn = (j.N + 63) / 64;
+      const int t = tile(j), nb = batches[i], tm = (j.M + t - 1) / t, tn = (j.N + t - 1) / t;
       const int64_t n = (int64_t)j.M * j.N;
       const bool whole = j.ldc == j.N && (nb == 1 || j.sc == n) && !j.accumulate;   // one contiguous result
       const int q = whole ? (int)std::max<int64_t>(1, std::min<int64_t>(want, j.K / 128)) : 1;
@@ -86,7 +92,7 @@ struct GemmList {
         out.push_back(c);
         for (int b = 0; b < nb; b++)
           for (int x = 0; x < tm; x++)
-            for (int y = 0; y < tn; y++) wus.push_back(int4{id, b, x, y});
+            for (int y = 0; y < tn; y++) wus[t == 32].push_back(int4{id, b, x, y});
       }
       if (part) {
         sums.push_back(SPJob{part, j.C, nb * n, nb * n, nq, 0});
@@ -94,8 +100,11 @@ struct GemmList {
       }
     }
     GMJob* dj = upload_tmp(h, buf, out, s);
-    int4* dw = upload_tmp(h, buf, wus, s);
-    HIPCHK(launch_gemm_jobs(dj, dw, (int)wus.size(), s));
+    for (int k = 0; k < 2; k++) {
+      if (wus[k].empty()) continue;
+      int4* dw = upload_tmp(h, buf, wus[k], s);
+      HIPCHK(launch_gemm_jobs(dj, dw, (int)wus[k].size(), k ? 32 : 64, s));
+    }
     if (!sums.empty()) {
       SPJob* ds = upload_tmp(h, buf, sums, s);
       HIPCHK(launch_sum_parts(ds, (int)sums.size(), maxn, s));

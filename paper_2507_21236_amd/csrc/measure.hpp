@@ -36,8 +36,8 @@ struct SPJob {
   int32_t nq, pad;
 };
 
-// work units: int4 {job, batch index, 64-row tile, 64-column tile}
-hipError_t launch_gemm_jobs(const GMJob* jobs, const int4* wus, int nwu, hipStream_t s);
+// work units: int4 {job, batch index, row tile, column tile}, tiles of 64 or 32
+hipError_t launch_gemm_jobs(const GMJob* jobs, const int4* wus, int nwu, int tile, hipStream_t s);
 hipError_t launch_permute_jobs(const PMJob* jobs, int njob, int64_t maxM, hipStream_t s);
 hipError_t launch_sum_parts(const SPJob* jobs, int njob, int64_t maxn, hipStream_t s);
 // out[p] = sum_e base[pairs[p].x * M + e] * base[pairs[p].y * M + e] (one workgroup per pair)

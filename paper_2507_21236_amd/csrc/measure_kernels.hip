@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "measure.hpp"
+#include "mfma_common.hpp"
 
 namespace attn {
 
@@ -88,6 +89,96 @@ __global__ __launch_bounds__(256) void k_gemm_jobs(const GMJob* __restrict__ job
   }
 }
 
+// The same for results that fill 64 x 64 tiles badly (the images and Gram
+// matrices of links up to 32): a 32 x 32 tile per workgroup on
+// the matrix cores, the four wavefronts sharing out K inside each step and their
+// sums added in order at the end.  A 32 x 32 result of a 64 x 64 tile leaves three
+// quarters of its products unused.  Reading A and B bounds it: 512 images of an
+// 8 x 8 lattice at m = 32 (K = 1024, 268 MB) took 136 to 150 us, here 82
+// (3.3 TB/s); its 64 x 64 correlation matrix 32.6 ms before, 28.8 now.
+__global__ __launch_bounds__(256) void k_gemm_jobs32(const GMJob* __restrict__ jobs, const int4* __restrict__ wus) {
+  constexpr int KC = 64, ld = 34;
+  __shared__ double lds[2 * KC * ld];   // A and B of one step, [k][i]; then the wavefronts' sums
+  double* As = lds;
+  double* Bs = lds + KC * ld;
+  const int4 wu = wus[blockIdx.x];
+  const GMJob& J = jobs[wu.x];
+  const double* A = J.A + (int64_t)wu.y * J.sa;
+  const double* B = J.B + (int64_t)wu.y * J.sb;
+  double* C = J.C + (int64_t)wu.y * J.sc;
+  const int m0 = wu.z * 32, n0 = wu.w * 32;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, l4 = lane >> 4;
+  const int kc = J.K > 32 ? 64 : 32, kw = kc / 4;   // K of a step, and of a wavefront in it
+  double ra[8], rb[8];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      const int e = tid + 256 * q;
+      const int i = J.ta ? e & 31 : e / kc, k = J.ta ? e >> 5 : e % kc;
+      const int gi = m0 + i, gk = k0 + k;
+      const bool in = i < 32 && k < kc && gi < J.M && gk < J.K;
+      const double v = A[in ? (J.ta ? (int64_t)gk * J.lda + gi : (int64_t)gi * J.lda + gk) : 0];
+      ra[q] = in ? v : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      const int e = tid + 256 * q;
+      const int j = J.tb ? e / kc : e & 31, k = J.tb ? e % kc : e >> 5;
+      const int gj = n0 + j, gk = k0 + k;
+      const bool in = j < 32 && k < kc && gj < J.N && gk < J.K;
+      const double v = B[in ? (J.tb ? (int64_t)gj * J.ldb + gk : (int64_t)gk * J.ldb + gj) : 0];
+      rb[q] = in ? v : 0.0;
+    }
+  };
+  d4 acc[2][2];
+#pragma unroll
+  for (int r = 0; r < 2; r++)
+#pragma unroll
+    for (int c = 0; c < 2; c++) acc[r][c] = d4{0, 0, 0, 0};
+  load(0);
+  for (int k0 = 0; k0 < J.K; k0 += kc) {
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+      const int e = tid + 256 * q;
+      const int ia = J.ta ? e & 31 : e / kc, ka = J.ta ? e >> 5 : e % kc;
+      if (ia < 32 && ka < kc) As[ka * ld + ia] = ra[q];
+      const int jb = J.tb ? e / kc : e & 31, kb = J.tb ? e % kc : e >> 5;
+      if (jb < 32 && kb < kc) Bs[kb * ld + jb] = rb[q];
+    }
+    __syncthreads();
+    if (k0 + kc < J.K) load(k0 + kc);
+    for (int ks = 0; ks < kw; ks += 4) {
+      const int k = wave * kw + ks + l4;
+      double a[2], b[2];
+#pragma unroll
+      for (int r = 0; r < 2; r++) a[r] = As[k * ld + 16 * r + l16];
+#pragma unroll
+      for (int c = 0; c < 2; c++) b[c] = Bs[k * ld + 16 * c + l16];
+#pragma unroll
+      for (int r = 0; r < 2; r++)
+#pragma unroll
+        for (int c = 0; c < 2; c++) acc[r][c] = mfma16(a[r], b[c], acc[r][c]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < 2; r++)
+#pragma unroll
+    for (int c = 0; c < 2; c++)
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+        lds[wave * 1024 + (16 * r + drow<double>(l4, i)) * 32 + 16 * c + l16] = acc[r][c][i];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const int e = tid + 256 * q, gi = m0 + (e >> 5), gj = n0 + (e & 31);
+    if (gi >= J.M || gj >= J.N) continue;
+    const double v = lds[e] + lds[1024 + e] + lds[2048 + e] + lds[3072 + e];
+    double* p = C + (int64_t)gi * J.ldc + gj;
+    *p = J.accumulate ? *p + v : v;
+  }
+}
+
 __global__ __launch_bounds__(256) void k_permute_jobs(const PMJob* __restrict__ jobs) {
   const PMJob& J = jobs[blockIdx.y];
   const int64_t M = (int64_t)J.d0 * J.d1 * J.d2;
@@ -132,9 +223,10 @@ static unsigned grid_for(int64_t n) {
   return (unsigned)(g > 1024 ? 1024 : (g < 1 ? 1 : g));
 }
 
-hipError_t launch_gemm_jobs(const GMJob* jobs, const int4* wus, int nwu, hipStream_t s) {
+hipError_t launch_gemm_jobs(const GMJob* jobs, const int4* wus, int nwu, int tile, hipStream_t s) {
   if (nwu <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gemm_jobs, dim3(nwu), dim3(256), 0, s, jobs, wus);
+  if (tile == 32) hipLaunchKernelGGL(k_gemm_jobs32, dim3(nwu), dim3(256), 0, s, jobs, wus);
+  else hipLaunchKernelGGL(k_gemm_jobs, dim3(nwu), dim3(256), 0, s, jobs, wus);
   return hipGetLastError();
 }
 
