@@ -515,9 +515,14 @@ void enqueue_step(attn_batch* b, int t, hipStream_t s0) {
       break;
     }
     run_matvec(b, S.mv, s0, J, 0, j + 1, 1);
-    HIPCHK(launch_kortho(J, nj, j, 1, 0, 1, b->precision == ATTN_F64, s0));
-    HIPCHK(launch_kortho(J, nj, j, 2, 1, 0, b->precision == ATTN_F64, s0));
-    HIPCHK(launch_kbeta(J, nj, j, S.kj_max, s0));
+    if (b->precision == ATTN_F64) {
+      HIPCHK(launch_kortho_split(J, nj, j, 0, s0));
+      HIPCHK(launch_kortho_split(J, nj, j, 1, s0));
+    } else {
+      HIPCHK(launch_kortho(J, nj, j, 0, s0));
+      HIPCHK(launch_kortho(J, nj, j, 1, s0));
+      HIPCHK(launch_kbeta(J, nj, j, S.kj_max, s0));
+    }
   }
   HIPCHK(launch_ktridiag(J, nj, s0));
   HIPCHK(launch_kritz(J, nj, s0));

@@ -759,11 +759,10 @@ __global__ __launch_bounds__(1024) void k_reduce_dots_list(const RDTask* __restr
   reduce_dots(t.srcs, t.nsrc, jobs[blockIdx.y], t.ml, t.mr, t.mp, i0, nv, pin);
 }
 
-// classical Gram-Schmidt pass against V[0..j]: h = sums of P(pin); w -= sum h_i V_i;
-// then P(pin + 1) = partial dots V[0..j] . w, or ||w||^2 when norm_only.
-// set_alpha (first pass): alpha_j = h_j.
-__global__ __launch_bounds__(256) void k_kortho(const KJob* __restrict__ jobs, int j, int pin,
-                                                int norm_only, int set_alpha) {
+// classical Gram-Schmidt pass of the low-precision solves against V[0..j]:
+// h = sums of P1 (first pass; alpha_j = h_j) or P2; w -= sum h_i V_i; then P2 =
+// partial dots V[0..j] . w, or after the second pass P3 = those of ||w||^2.
+__global__ __launch_bounds__(256) void k_kortho(const KJob* __restrict__ jobs, int j, int second) {
   __shared__ double red[4];
   __shared__ double hs[128];
   const KJob& J = jobs[blockIdx.y];
@@ -772,13 +771,13 @@ __global__ __launch_bounds__(256) void k_kortho(const KJob* __restrict__ jobs, i
   const int64_t n = J.n;
   double* w = J.w;
   __shared__ double red8[4 * kDotChunk];
-  sums_of_partials(parea(J, pin), nv, hs, red8);
-  if (set_alpha && blockIdx.x == 0 && threadIdx.x == 0) {
+  sums_of_partials(parea(J, second ? 2 : 1), nv, hs, red8);
+  if (!second && blockIdx.x == 0 && threadIdx.x == 0) {
     J.st->alpha[j] = hs[j];
     if (!isfinite(hs[j])) fail_status(J.st, 1);
   }
   const int b = blockIdx.x;
-  double* po = parea(J, pin + 1);
+  double* po = parea(J, second ? 3 : 2);
   if ((n & 1) == 0) {
     // even n: element pairs (2 e, 2 e + 1) per thread, 16-byte loads
     const int64_t np = n / 2;
@@ -788,7 +787,7 @@ __global__ __launch_bounds__(256) void k_kortho(const KJob* __restrict__ jobs, i
       for (int i = 0; i < nv; i++) x -= hs[i] * reinterpret_cast<const dv2*>(J.V + (int64_t)i * n)[e];
       w2[e] = x;
     }
-    if (norm_only) {
+    if (second) {
       double acc = 0;
       for (int64_t e = (int64_t)b * 256 + threadIdx.x; e < np; e += (int64_t)kRedBlocks * 256) {
         const dv2 x = w2[e];
@@ -823,7 +822,7 @@ __global__ __launch_bounds__(256) void k_kortho(const KJob* __restrict__ jobs, i
     for (int i = 0; i < nv; i++) x -= hs[i] * J.V[(int64_t)i * n + e];
     w[e] = x;
   }
-  if (norm_only) {
+  if (second) {
     double acc = 0;
     for (int64_t e = (int64_t)b * 256 + threadIdx.x; e < n; e += (int64_t)kRedBlocks * 256)
       acc += w[e] * w[e];
@@ -834,35 +833,74 @@ __global__ __launch_bounds__(256) void k_kortho(const KJob* __restrict__ jobs, i
   block_dots(J, w, nv, po, red8);
 }
 
-// The same pass for FP64 solves, with the entries dealt to blocks of 1024
-// threads as in k_kdots: wavefronts share out the sums of partials, and the
-// 1024 / c threads of an entry share out the basis vectors.  What bounds it at
-// the small nodes is the chain partials -> coefficients -> update -> dots; four
+// largest |alpha_k| of the first j + 1 <= 64 steps, by each wavefront: one load
+// per lane (a loop over them waits for each in turn)
+__device__ __forceinline__ double max_alpha(const KrylovState* st, int j) {
+  const int lane = threadIdx.x & 63;
+  return wave_max(lane <= j ? fabs(st->alpha[lane]) : 0.0);
+}
+
+// beta_j of a step and its breakdown test, by every block alike; block 0 records
+// them.  The caller's barrier before it: the block has read the state by then.
+__device__ __forceinline__ bool set_beta(KrylovState* st, int j, double b, double amax) {
+  const bool brk = !(b > 1e-14 * amax);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (!isfinite(b)) fail_status(st, 1);
+    if (brk) st->stop = 1;
+    else { st->beta[j] = b; st->keff = j + 2; }
+  }
+  return brk;
+}
+
+// The passes of FP64 solves, with the entries dealt to blocks of 1024 threads
+// as in k_kdots: wavefronts share out the sums of partials, and the 1024 / c
+// threads of an entry share out the basis vectors.  What bounds them at the
+// small nodes is the chain partials -> coefficients -> update -> dots; four
 // wavefronts walking all vectors took 6.1 us a pass over the solves of an 8 x 8
 // m = 32 sweep, 5.1 this way.
-__global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ jobs, int j, int pin,
-                                                       int norm_only, int set_alpha) {
+// The first pass takes the coefficients from P1 and leaves the dots of V[0..j]
+// with the new w in P2 and ||w||^2 in P3.  The second takes its coefficients h
+// from P2, and beta_j^2 = ||w||^2 - sum h^2 is then known before its update:
+// it writes V_{j+1} (and the copies) itself, where summing the norm of the
+// result needed one more launch (heaviest node of 8 x 8 m = 16: a solve of 20
+// steps 931 us so, 864 now).  No digits are lost: h is what
+// rounding left along V after the first pass, so sum h^2 reaches a sizeable share of
+// ||w||^2 only where beta_j is of that rounding's size, which the breakdown
+// test ends.
+template <bool SECOND>
+__global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ jobs, int j) {
   const KJob& J = jobs[blockIdx.y];
-  if (J.st->stop) return;
+  KrylovState* st = J.st;
   __shared__ double hs[64], part[1024], red[64 * kDotChunk];
+  __shared__ int stop;
   const int nv = j + 1, t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  if (t == 0) stop = st->stop;   // once: block 0 of a second pass may set it meanwhile
   const int64_t n = J.n;
-  const double* P = parea(J, pin);
-  for (int q = wave; q < nv; q += 16) {
+  const double* P = parea(J, SECOND ? 2 : 1);
+  for (int q = wave; q < nv + SECOND; q += 16) {
+    const double* pq = q < nv ? P + q * kRedBlocks : parea(J, 3);
     double v = 0;
 #pragma unroll
-    for (int u = 0; u < kRedBlocks / 64; u++) v += P[q * kRedBlocks + lane + 64 * u];
+    for (int u = 0; u < kRedBlocks / 64; u++) v += pq[lane + 64 * u];
     v = wave_sum(v);
     if (lane == 0) hs[q] = v;
   }
+  const double amax = SECOND ? max_alpha(st, j) : 0.0;
   __syncthreads();
-  if (set_alpha && blockIdx.x == 0 && t == 0) {
-    J.st->alpha[j] = hs[j];
-    if (!isfinite(hs[j])) fail_status(J.st, 1);
+  if (stop) return;
+  double inv = 0;
+  if (SECOND) {
+    const double d = hs[nv] - wave_sum(lane < nv ? hs[lane] * hs[lane] : 0.0);
+    const double b = sqrt(d < 0.0 ? 0.0 : d);
+    if (set_beta(st, j, b, amax)) return;
+    inv = 1.0 / b;
+  } else if (blockIdx.x == 0 && t == 0) {
+    st->alpha[j] = hs[j];
+    if (!isfinite(hs[j])) fail_status(st, 1);
   }
   const int c = dot_chunk(n), S = 1024 / c, g = t / c, i = t - g * c;
   double* w = J.w;
-  double* po = parea(J, pin + 1);
+  double* out = J.V + (int64_t)(j + 1) * n;
   double nrm = 0;
   for (int64_t e0 = (int64_t)blockIdx.x * c; e0 < n; e0 += (int64_t)kRedBlocks * c) {   // once when c < 1024
     const int64_t e = e0 + i;
@@ -881,30 +919,33 @@ __global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ 
     }
     if (g == 0 && e < n) {
       const double x = w[e] - a;
-      w[e] = x;
-      part[i] = x;
-      nrm += x * x;
+      if (SECOND) {
+        out[e] = x * inv;
+        write_copies(J, e, x * inv);
+      } else {
+        w[e] = x;
+        part[i] = x;
+        nrm += x * x;
+      }
     } else if (g == 0) {
       part[i] = 0.0;
     }
   }
-  if (norm_only) {
-    const double s = wave_sum(nrm);
-    if (lane == 0) red[wave] = s;
-    __syncthreads();
-    if (t == 0) {
-      double v = 0;
-      for (int q = 0; q < 16; q++) v += red[q];
-      po[blockIdx.x] = v;
-    }
-    return;
+  if (SECOND) return;
+  const double s = wave_sum(nrm);
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  if (t == 0) {
+    double v = 0;
+    for (int q = 0; q < 16; q++) v += red[q];
+    parea(J, 3)[blockIdx.x] = v;
   }
   __syncthreads();
   if (S > 1) {
     const bool mine = (int64_t)blockIdx.x * c < n;   // part holds this block's entries
-    block_dots_split(J, mine ? part[i] : 0.0, c, 0, nv, po, red);
+    block_dots_split(J, mine ? part[i] : 0.0, c, 0, nv, parea(J, 2), red);
   } else {
-    block_dots_1k(J, w, 0, nv, po, red);
+    block_dots_1k(J, w, 0, nv, parea(J, 2), red);
   }
 }
 
@@ -915,16 +956,9 @@ __global__ __launch_bounds__(256) void k_kbeta(const KJob* __restrict__ jobs, in
   KrylovState* st = J.st;
   if (st->stop) return;
   const double b = sqrt(sum_partials(parea(J, 3), red));
-  double amax = 0;
-  for (int k = 0; k <= j; k++) amax = fmax(amax, fabs(st->alpha[k]));
-  const bool brk = !(b > 1e-14 * amax);
-  __syncthreads();   // every block has read the state before block 0 updates it
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    if (!isfinite(b)) fail_status(st, 1);
-    if (brk) st->stop = 1;
-    else { st->beta[j] = b; st->keff = j + 2; }
-  }
-  if (brk) return;
+  const double amax = max_alpha(st, j);
+  __syncthreads();
+  if (set_beta(st, j, b, amax)) return;
   const double inv = 1.0 / b;
   double* out = J.V + (int64_t)(j + 1) * J.n;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < J.n; e += (int64_t)gridDim.x * 256) {
@@ -2701,12 +2735,14 @@ hipError_t launch_reduce_dots_list(const RDTask* tasks, const KJob* jobs, int nj
   return hipGetLastError();
 }
 
-hipError_t launch_kortho(const KJob* jobs, int nj, int j, int pin, int norm_only, int set_alpha, int split,
-                         hipStream_t s) {
-  if (split)
-    hipLaunchKernelGGL(k_kortho_split, dim3(kRedBlocks, nj), dim3(1024), 0, s, jobs, j, pin, norm_only, set_alpha);
-  else
-    hipLaunchKernelGGL(k_kortho, dim3(kRedBlocks, nj), dim3(256), 0, s, jobs, j, pin, norm_only, set_alpha);
+hipError_t launch_kortho(const KJob* jobs, int nj, int j, int second, hipStream_t s) {
+  hipLaunchKernelGGL(k_kortho, dim3(kRedBlocks, nj), dim3(256), 0, s, jobs, j, second);
+  return hipGetLastError();
+}
+
+hipError_t launch_kortho_split(const KJob* jobs, int nj, int j, int second, hipStream_t s) {
+  if (second) hipLaunchKernelGGL(k_kortho_split<true>, dim3(kRedBlocks, nj), dim3(1024), 0, s, jobs, j);
+  else hipLaunchKernelGGL(k_kortho_split<false>, dim3(kRedBlocks, nj), dim3(1024), 0, s, jobs, j);
   return hipGetLastError();
 }
 

@@ -51,9 +51,11 @@ hipError_t launch_reduce_dots(const RDSrc* srcs, int nsrc, const KJob* job, int 
 // the same over a list: job k sums task k's sources into its w
 hipError_t launch_reduce_dots_list(const RDTask* tasks, const KJob* jobs, int nj, int i0, int nv, int pin,
                                    hipStream_t s);
-hipError_t launch_kortho(const KJob* jobs, int nj, int j, int pin, int norm_only, int set_alpha, int split,
-                         hipStream_t s);
+// one Gram-Schmidt pass of a step of low-precision solves; launch_kbeta ends the step
+hipError_t launch_kortho(const KJob* jobs, int nj, int j, int second, hipStream_t s);
 hipError_t launch_kbeta(const KJob* jobs, int nj, int j, int64_t nmax, hipStream_t s);
+// of FP64 solves: the second pass ends the step itself
+hipError_t launch_kortho_split(const KJob* jobs, int nj, int j, int second, hipStream_t s);
 hipError_t launch_ktridiag(const KJob* jobs, int nj, hipStream_t s);
 hipError_t launch_kritz(const KJob* jobs, int nj, hipStream_t s);
 // Whether the one-workgroup Lanczos of a node of M entries holds its basis in

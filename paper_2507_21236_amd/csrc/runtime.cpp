@@ -1172,10 +1172,14 @@ double lanczos(attn_handle* h, int n, int kreq, int precision, int* nmv, hipStre
       HIPCHK(launch_kalpha(J, 1, j, s));
       break;
     }
-    const int split = precision == ATTN_F64;
-    HIPCHK(launch_kortho(J, 1, j, 1, 0, 1, split, s));
-    HIPCHK(launch_kortho(J, 1, j, 2, 1, 0, split, s));
-    HIPCHK(launch_kbeta(J, 1, j, Msz, s));
+    if (precision == ATTN_F64) {
+      HIPCHK(launch_kortho_split(J, 1, j, 0, s));
+      HIPCHK(launch_kortho_split(J, 1, j, 1, s));
+    } else {
+      HIPCHK(launch_kortho(J, 1, j, 0, s));
+      HIPCHK(launch_kortho(J, 1, j, 1, s));
+      HIPCHK(launch_kbeta(J, 1, j, Msz, s));
+    }
   }
   HIPCHK(launch_ktridiag(J, 1, s));
   HIPCHK(launch_kritz(J, 1, s));
