@@ -874,8 +874,13 @@ __global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ 
   __shared__ double hs[64], part[1024], red[64 * kDotChunk];
   __shared__ int stop;
   const int nv = j + 1, t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  if (t == 0) stop = st->stop;   // once: block 0 of a second pass may set it meanwhile
   const int64_t n = J.n;
+  const int c = dot_chunk(n), S = 1024 / c, g = t / c, i = t - g * c;
+  if ((int64_t)blockIdx.x * c >= n) {   // no entries: partial sums of zero
+    if (!SECOND && t <= nv) (t < nv ? parea(J, 2) + t * kRedBlocks : parea(J, 3))[blockIdx.x] = 0.0;
+    return;
+  }
+  if (t == 0) stop = st->stop;   // once: block 0 of a second pass may set it meanwhile
   const double* P = parea(J, SECOND ? 2 : 1);
   for (int q = wave; q < nv + SECOND; q += 16) {
     const double* pq = q < nv ? P + q * kRedBlocks : parea(J, 3);
@@ -898,7 +903,6 @@ __global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ 
     st->alpha[j] = hs[j];
     if (!isfinite(hs[j])) fail_status(st, 1);
   }
-  const int c = dot_chunk(n), S = 1024 / c, g = t / c, i = t - g * c;
   double* w = J.w;
   double* out = J.V + (int64_t)(j + 1) * n;
   double nrm = 0;
@@ -942,8 +946,7 @@ __global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ 
   }
   __syncthreads();
   if (S > 1) {
-    const bool mine = (int64_t)blockIdx.x * c < n;   // part holds this block's entries
-    block_dots_split(J, mine ? part[i] : 0.0, c, 0, nv, parea(J, 2), red);
+    block_dots_split(J, part[i], c, 0, nv, parea(J, 2), red);
   } else {
     block_dots_1k(J, w, 0, nv, parea(J, 2), red);
   }
