@@ -501,7 +501,18 @@ void enqueue_step(attn_batch* b, int t, hipStream_t s0) {
     HIPCHK(launch_combine(S.d_cb_tasks, S.d_cb_terms, (int)S.cb_tasks.size(), S.cb_maxn, s0));
   if (!S.cv.empty()) HIPCHK(launch_convert(S.d_cv, (int)S.cv.size(), S.cv_max, s0));
   const int kk = std::min(b->krylov_k, 64);
-  if (!S.tj.empty()) HIPCHK(launch_tiny(S.d_tj, (int)S.tj.size(), S.tj_minM, S.tj_maxM, kk, s0));
+  // The one-workgroup solves run beside those over the whole chip, on a stream of
+  // their own: other instances' buffers, and as many CUs as instances (four
+  // 8 x 8 instances of m = 8 to 32: 65 ms a sweep in line, 57 so).  Not beside
+  // the persistent launch, whose waits count on its workgroups running at once.
+  const bool fork = !S.tj.empty() && !S.kj.empty() && !S.mv.use_pm;
+  if (fork) {
+    HIPCHK(hipEventRecord(b->evs[0], s0));
+    HIPCHK(hipStreamWaitEvent(b->s[1], b->evs[0], 0));
+  }
+  if (!S.tj.empty())
+    HIPCHK(launch_tiny(S.d_tj, (int)S.tj.size(), S.tj_minM, S.tj_maxM, kk, fork ? b->s[1] : s0));
+  if (fork) HIPCHK(hipEventRecord(b->evs[1], b->s[1]));
   if (S.kj.empty()) return;
   const int nj = (int)S.kj.size();
   const KJob* J = S.d_kj;
@@ -527,6 +538,7 @@ void enqueue_step(attn_batch* b, int t, hipStream_t s0) {
   HIPCHK(launch_ktridiag(J, nj, s0));
   HIPCHK(launch_kritz(J, nj, s0));
   HIPCHK(launch_kscale(J, nj, S.kj_max, 1, s0));
+  if (fork) HIPCHK(hipStreamWaitEvent(s0, b->evs[1], 0));
 }
 
 // Per step, time the step's matvec as staged launches and as the persistent
