@@ -466,8 +466,15 @@ __device__ __forceinline__ f4 mfma_bf(bf8 a, bf8 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// One work unit is a slice, a wavefront of it two row strips, so that a fragment
+// of X_s or B serves both strips' products: with one strip a wavefront the 2 KiB
+// of a fragment feed 96 cycles of products, more than the L1 of a CU delivers to
+// its four SIMDs.  Heaviest node of 8 x 8 m = 96: 1.31 ms with one strip, 0.98 with
+// two; of m = 128: 4.60 and 3.25 (1.50 and 7.1 with flat loads and four strips a
+// work unit).  Two workgroups to a CU bound the registers (256; a few addresses
+// are spilled at legs 128).
 template <int NB>
-__global__ __launch_bounds__(512) void k_sandwich_bf2(const SWTask* __restrict__ tasks,
+__global__ __launch_bounds__(256, 2) void k_sandwich_bf2(const SWTask* __restrict__ tasks,
                                                       const SWItem* __restrict__ items,
                                                       const int4* __restrict__ wus,
                                                       const float* __restrict__ xbase) {
@@ -476,14 +483,14 @@ __global__ __launch_bounds__(512) void k_sandwich_bf2(const SWTask* __restrict__
   const SWTask& t = tasks[wu.x];
   const int s = wu.y;
   const int ma = t.ma;
-  constexpr int mb = 16 * NB;
+  constexpr int mb = 16 * NB, MW = 2;
   const int lda = ma + 8;                      // LDS row = one column b of X_s
   __bf16* xh = reinterpret_cast<__bf16*>(smem_raw);
   __bf16* xl = xh + mb * lda;
   const float* X = (t.x ? (const float*)t.x : xbase) + (int64_t)s * t.xs_slice;
   for (int e = threadIdx.x; e < ma * mb; e += blockDim.x) {
     const int a = e / mb, b = e - a * mb;
-    const float v = X[(int64_t)a * t.xs_row + b];
+    const float v = gload(X + (int64_t)a * t.xs_row + b);
     const __bf16 hi = (__bf16)v;
     const __bf16 lo = (__bf16)(v - (float)hi);
     const int pos = bf_pinv(a);
@@ -492,83 +499,110 @@ __global__ __launch_bounds__(512) void k_sandwich_bf2(const SWTask* __restrict__
   }
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int strip = wu.z + wave;
+  const int strip = wu.z + MW * wave;          // legs are multiples of 32: whole pairs
   if (strip * 16 >= ma) return;
   const int l16 = lane & 15, g = lane >> 4;
   const int arow = strip * 16 + l16;
   const int64_t mma = (int64_t)ma * ma, mmb = (int64_t)mb * mb;
-  f4 acc[NB];
+  f4 acc[MW][NB];
 #pragma unroll
-  for (int q = 0; q < NB; q++) acc[q] = f4{0, 0, 0, 0};
+  for (int w = 0; w < MW; w++)
+#pragma unroll
+    for (int q = 0; q < NB; q++) acc[w][q] = f4{0, 0, 0, 0};
   const int iend = t.item0 + t.nitem;
   for (int it = t.item0; it < iend; it++) {
     const __bf16* A = (const __bf16*)items[it].A;
     const __bf16* B = (const __bf16*)items[it].B;
     const float coef = (float)items[it].coef;
-    f4 t1[NB];
+    f4 t1[MW][NB];
     if (A) {
 #pragma unroll
-      for (int q = 0; q < NB; q++) t1[q] = f4{0, 0, 0, 0};
-      const bf8* Ah = (const bf8*)(A + (int64_t)arow * ma + 8 * g);
-      const bf8* Al = (const bf8*)(A + mma + (int64_t)arow * ma + 8 * g);
+      for (int w = 0; w < MW; w++)
+#pragma unroll
+        for (int q = 0; q < NB; q++) t1[w][q] = f4{0, 0, 0, 0};
+      const __bf16* Ar = A + (int64_t)arow * ma + 8 * g;
+#pragma unroll 1
       for (int c = 0; c < ma / 32; c++) {
-        const bf8 ah = Ah[4 * c], al = Al[4 * c];
+        bf8 ah[MW], al[MW];
+#pragma unroll
+        for (int w = 0; w < MW; w++) {
+          ah[w] = gload((const bf8*)(Ar + 16 * w * ma + 32 * c));
+          al[w] = gload((const bf8*)(Ar + 16 * w * ma + 32 * c + mma));
+        }
 #pragma unroll
         for (int q = 0; q < NB; q++) {
           const int off = (16 * q + l16) * lda + 32 * c + 8 * g;
           const bf8 vh = *(const bf8*)(xh + off);
           const bf8 vl = *(const bf8*)(xl + off);
-          t1[q] = mfma_bf(vh, ah, t1[q]);
-          t1[q] = mfma_bf(vh, al, t1[q]);
-          t1[q] = mfma_bf(vl, ah, t1[q]);
+#pragma unroll
+          for (int w = 0; w < MW; w++) {
+            t1[w][q] = mfma_bf(vh, ah[w], t1[w][q]);
+            t1[w][q] = mfma_bf(vh, al[w], t1[w][q]);
+            t1[w][q] = mfma_bf(vl, ah[w], t1[w][q]);
+          }
         }
       }
 #pragma unroll
-      for (int q = 0; q < NB; q++) t1[q] *= coef;
+      for (int w = 0; w < MW; w++)
+#pragma unroll
+        for (int q = 0; q < NB; q++) t1[w][q] *= coef;
     } else {
-      const int pa = bf_pinv(arow);
 #pragma unroll
-      for (int q = 0; q < NB; q++)
+      for (int w = 0; w < MW; w++) {
+        const int pa = bf_pinv(arow + 16 * w);
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const int p = 16 * q + drow_bf(g, i);
-          t1[q][i] = ((float)xh[p * lda + pa] + (float)xl[p * lda + pa]) * coef;
-        }
+        for (int q = 0; q < NB; q++)
+#pragma unroll
+          for (int i = 0; i < 4; i++) {
+            const int p = 16 * q + drow_bf(g, i);
+            t1[w][q][i] = ((float)xh[p * lda + pa] + (float)xl[p * lda + pa]) * coef;
+          }
+      }
     }
     if (B) {
 #pragma unroll
       for (int c = 0; c < NB / 2; c++) {
-        bf8 th, tl;
+        bf8 th[MW], tl[MW];
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-          const float v = t1[2 * c + j / 4][j % 4];
-          th[j] = (__bf16)v;
-          tl[j] = (__bf16)(v - (float)th[j]);
-        }
+        for (int w = 0; w < MW; w++)
+#pragma unroll
+          for (int j = 0; j < 8; j++) {
+            const float v = t1[w][2 * c + j / 4][j % 4];
+            th[w][j] = (__bf16)v;
+            tl[w][j] = (__bf16)(v - (float)th[w][j]);
+          }
 #pragma unroll
         for (int tq = 0; tq < NB; tq++) {
           const int64_t off = (int64_t)(16 * tq + l16) * mb + 32 * c + 8 * g;
-          const bf8 bh = *(const bf8*)(B + off);
-          const bf8 bl = *(const bf8*)(B + mmb + off);
-          acc[tq] = mfma_bf(bh, th, acc[tq]);
-          acc[tq] = mfma_bf(bl, th, acc[tq]);
-          acc[tq] = mfma_bf(bh, tl, acc[tq]);
+          const bf8 bh = gload((const bf8*)(B + off));
+          const bf8 bl = gload((const bf8*)(B + mmb + off));
+#pragma unroll
+          for (int w = 0; w < MW; w++) {
+            acc[w][tq] = mfma_bf(bh, th[w], acc[w][tq]);
+            acc[w][tq] = mfma_bf(bl, th[w], acc[w][tq]);
+            acc[w][tq] = mfma_bf(bh, tl[w], acc[w][tq]);
+          }
         }
       }
     } else {
 #pragma unroll
-      for (int q = 0; q < NB; q++) acc[q] += t1[q];
+      for (int w = 0; w < MW; w++)
+#pragma unroll
+        for (int q = 0; q < NB; q++) acc[w][q] += t1[w][q];
     }
   }
-  float* Y = (float*)t.y + (int64_t)s * t.ys_slice + (int64_t)arow * t.ys_row;
 #pragma unroll
-  for (int q = 0; q < NB; q++)
+  for (int w = 0; w < MW; w++) {
+    float* Y = (float*)t.y + (int64_t)s * t.ys_slice + (int64_t)(arow + 16 * w) * t.ys_row;
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int c = 16 * q + drow_bf(g, i);
-      if (t.accumulate) Y[c] += acc[q][i];
-      else Y[c] = acc[q][i];
-    }
+    for (int q = 0; q < NB; q++)
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int c = 16 * q + drow_bf(g, i);
+        if (t.accumulate) Y[c] += acc[w][q][i];
+        else Y[c] = acc[w][q][i];
+      }
+  }
 }
 
 // Wave-per-slice form for legs <= 64 (ma = 16 MA, mb = 16 NB, both multiples
@@ -621,7 +655,7 @@ __global__ __launch_bounds__(256) void k_sandwich_bf2w(const SWTask* __restrict_
       const __bf16* src = nullptr;
       if (ch < 2 * NA) src = A ? A + (int64_t)ch * 8 : nullptr;
       else if (ch < NTOT) src = B ? B + (int64_t)(ch - 2 * NA) * 8 : nullptr;
-      if (src) pre[r] = *(const bf8*)src;
+      if (src) pre[r] = gload((const bf8*)src);
     }
   };
   auto store = [&](int buf) {
@@ -1387,7 +1421,7 @@ template <int NB>
 static hipError_t sand_bf2_launch(const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
                                   int ma, const void* xbase, hipStream_t s) {
   const size_t lds = (size_t)2 * (16 * NB) * (ma + 8) * sizeof(__bf16);
-  hipLaunchKernelGGL((k_sandwich_bf2<NB>), dim3(nwu), dim3(64 * sw_strips(ma)), lds, s, tasks, items, wus,
+  hipLaunchKernelGGL((k_sandwich_bf2<NB>), dim3(nwu), dim3(32 * sw_strips(ma)), lds, s, tasks, items, wus,
                      (const float*)xbase);
   return hipGetLastError();
 }

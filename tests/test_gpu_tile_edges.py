@@ -12,7 +12,7 @@ import pytest
 from oracle.measure import measure, product_expectation
 from problems import make_problem
 from problems.models import PX, PZ
-from tests.gpu_util import make_pair
+from tests.gpu_util import make_pair, move_both, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -44,4 +44,22 @@ def test_observables_at_the_edges_of_the_tiles(m):
     for i, j in pairs:
         want = measure(o.tree, o.T, [i, j], [PZ, PX], p.de_sites, p.de_u)
         assert abs(C[i, j] - want) <= 1e-12, (m, i, j, C[i, j], want)
+    a.close()
+
+
+@pytest.mark.parametrize("m", [32, 64, 96, 128])
+def test_split_bf16_matvecs_at_every_chunk_count(m):
+    import torch
+    from paper_2507_21236_amd import ATTN_BF16X2
+    p = make_problem("edges", 5, "ising", m, 90 + m, 6)
+    a, o = make_pair(p)
+    rng = np.random.default_rng(m)
+    sizes = [int(np.prod(t.shape)) for t in o.T]
+    for n in sorted(range(o.tree.n_nodes), key=lambda n: -sizes[n])[:3] + [o.tree.root]:
+        move_both(a, o, n)
+        x = torch.from_numpy(rng.standard_normal(o.T[n].shape)).to("cuda", torch.float32)
+        y = torch.empty_like(x)
+        a.heff_apply(n, x, y, dtype=ATTN_BF16X2)
+        torch.cuda.synchronize()
+        assert rel(y.double().cpu().numpy(), o.matvec(n, x.double().cpu().numpy())) < 1e-4, (m, n, x.shape)
     a.close()
