@@ -670,17 +670,13 @@ void* to_mirror(attn_handle* h, const void* p, int fmt) {
   const uintptr_t a = (uintptr_t)p;
   const uintptr_t c0 = (uintptr_t)h->d_mvcomb;
   if (a >= c0 && a < c0 + (uintptr_t)h->mvcomb_elems * 8) return (char*)h->comb_lp[fmt - 1] + (a - c0) / 2;
-  const Tree& tr = h->M.tree;
-  for (int dir = 0; dir < 2; dir++)
-    for (int e = 0; e < tr.n_edges(); e++) {
-      const uintptr_t b = (uintptr_t)h->store[dir][e];
-      if (b && a >= b && a < b + (uintptr_t)h->store_elems[dir][e] * 8) {
-        void* m = h->mir[fmt - 1][dir][e];
-        if (!m) throw StatusFail{ATTN_ERR_STATE, "internal: block without mirror"};
-        return (char*)m + (a - b) / 2;
-      }
-    }
-  throw StatusFail{ATTN_ERR_STATE, "internal: block outside every store"};
+  // binary search: the lists of all nodes name hundreds of thousands of blocks
+  const auto& v = h->store_ranges;
+  auto it = std::upper_bound(v.begin(), v.end(), a, [](uintptr_t x, const StoreRange& r) { return x < r.begin; });
+  if (it == v.begin() || a >= (--it)->end) throw StatusFail{ATTN_ERR_STATE, "internal: block outside every store"};
+  void* m = h->mir[fmt - 1][it->dir][it->edge];
+  if (!m) throw StatusFail{ATTN_ERR_STATE, "internal: block without mirror"};
+  return (char*)m + (a - it->begin) / 2;
 }
 
 // The split-BF16 kernel at legs 64 x 64 keeps one workgroup of eight waves
@@ -779,29 +775,36 @@ std::vector<CVTask> lowp_conversions(attn_handle* h, int n, int dtype) {
   const MVDev& D = h->mv[n];
   const MVDev& L = h->mvlp[dtype - 1][n];
   constexpr int64_t kConvertRun = (int64_t)1 << 16;
-  std::map<uintptr_t, int> need[2];   // block -> dimension, per format
+  std::vector<std::pair<uintptr_t, int>> need[2];   // (block, dimension), per format
+  auto add = [&](int fmt, const void* p, int m) {
+    if (p) need[fmt - 1].push_back({(uintptr_t)p, m});
+  };
   for (size_t g = 0; g < D.sw.size(); g++) {
     const int fmt = L.sw[g].fmt == 2 || L.sw[g].fmt == 3 ? 2 : 1;
     for (const SWItem& it : D.sw[g].items) {
-      if (it.A) need[fmt - 1][(uintptr_t)it.A] = D.sw[g].ma;
-      if (it.B) need[fmt - 1][(uintptr_t)it.B] = D.sw[g].mb;
+      add(fmt, it.A, D.sw[g].ma);
+      add(fmt, it.B, D.sw[g].mb);
     }
   }
   for (const std::vector<MPGroup>* c : {&D.chainA, &D.chainB, &D.chainC})
     for (const MPGroup& g : *c)
-      for (const MPJob& j : g.jobs) need[0][(uintptr_t)j.A] = g.mj;
+      for (const MPJob& j : g.jobs) add(1, j.A, g.mj);
   std::vector<CVTask> cv;
-  for (int fmt = 1; fmt <= 2; fmt++)
-    for (auto& kv : need[fmt - 1]) {
-      const int64_t mm = (int64_t)kv.second * kv.second;
+  for (int fmt = 1; fmt <= 2; fmt++) {
+    auto& v = need[fmt - 1];
+    std::sort(v.begin(), v.end());
+    v.erase(std::unique(v.begin(), v.end()), v.end());
+    for (auto& kv : v) {
+      const int64_t n2 = (int64_t)kv.second * kv.second;
       void* dst = to_mirror(h, (const void*)kv.first, fmt);
-      if (!cv.empty() && cv.back().fmt == fmt && cv.back().m == kv.second && cv.back().n + mm <= kConvertRun &&
+      if (!cv.empty() && cv.back().fmt == fmt && cv.back().m == kv.second && cv.back().n + n2 <= kConvertRun &&
           (uintptr_t)(cv.back().src + cv.back().n) == kv.first && (char*)cv.back().dst + cv.back().n * 4 == dst) {
-        cv.back().n += mm;
+        cv.back().n += n2;
         continue;
       }
-      cv.push_back({(const double*)kv.first, dst, mm, kv.second, fmt});
+      cv.push_back({(const double*)kv.first, dst, n2, kv.second, fmt});
     }
+  }
   return cv;
 }
 
@@ -1396,6 +1399,12 @@ attn_status attn_build_tpo(const attn_problem* p, attn_handle** out) {
         h->store[dir][e] = (double*)q;
       }
     }
+    for (int dir = 0; dir < 2; dir++)
+      for (int e = 0; e < tr.n_edges(); e++)
+        if (const uintptr_t b = (uintptr_t)h->store[dir][e])
+          h->store_ranges.push_back({b, b + (uintptr_t)h->store_elems[dir][e] * 8, dir, e});
+    std::sort(h->store_ranges.begin(), h->store_ranges.end(),
+              [](const StoreRange& x, const StoreRange& y) { return x.begin < y.begin; });
     // scratch sizing
     int64_t part_need = 0, chain_need = 0, mvcomb_need = 0, envcomb_need = 0, z_need = 0, grp_need = 0;
     for (int n = 0; n < nn; n++) {

@@ -261,6 +261,11 @@ struct ProblemCopy {
   uint64_t hash() const;
 };
 
+struct StoreRange {   // addresses of one effective-operator store
+  uintptr_t begin, end;
+  int dir, edge;
+};
+
 struct attn_handle {
   Model M;
   ProblemCopy prob;
@@ -331,6 +336,7 @@ struct attn_handle {
   bool lowp_ready[2] = {false, false};
   std::vector<void*> mir[2][2];     // [format - 1][direction][edge]
   std::vector<int64_t> store_elems[2];
+  std::vector<StoreRange> store_ranges;   // the stores by address
   void* comb_lp[2] = {nullptr, nullptr};
   int64_t mvcomb_elems = 0;
   std::vector<MVDev> mvlp[2];
