@@ -455,10 +455,16 @@ inline void chunk_shares(int64_t C, const int64_t* items, int n, int64_t* c) {
 // between two and eight rounds: a workgroup lasts its items and one more (its
 // slice in and out), and a chunk costs the write and the later read of a
 // partial output, 50 / m items of the whole chip (16 bytes per entry at
-// 4.75 TB/s against 4 m flops per entry and item at 60 TFLOP/s).
-inline int64_t wide_chunks(const int64_t* items, int n, int64_t units, int m, int strips) {
+// 4.75 TB/s against 4 m flops per entry and item at 60 TFLOP/s).  Counts past the
+// most chunks that the spectators may have (cap each) are not tried: at a node
+// with one slice there would be thousands (building the lists of an 8 x 8 m = 96
+// handle: 300 ms with them, 36 without).
+inline int64_t wide_chunks(const int64_t* items, int n, int64_t units, int m, int strips, int64_t cap) {
   const int64_t slots = 256 * (strips <= 6 ? 2 : 1);
-  const int64_t lo = std::max<int64_t>(n, 2 * slots / units), hi = std::max<int64_t>(lo, 8 * slots / units);
+  int64_t most = 0;
+  for (int g = 0; g < n; g++) most += std::min(items[g], cap);
+  const int64_t lo = std::min(most, std::max<int64_t>(n, 2 * slots / units));
+  const int64_t hi = std::min(most, std::max<int64_t>(lo, 8 * slots / units));
   double best = 0;
   int64_t bestC = lo;
   for (int64_t C = lo; C <= hi; C++) {
@@ -507,7 +513,7 @@ inline void mv_chunk_counts(const int64_t nitems[3], const int ma[3], const int 
       if (nitems[q] > 0 && ma[q] == ma[sp] && mb[q] == mb[sp]) { it[ng] = nitems[q]; grp[ng++] = q; done[q] = true; }
     int64_t C = ng * std::max<int64_t>(1, target[sp] / std::max<int64_t>(1, units[sp]));
     if (sw_on_mfma(ma[sp], mb[sp]) && sw_strips(ma[sp]) > 4)
-      C = wide_chunks(it, ng, units[sp], ma[sp], sw_strips(ma[sp]));
+      C = wide_chunks(it, ng, units[sp], ma[sp], sw_strips(ma[sp]), chunk_cap(Msz));
     chunk_shares(C, it, ng, c);
     for (int g = 0; g < ng; g++) {
       const int q = grp[g];
