@@ -464,8 +464,8 @@ void build_env_dev(attn_handle* h, const EnvPlan& P, EnvDev& D) {
   const int64_t F = Msz / mj;
   const bool gmf = gram_mfma_ok(mj, Msz);
   int64_t fchunk = F;
-  if (gmf) fchunk = gram_chunk(F, 8);   // enough gram workgroups: ~8 chunks of the free index per output at most
-  const int nfc = (int)((F + fchunk - 1) / fchunk);
+  if (gmf) fchunk = gram_chunk(F, kEnvGramParts);
+  const int nfc = gmf ? gram_parts(F, kEnvGramParts) : 1;
   int cap = 0;
   const std::vector<int> pieces = env_pieces(M, P, cap);
   const bool multi = sw_env_mfma(ma, mb);
@@ -512,6 +512,7 @@ void build_env_dev(attn_handle* h, const EnvPlan& P, EnvDev& D) {
       ch.gr.reds.push_back(rd);
       pslot += (int64_t)np * nfc;
     }
+    if (pslot * mj * mj > h->grpart_cap) throw StatusFail{ATTN_ERR_STATE, "internal: scratch of partial grams"};
     // tasks: on the matrix cores several virtual outputs share a task (one
     // staging of each slice of T serves all of them), packed longest first into
     // the least loaded task and issued heaviest first; otherwise one per task
@@ -983,8 +984,9 @@ void build_qr_dev(attn_handle* h, int n, int leg, QRDev& Q) {
   Q.mj = mj; Q.rows = rows; Q.Msz = Msz;
   Q.gmf = gram_mfma_ok(mj, Msz);
   int64_t fchunk = rows;
-  if (Q.gmf) fchunk = gram_chunk(rows, 32);
-  Q.nfc = (int)((rows + fchunk - 1) / fchunk);
+  if (Q.gmf) fchunk = gram_chunk(rows, kQrGramParts);
+  Q.nfc = Q.gmf ? gram_parts(rows, kQrGramParts) : 1;
+  if ((int64_t)Q.nfc * mj * mj > h->grpart_cap) throw StatusFail{ATTN_ERR_STATE, "internal: scratch of partial grams"};
   GRReduce gr;
   gr.partial = h->d_grpart; gr.out = G; gr.m = mj; gr.npart = Q.nfc; gr.coef = 1.0; gr.accumulate = 0; gr.pad = 0;
   Q.d_gr = upload(h, std::vector<GRReduce>{gr});
@@ -1446,9 +1448,10 @@ attn_status attn_build_tpo(const attn_problem* p, attn_handle** out) {
         const int64_t nout = std::max<int64_t>(1, std::max(std::min<int64_t>(per, nz), maxp));
         z_need = std::max(z_need, nout * Msz);
         const int mj = dm[ep->leg];
-        grp_need = std::max(grp_need, nout * 8 * (int64_t)mj * mj + (int64_t)mj * mj);
+        const int parts = gram_mfma_ok(mj, Msz) ? gram_parts(Msz / mj, kEnvGramParts) : 1;
+        grp_need = std::max(grp_need, nout * parts * (int64_t)mj * mj);
       }
-      for (int leg = 0; leg < 3; leg++) grp_need = std::max(grp_need, (int64_t)64 * dm[leg] * dm[leg]);
+      for (int leg = 0; leg < 3; leg++) grp_need = std::max(grp_need, (int64_t)kQrGramParts * dm[leg] * dm[leg]);
     }
     auto alloc = [&](int64_t n_doubles) -> double* {
       return (double*)dev_alloc(h, std::max<int64_t>(n_doubles, 1) * sizeof(double));
@@ -1468,7 +1471,8 @@ attn_status attn_build_tpo(const attn_problem* p, attn_handle** out) {
     h->mvcomb_elems = mvcomb_need;
     h->d_envcomb = alloc(envcomb_need);
     h->d_Z = alloc(z_need);
-    h->d_grpart = alloc(grp_need);
+    h->grpart_cap = std::max<int64_t>(grp_need, 1);
+    h->d_grpart = alloc(h->grpart_cap);
     h->d_red = alloc((int64_t)4 * 64 * kRedBlocks);
     for (int n = 0; n < nn; n++)
       for (int l = 0; l < 3; l++) h->mmax = std::max(h->mmax, tr.nodes[n].dims[l]);

@@ -231,13 +231,21 @@ inline bool mode_mfma_ok(int mj, int64_t M) {
 inline int64_t mode_blocks(int mj, int64_t M) { return (M / mj + 63) / 64; }
 inline bool gram_mfma_ok(int mj, int64_t M) { return mode_mfma_ok(mj, M); }
 // Free indices per gram work unit (whole 64-wide blocks, the last unit takes
-// what is left): about `parts` units where the free range allows it.
+// what is left): at most `parts` units, about that many where the free range
+// allows it.
 inline int64_t gram_chunk(int64_t F, int parts) {
-  int64_t c = std::max<int64_t>(64, ((F / parts) + 63) / 64 * 64);
+  int64_t c = std::max<int64_t>(64, ((F + parts - 1) / parts + 63) / 64 * 64);
   if (F % 64 == 0)
     while (F % c) c += 64;   // equal units
   return c;
 }
+inline int gram_parts(int64_t F, int parts) {
+  const int64_t c = gram_chunk(F, parts);
+  return (int)((F + c - 1) / c);
+}
+// Parts of the grams of effective-operator updates and of QRs: enough workgroups,
+// few partial sums to add up.
+constexpr int kEnvGramParts = 8, kQrGramParts = 32;
 
 }  // namespace rt
 
@@ -306,7 +314,8 @@ struct attn_handle {
   double* d_mvcomb = nullptr;
   double* d_envcomb = nullptr;
   double* d_Z = nullptr;
-  double* d_grpart = nullptr;
+  double* d_grpart = nullptr;   // partial grams of one chunk of outputs
+  int64_t grpart_cap = 0;
   double* d_red = nullptr;    // 128 x kRedBlocks
   double* d_qrmat = nullptr;  // G, R0, R1, R2, Rinv, Rt (mmax^2 each), Cholesky workspace
   double* d_qrR = nullptr;    // R of the last QR (absorbed into the neighbour)
