@@ -66,7 +66,7 @@ __device__ __forceinline__ void mode_mfma(const MPTask& t, const MPJob* __restri
   auto fetch = [&](int jb) {
     const __amdgpu_buffer_rsrc_t r = block_rsrc(jobs[jb].in ? (const T*)jobs[jb].in : xbase, M);
 #pragma unroll
-    for (int u = 0; u < NPT; u++) pf[u] = bload<T>(r, off[u], 0);
+    for (int u = 0; u < NPT; u++) pf[u] = bload<T>(r, off[u]);
   };
   v4 acc[NQ][FT];
 #pragma unroll
@@ -80,10 +80,11 @@ __device__ __forceinline__ void mode_mfma(const MPTask& t, const MPJob* __restri
     const __amdgpu_buffer_rsrc_t ra = block_rsrc((const T*)jobs[jb].A, mj * mj);
     const T coef = (T)jobs[jb].coef;
     T ab[PA][NQ];
+    int an = ao;   // the next K step to load, past the end too
 #pragma unroll
-    for (int u = 0; u < PA; u++)
+    for (int u = 0; u < PA; u++, an += astep)
 #pragma unroll
-      for (int q = 0; q < NQ; q++) ab[u][q] = bload<T>(ra, ao + 16 * q * (int)sizeof(T), u * astep);
+      for (int q = 0; q < NQ; q++) ab[u][q] = bload<T>(ra, an + 16 * q * (int)sizeof(T));
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < NPT; u++) {
@@ -102,8 +103,9 @@ __device__ __forceinline__ void mode_mfma(const MPTask& t, const MPJob* __restri
 #pragma unroll
         for (int q = 0; q < NQ; q++) {
           av[q] = ab[u][q];
-          ab[u][q] = bload<T>(ra, ao + 16 * q * (int)sizeof(T), (ks + u + PA) * astep);
+          ab[u][q] = bload<T>(ra, an + 16 * q * (int)sizeof(T));
         }
+        an += astep;
 #pragma unroll
         for (int c = 0; c < FT; c++) {
           const T bop = xr[u * 4 * ld + 16 * c] * coef;

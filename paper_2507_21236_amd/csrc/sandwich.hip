@@ -62,7 +62,7 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
     }
     const __amdgpu_buffer_rsrc_t ra = block_rsrc(A, ma * ma);
     for (int ks = 0; 4 * ks < ma; ks++) {
-      const T b0 = bload<T>(ra, (l4 * ma + arow) * (int)sizeof(T), 4 * ks * ma * (int)sizeof(T)) * coef;
+      const T b0 = bload<T>(ra, ((4 * ks + l4) * ma + arow) * (int)sizeof(T)) * coef;
       const T* xr = lds + (4 * ks + l4) * ld + pc;
 #pragma unroll
       for (int q = 0; q < NB; q++) acc[q] = mfma16(xr[16 * q], b0, acc[q]);
@@ -151,6 +151,11 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
 #pragma unroll
     for (int i = 0; i < 4; i++) bo[i] = (pk[i] * mb + pc) * (int)sizeof(T);
     const int bstep = 16 * mb * (int)sizeof(T);
+    // rows of the last tile, which may lie past the end; the tiles before it are
+    // in range with 16 columns to spare, so their row offset can be uniform
+    int bl[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) bl[i] = bo[i] + (NB - 1) * bstep;
     for (int it = i0; it < i1; it++) {
       const T* A = (const T*)items[it].A;
       const T* B = (const T*)items[it].B;
@@ -161,16 +166,19 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
 #pragma unroll
         for (int q = 0; q < NB; q++) t1[q] = v4{0, 0, 0, 0};
         const T* xr = lds + l4 * ld + pc;
-        T a0 = bload<T>(ra, ao, 0), a1 = bload<T>(ra, ao, astep);
+        T a0 = bload<T>(ra, ao), a1 = bload<T>(ra, ao + astep);
+        int an = ao + 2 * astep;   // the next K step to load, past the end too
         for (int ks = 0; ks < KS; ks += 2) {
           const T b0 = a0 * coef;
-          a0 = bload<T>(ra, ao, (ks + 2) * astep);
+          a0 = bload<T>(ra, an);
+          an += astep;
 #pragma unroll
           for (int q = 0; q < NB; q++) t1[q] = mfma16(xr[16 * q], b0, t1[q]);
           __builtin_amdgcn_sched_barrier(0);
           if (ks + 1 < KS) {
             const T b1 = a1 * coef;
-            a1 = bload<T>(ra, ao, (ks + 3) * astep);
+            a1 = bload<T>(ra, an);
+            an += astep;
 #pragma unroll
             for (int q = 0; q < NB; q++) t1[q] = mfma16(xr[4 * ld + 16 * q], b1, t1[q]);
             __builtin_amdgcn_sched_barrier(0);
@@ -191,7 +199,7 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
 #pragma unroll
         for (int g = 0; g < PB; g++)
 #pragma unroll
-          for (int tq = 0; tq < NB; tq++) bb[g][tq] = bload<T>(rb, bo[g] + 16 * tq * (int)sizeof(T), 0);
+          for (int tq = 0; tq < NB; tq++) bb[g][tq] = bload<T>(rb, (NB == 1 ? bl[g] : bo[g]) + 16 * tq * (int)sizeof(T));
 #pragma unroll
         for (int g = 0; g < 4 * NB; g++) {
           // the lowest row of the group (wave-uniform): past the end, no product
@@ -203,7 +211,8 @@ __device__ __forceinline__ void sandwich_rows(const SWTask& t, const SWItem* __r
             const int gn = g + PB;
 #pragma unroll
             for (int tq = 0; tq < NB; tq++)
-              bb[g % PB][tq] = bload<T>(rb, bo[gn % 4] + 16 * tq * (int)sizeof(T), (gn / 4) * bstep);
+              bb[g % PB][tq] = gn / 4 == NB - 1 ? bload<T>(rb, bl[gn % 4] + 16 * tq * (int)sizeof(T))
+                                                : bload<T>(rb, bo[gn % 4] + 16 * tq * (int)sizeof(T), (gn / 4) * bstep);
           }
 #pragma unroll
           for (int tq = 0; tq < NB; tq++) acc[tq] = mfma16(bv[tq], t1[g / 4][g % 4], acc[tq]);
