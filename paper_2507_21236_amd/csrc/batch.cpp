@@ -207,6 +207,7 @@ void add_sandwich(attn_batch* b, attn_handle* h, int n, const void* x, attn_batc
         si.coef = its[i]->coef;
         m.sw_items.push_back(si);
       }
+      items_without_b_first(m.sw_items, t.item0);
       const int ti = (int)m.sw_tasks.size();
       m.sw_tasks.push_back(t);
       if (mf && w2_allowed(b, ma, mb) && tile_for(b, ma, mb) == 2) {

@@ -254,6 +254,7 @@ void build_mv_dev(attn_handle* h, int n, std::vector<int64_t>& comb_off_out) {
         si.coef = its[i]->coef;
         g.items.push_back(si);
       }
+      items_without_b_first(g.items, t.item0);
       t.nitem = (int)(i1 - i0);
       t.accumulate = 0;
       add_sw_task(g, t, ns);
@@ -568,6 +569,7 @@ void build_env_dev(attn_handle* h, const EnvPlan& P, EnvDev& D) {
           g.items.push_back(si);
           nit++;
         }
+        items_without_b_first(g.items, g.items.size() - vo.ni);
       }
       if (!multi) t.nitem = nit;
       add_sw_task(g, t, ns);

@@ -127,6 +127,13 @@ struct SWGroup {
   SWOut* d_outs = nullptr;
 };
 
+// The items of one task or output, from `first` on, into the order that the
+// FP64 and FP32 kernels rely on: those without B first (their loop over the rest
+// loads through B without looking).  The plans list them so already.
+inline void items_without_b_first(std::vector<SWItem>& v, size_t first) {
+  std::stable_partition(v.begin() + first, v.end(), [](const SWItem& it) { return !it.B; });
+}
+
 struct MPGroup {
   int mj = 0;
   bool mfma = false;
