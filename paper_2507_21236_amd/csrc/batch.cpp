@@ -448,15 +448,15 @@ void build_step(attn_batch* b, int t) {
   upload_merged(b, S.mv);
 }
 
-// One matvec of every job; with J also the partial dots of basis vectors
-// [i0, i0 + nv) with the products into area pin (FP64 staged launches: in the
-// launch that sums the partial outputs).
-void run_matvec(attn_batch* b, attn_batch::Merged& m, hipStream_t s, const KJob* J = nullptr, int i0 = 0, int nv = 0,
-                int pin = 0) {
+// One matvec of every job and the partial dots of basis vectors [i0, i0 + nv)
+// with the products into area pin (FP64 staged launches: in the launch that sums
+// the partial outputs).
+void run_matvec(attn_batch* b, attn_batch::Merged& m, hipStream_t s, const KJob* J, int i0, int nv, int pin) {
   const int dt = b->precision == ATTN_F64 ? 0 : 1;
+  const int nj = (int)m.rd.size();
   if (m.use_pm) {
     HIPCHK(launch_batch_matvec(dt, m.pm, m.pm_grid, m.pm_lds, s));
-    if (J) HIPCHK(launch_kdots(J, (int)m.rd.size(), i0, nv, pin, dt == 0, s));
+    HIPCHK(launch_kdots(J, nj, i0, nv, pin, dt == 0, s));
     return;
   }
   for (int k = 0; k < 3; k++)
@@ -466,12 +466,12 @@ void run_matvec(attn_batch* b, attn_batch::Merged& m, hipStream_t s, const KJob*
   if (!m.sw_wus2.empty())
     HIPCHK(launch_sandwich(4, 64, 64, m.d_sw_tasks, m.d_sw_items, m.d_sw_wus2, (int)m.sw_wus2.size(), nullptr, s,
                            nullptr));
-  if (J && dt == 0) {
-    HIPCHK(launch_reduce_dots_list(m.d_rd, J, (int)m.rd.size(), i0, nv, pin, s));
+  if (dt == 0) {
+    HIPCHK(launch_reduce_dots_list(m.d_rd, J, nj, i0, nv, pin, s));
     return;
   }
-  HIPCHK(launch_reduce_list(dt, m.d_rd, (int)m.rd.size(), m.rd_max, s));
-  if (J) HIPCHK(launch_kdots(J, (int)m.rd.size(), i0, nv, pin, dt == 0, s));
+  HIPCHK(launch_reduce_list(m.d_rd, nj, m.rd_max, s));
+  HIPCHK(launch_kdots(J, nj, i0, nv, pin, 0, s));
 }
 
 // Enqueue step t on stream s0; the centre moves of the instances are spread
@@ -543,22 +543,25 @@ void enqueue_step(attn_batch* b, int t, hipStream_t s0) {
 }
 
 // Per step, time the step's matvec as staged launches and as the persistent
-// launch (one warm-up, then three of each; the inputs are whatever the
-// buffers hold, which does not change the time of the contractions) and keep
+// launch, each with the dots that follow it in a solve (as many basis vectors as
+// its middle step has; one warm-up, then three of each; the inputs are whatever
+// the buffers hold, which does not change the time of the contractions) and keep
 // the faster.  Both forms give the same results bit for bit.
 void choose_forms(attn_batch* b) {
   hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
   hipStream_t s = b->s[0];
+  const int kk = std::min(b->krylov_k, 64);
   for (auto& S : b->steps) {
     if (S.kj.empty()) continue;
+    HIPCHK(launch_kinit(S.d_kj, (int)S.kj.size(), kk, s));   // no job stopped: the dots run
     float t[2] = {0, 0};
     for (int f = 0; f < 2; f++) {
       S.mv.use_pm = f == 1;
-      run_matvec(b, S.mv, s);
+      run_matvec(b, S.mv, s, S.d_kj, 0, (kk + 1) / 2, 1);
       HIPCHK(hipEventRecord(e0, s));
-      for (int r = 0; r < 3; r++) run_matvec(b, S.mv, s);
+      for (int r = 0; r < 3; r++) run_matvec(b, S.mv, s, S.d_kj, 0, (kk + 1) / 2, 1);
       HIPCHK(hipEventRecord(e1, s));
       HIPCHK(hipEventSynchronize(e1));
       HIPCHK(hipEventElapsedTime(&t[f], e0, e1));

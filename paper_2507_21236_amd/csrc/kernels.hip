@@ -24,8 +24,7 @@ __device__ __forceinline__ void fail_status(KrylovState* st, int v) {
   atomicOr(&st->sticky, v);
 }
 
-// Sum of entry e (et in the transposed layout) of nsrc partial outputs, cut
-// into S groups of consecutive sources.
+// Sum of entry e (et in the transposed layout) over the partial outputs [k0, k1).
 template <typename TI>
 __device__ __forceinline__ double sum_sources(const RDSrc* __restrict__ srcs, int k0, int k1, int64_t e, int64_t et) {
   double acc = 0;
@@ -34,12 +33,6 @@ __device__ __forceinline__ double sum_sources(const RDSrc* __restrict__ srcs, in
     const TI* src = (const TI*)srcs[k].p;
     acc += (double)(srcs[k].layout ? src[et] : src[e]);
   }
-  return acc;
-}
-template <typename TI>
-__device__ __forceinline__ double sum_grouped(const RDSrc* __restrict__ srcs, int nsrc, int S, int64_t e, int64_t et) {
-  double acc = sum_sources<TI>(srcs, 0, nsrc / S, e, et);
-  for (int g = 1; g < S; g++) acc += sum_sources<TI>(srcs, nsrc * g / S, nsrc * (g + 1) / S, e, et);
   return acc;
 }
 
@@ -85,8 +78,8 @@ __global__ __launch_bounds__(256) void k_batch_mode(const MPTask* __restrict__ t
   }
 }
 
-// y = sum of the partial outputs of each task (fixed order), as k_reduce_out
-template <typename TI, typename TO>
+// y = sum of the FP32 partial outputs of each task, in one run per entry as the
+// low-precision solves of a single handle do
 __global__ __launch_bounds__(256) void k_reduce_list(const RDTask* __restrict__ tasks) {
   const RDTask& t = tasks[blockIdx.y];
   const int64_t M = (int64_t)t.ml * t.mr * t.mp;
@@ -94,9 +87,7 @@ __global__ __launch_bounds__(256) void k_reduce_list(const RDTask* __restrict__ 
     const int64_t l = e / ((int64_t)t.mr * t.mp);
     const int64_t rem = e - l * t.mr * t.mp;
     const int64_t r = rem / t.mp, p = rem - r * t.mp;
-    const int64_t et = p * t.ml * t.mr + l * t.mr + r;
-    // FP32 partial outputs are summed in one run, as the low-precision solves do
-    ((TO*)t.y)[e] = (TO)sum_grouped<TI>(t.srcs, t.nsrc, sizeof(TI) == 8 ? sum_groups(M) : 1, e, et);
+    ((double*)t.y)[e] = sum_sources<float>(t.srcs, 0, t.nsrc, e, p * t.ml * t.mr + l * t.mr + r);
   }
 }
 
@@ -2848,12 +2839,9 @@ hipError_t launch_batch_mode(int dtype, const MPTask* tasks, const MPJob* jobs, 
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_list(int dtype_in, const RDTask* tasks, int ntask, int64_t maxM, hipStream_t s) {
+hipError_t launch_reduce_list(const RDTask* tasks, int ntask, int64_t maxM, hipStream_t s) {
   if (ntask == 0) return hipSuccess;
-  if (dtype_in == 0)
-    hipLaunchKernelGGL((k_reduce_list<double, double>), dim3(gridv(maxM), ntask), dim3(256), 0, s, tasks);
-  else
-    hipLaunchKernelGGL((k_reduce_list<float, double>), dim3(gridv(maxM), ntask), dim3(256), 0, s, tasks);
+  hipLaunchKernelGGL(k_reduce_list, dim3(gridv(maxM), ntask), dim3(256), 0, s, tasks);
   return hipGetLastError();
 }
 

@@ -76,7 +76,8 @@ hipError_t launch_batch_matvec(int dtype, const PMArgs& a, int grid, size_t lds,
 hipError_t batch_matvec_occupancy(int dtype, size_t lds, int* per_cu);
 hipError_t launch_batch_mode(int dtype, const MPTask* tasks, const MPJob* jobs, const int2* wus, int nwu,
                              size_t lds, hipStream_t s);
-hipError_t launch_reduce_list(int dtype_in, const RDTask* tasks, int ntask, int64_t maxM, hipStream_t s);
+// FP32 partial outputs (FP64 solves: launch_reduce_dots_list)
+hipError_t launch_reduce_list(const RDTask* tasks, int ntask, int64_t maxM, hipStream_t s);
 hipError_t launch_zero(double* p, int64_t n, hipStream_t s);
 // dst = src (n doubles; the ranges do not overlap)
 hipError_t launch_copy(double* dst, const double* src, int64_t n, hipStream_t s);

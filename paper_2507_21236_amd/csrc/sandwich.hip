@@ -1203,7 +1203,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // per-unit timestamp trace put the remaining gap in per-ticket latency
 // (ticket atomic, descriptor loads, publish: about 5 us between units) and in
 // the reduction tail; the staged launches stay the default.
-// same per-element sum as k_reduce_list
+// same per-element sum as k_reduce_dots_list (FP64) and k_reduce_list (FP32)
 template <typename TI>
 __device__ __forceinline__ void pm_reduce(const RDTask& t, int64_t e0) {
   const int64_t M = (int64_t)t.ml * t.mr * t.mp;
