@@ -170,6 +170,7 @@ void XEngine::run(const std::vector<XProd>& prods, std::vector<double>& out, hip
   // an earlier run that failed may have left work on the stream
   HIPCHK(hipStreamSynchronize(s));
   h->xstage.used = 0;
+  WorkspaceRun whole(h->xkeep, h->xtmp);
   Buf buf(h->xkeep);   // to the end of the run
   double* d_ops = upload_tmp(h, buf, ops.empty() ? std::vector<double>(1, 0.0) : ops, s);
   auto Tptr = [&](int n) { return h->d_T + h->T_off[n]; };
@@ -527,8 +528,7 @@ void XEngine::run(const std::vector<XProd>& prods, std::vector<double>& out, hip
                              : std::lower_bound(c.pairs.begin(), c.pairs.end(), std::make_pair(w[1], w[2])) - c.pairs.begin();
     out[p] = hres[(size_t)(c.off + at)];
   }
-  h->xkeep.trim(Workspace::kKeep);
-  h->xtmp.trim(Workspace::kKeep);
+  whole.ok = true;
 }
 
 }  // namespace rt

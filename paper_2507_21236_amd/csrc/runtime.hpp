@@ -41,28 +41,41 @@ struct StatusFail {
 // Device memory handed out in order and taken back by marks, kept from one
 // call to the next (an allocation of the size a call needs costs up to
 // hundreds of milliseconds: 8 x 8 m = 32 correlation matrix, 90 to 600 ms a call,
-// 33 ms with it).  Every user runs in order on one stream.  After a call at
-// most kKeep bytes stay; the rest is freed, and all of it with the handle.
+// 33 ms with it).  Every user runs in order on one stream.  Blocks that nobody
+// uses and that are too small for a request are freed before it gets a new one, so
+// growing requests do not add up.  After a call at most kKeep bytes stay; the
+// rest is freed, after a call that failed all of it, and with the handle.
 struct Workspace {
   static constexpr size_t kKeep = (size_t)256 << 20;
   struct Block { char* p; size_t cap, used; };
   struct Mark { size_t cur, used; };
-  std::vector<Block> blocks;
-  size_t cur = 0;   // block that serves the next request
+  std::vector<Block> blocks;   // those behind cur are unused
+  size_t cur = 0;              // block that serves the next request
+  size_t held() const {
+    size_t total = 0;
+    for (auto& b : blocks) total += b.cap;
+    return total;
+  }
   void* get(size_t bytes) {
     bytes = (bytes + 255) / 256 * 256;
-    while (cur < blocks.size() && blocks[cur].used + bytes > blocks[cur].cap) {
-      if (cur + 1 == blocks.size()) break;
-      blocks[++cur].used = 0;
-    }
     if (blocks.empty() || blocks[cur].used + bytes > blocks[cur].cap) {
-      size_t total = 0;
-      for (auto& b : blocks) total += b.cap;
-      const size_t cap = std::max(bytes, std::min<size_t>(std::max<size_t>(total, (size_t)4 << 20), (size_t)128 << 20));
-      void* p = nullptr;
-      HIPCHK(hipMalloc(&p, cap));
-      blocks.push_back({(char*)p, cap, 0});
-      cur = blocks.size() - 1;
+      if (!blocks.empty() && blocks[cur].used > 0) cur++;   // its rest is left until the scope ends
+      size_t k = cur;                                       // the first unused block that holds the request
+      while (k < blocks.size() && blocks[k].cap < bytes) k++;
+      if (k < blocks.size()) {
+        std::swap(blocks[cur], blocks[k]);
+      } else {
+        pop_to(cur);   // all too small
+        const size_t cap = std::max(bytes, std::min<size_t>(std::max<size_t>(held(), (size_t)4 << 20), (size_t)128 << 20));
+        void* p = nullptr;
+        const hipError_t e = hipMalloc(&p, cap);
+        if (e != hipSuccess) {
+          if (cur > 0) cur--;
+          throw HipFail{e, "hipMalloc of a workspace"};
+        }
+        blocks.push_back({(char*)p, cap, 0});
+      }
+      blocks[cur].used = 0;
     }
     void* r = blocks[cur].p + blocks[cur].used;
     blocks[cur].used += bytes;
@@ -72,17 +85,34 @@ struct Workspace {
   void reset(Mark m) {
     cur = m.cur;
     if (cur < blocks.size()) blocks[cur].used = m.used;
+    else cur = blocks.empty() ? 0 : blocks.size() - 1;   // the unused block of the mark is gone
   }
-  // frees blocks from the last one until at most `keep` bytes are left (the device is idle)
-  void trim(size_t keep) {
-    size_t total = 0;
-    for (auto& b : blocks) total += b.cap;
-    while (!blocks.empty() && total > keep) {
-      total -= blocks.back().cap;
+  // frees the blocks from index n on (hipFree waits for the work that uses them)
+  void pop_to(size_t n) {
+    while (blocks.size() > n) {
       (void)hipFree(blocks.back().p);
       blocks.pop_back();
     }
-    if (cur >= blocks.size()) cur = blocks.empty() ? 0 : blocks.size() - 1;
+  }
+  // frees blocks from the last one until at most `keep` bytes are left (nothing in use)
+  void trim(size_t keep) {
+    size_t n = blocks.size(), total = held();
+    while (n > 0 && total > keep) total -= blocks[--n].cap;
+    pop_to(n);
+    cur = 0;
+  }
+};
+
+// One run over two workspaces: when it ends they keep at most kKeep each, and
+// nothing if it failed.  Declared before the scopes that use them.
+struct WorkspaceRun {
+  Workspace &a, &b;
+  bool ok = false;
+  WorkspaceRun(Workspace& x, Workspace& y) : a(x), b(y) {}
+  WorkspaceRun(const WorkspaceRun&) = delete;
+  ~WorkspaceRun() {
+    a.trim(ok ? Workspace::kKeep : 0);
+    b.trim(ok ? Workspace::kKeep : 0);
   }
 };
 

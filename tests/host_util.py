@@ -16,7 +16,7 @@ def run_host(source, tmp_path):
         pytest.skip("no host compiler or HIP headers")
     cpp, exe = tmp_path / "prog.cpp", tmp_path / "prog"
     cpp.write_text(source)
-    subprocess.run([cxx, "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"),
+    subprocess.run([cxx, "-std=c++17", "-O1", "-w", "-D_GLIBCXX_ASSERTIONS", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"),
                     "-I", os.path.join(ROOT, "paper_2507_21236_amd", "csrc"), "-I", "/opt/rocm/include",
                     str(cpp), "-o", str(exe)], check=True)
     return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
