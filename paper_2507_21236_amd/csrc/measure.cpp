@@ -611,8 +611,11 @@ void to_engine(XEngine& E, const std::vector<HostProd>& hp, std::vector<XProd>& 
   }
 }
 
+// Waits for the device (the caller's work on any stream: the tensors are read on
+// the default stream) and brings the centre to the root.
 attn_status need_root(attn_handle* h) {
   if (!h->state_ready) { h->err = "no state (attn_init_state not called)"; return ATTN_ERR_STATE; }
+  HIPCHK(hipDeviceSynchronize());
   const int root = h->M.tree.root;
   if (h->center != root) {
     attn_status st = attn_move_center(h, root, nullptr);
