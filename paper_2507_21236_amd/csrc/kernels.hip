@@ -833,8 +833,8 @@ __device__ __forceinline__ double max_alpha(const KrylovState* st, int j) {
 
 // beta_j of a step and its breakdown test, by every block alike; block 0 records
 // them.  The caller's barrier before it: the block has read the state by then.
-__device__ __forceinline__ bool set_beta(KrylovState* st, int j, double b, double amax) {
-  const bool brk = !(b > 1e-14 * amax);
+__device__ __forceinline__ bool set_beta(KrylovState* st, int j, double b, double amax, bool exhausted = false) {
+  const bool brk = exhausted || !(b > 1e-14 * amax);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (!isfinite(b)) fail_status(st, 1);
     if (brk) st->stop = 1;
@@ -854,10 +854,8 @@ __device__ __forceinline__ bool set_beta(KrylovState* st, int j, double b, doubl
 // from P2, and beta_j^2 = ||w||^2 - sum h^2 is then known before its update:
 // it writes V_{j+1} (and the copies) itself, where summing the norm of the
 // result needed one more launch (heaviest node of 8 x 8 m = 16: a solve of 20
-// steps 931 us so, 864 now).  No digits are lost: h is what
-// rounding left along V after the first pass, so sum h^2 reaches a sizeable share of
-// ||w||^2 only where beta_j is of that rounding's size, which the breakdown
-// test ends.
+// steps 931 us so, 864 now); lanczos_exhausted ends the run before the difference
+// loses its digits.
 template <bool SECOND>
 __global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ jobs, int j) {
   const KJob& J = jobs[blockIdx.y];
@@ -888,7 +886,7 @@ __global__ __launch_bounds__(1024) void k_kortho_split(const KJob* __restrict__ 
   if (SECOND) {
     const double d = hs[nv] - wave_sum(lane < nv ? hs[lane] * hs[lane] : 0.0);
     const double b = sqrt(d < 0.0 ? 0.0 : d);
-    if (set_beta(st, j, b, amax)) return;
+    if (set_beta(st, j, b, amax, lanczos_exhausted(hs[nv], d))) return;
     inv = 1.0 / b;
   } else if (blockIdx.x == 0 && t == 0) {
     st->alpha[j] = hs[j];

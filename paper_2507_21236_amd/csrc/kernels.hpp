@@ -157,6 +157,16 @@ constexpr int dot_chunk(int64_t n) {
 }
 constexpr int sum_groups(int64_t n) { return 1024 / dot_chunk(n); }
 
+// FP64 Lanczos steps take beta^2 as d = ||w||^2 - sum h^2, w after the first
+// Gram-Schmidt pass and h its components along the basis, which that pass left
+// there by rounding.  Where they are nearly all of w (beta below a tenth of ||w||,
+// the usual limit of "twice is enough"), w lies in the span of the basis to
+// rounding: the step ends the run.  Above, d keeps its digits to a hundred units
+// of rounding, and with them the norm of the next basis vector.  The test of beta
+// against the largest alpha does not see it where every alpha is of rounding's
+// size (a start vector with <H> = 0 in a small invariant subspace).  NaN ends it too.
+constexpr bool lanczos_exhausted(double w2, double d) { return !(d > 0.01 * w2); }
+
 struct RDSrc {
   const void* p;
   int32_t layout;
