@@ -11,10 +11,11 @@ namespace attn {
 constexpr int kRedBlocks = 256;
 
 // outs (MFMA shapes only): tasks with pad = 1 write several outputs, items of
-// output o = outs[task.item0 + k] going to its own y
+// output o = outs[task.item0 + k] going to its own y; wg_strips (MFMA shapes, one
+// slice per unit): row strips of a work unit from its first one on (0: all)
 hipError_t launch_sandwich(int dtype, int ma, int mb, const SWTask* tasks, const SWItem* items,
                            const int4* wus, int nwu, const void* xbase, hipStream_t s,
-                           const SWOut* outs = nullptr);
+                           const SWOut* outs = nullptr, int wg_strips = 0);
 hipError_t launch_mode(int dtype, int mj, bool mfma, const MPTask* tasks, const MPJob* jobs,
                        const int2* wus, int nwu, const void* xbase, hipStream_t s);
 // The FP64 sandwich launch (ma, mb) with the units of a mode-product launch

@@ -172,8 +172,22 @@ void xcd_order(std::vector<U>& wus) {
   wus.swap(out);
 }
 
+// Work units of one slice each -> of wg_strips row strips each (a list copied
+// from another plan has been cut already).
+void cut_slices(SWGroup& g) {
+  if (g.wg_strips || g.tasks.empty() || !(g.tasks[0].pad ? sw_env_mfma(g.ma, g.mb) : sw_mfma(g.ma, g.mb))) return;
+  const int strips = sw_strips(g.ma);
+  g.wg_strips = sw_wg_strips(strips, (int64_t)g.wus.size());
+  if (g.wg_strips == strips) return;
+  std::vector<int4> w;
+  for (const int4& wu : g.wus)
+    for (int st = 0; st < strips; st += g.wg_strips) w.push_back(make_int4(wu.x, wu.y, st, 0));
+  g.wus.swap(w);
+}
+
 void upload_sw(attn_handle* h, std::vector<SWGroup>& gs, bool by_xcd = false) {
   for (auto& g : gs) {
+    cut_slices(g);
     if (by_xcd) xcd_order(g.wus);
     g.d_tasks = upload(h, g.tasks);
     g.d_outs = upload(h, g.outs);
@@ -591,7 +605,7 @@ void run_comb(CBPlan& P, hipStream_t s) {
 void run_sw(std::vector<SWGroup>& gs, int dtype, const void* xbase, hipStream_t s) {
   for (auto& g : gs)
     HIPCHK(launch_sandwich(dtype, g.ma, g.mb, g.d_tasks, g.d_items, g.d_wus, (int)g.wus.size(), xbase, s,
-                           g.d_outs));
+                           g.d_outs, g.wg_strips));
 }
 
 hipEvent_t next_event(attn_handle* h) {
@@ -611,7 +625,8 @@ void run_sw_mv(attn_handle* h, std::vector<SWGroup>& gs, int dtype, const void* 
       a = (int)h->ev_used;
       HIPCHK(hipEventRecord(next_event(h), s));
     }
-    HIPCHK(launch_sandwich(g.fmt >= 2 ? g.fmt : dtype, g.ma, g.mb, g.d_tasks, g.d_items, g.d_wus, (int)g.wus.size(), xbase, s));
+    HIPCHK(launch_sandwich(g.fmt >= 2 ? g.fmt : dtype, g.ma, g.mb, g.d_tasks, g.d_items, g.d_wus, (int)g.wus.size(), xbase,
+                           s, nullptr, g.wg_strips));
     if (a >= 0) {
       b = (int)h->ev_used;
       HIPCHK(hipEventRecord(next_event(h), s));
@@ -639,7 +654,8 @@ void matvec_f64(attn_handle* h, int n, const double* x, double* y, hipStream_t s
   // (not while those launches are being timed)
   const bool joint = D.sw.size() == 1 && D.chainS.size() == 1 && D.chainS[0].mfma &&
                      D.chainS[0].mj <= 64 && sw_mfma(D.sw[0].ma, D.sw[0].mb) &&
-                     sw_strips(D.chainS[0].mj) == sw_strips(D.sw[0].mb) && !h->prof;
+                     sw_strips(D.chainS[0].mj) == sw_strips(D.sw[0].mb) &&
+                     D.sw[0].wg_strips == sw_strips(D.sw[0].ma) && !h->prof;
   if (joint) {
     const SWGroup& g = D.sw[0];
     const MPGroup& c = D.chainS[0];
@@ -2221,7 +2237,7 @@ struct Checker {
       const bool mf = t.pad ? sw_env_mfma(t.ma, t.mb) : sw_mfma(t.ma, t.mb);
       int64_t rows_hi;
       if (mf) {
-        if (wu.z != 0) { fail("sandwich: strip"); return; }
+        if (g.wg_strips < 1 || wu.z < 0 || wu.z % g.wg_strips || wu.z >= sw_strips(t.ma)) { fail("sandwich: strip"); return; }
         rows_hi = t.ma;   // the WG stages all rows of the slice
       } else {
         if (wu.z < 0 || wu.z >= t.ma * t.mb) { fail("sandwich: element"); return; }

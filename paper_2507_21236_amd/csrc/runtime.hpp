@@ -146,6 +146,7 @@ struct Stage {
 struct SWGroup {
   int ma = 0, mb = 0;
   int fmt = 0;        // low-precision plans: 1 = FP32 blocks, 2 = split-BF16 blocks
+  int wg_strips = 0;  // row strips of a work unit on the matrix cores (set at upload)
   double flops = 0;   // algorithmic flops of one launch
   std::vector<SWTask> tasks;
   std::vector<SWItem> items;
@@ -156,6 +157,14 @@ struct SWGroup {
   int4* d_wus = nullptr;
   SWOut* d_outs = nullptr;
 };
+
+// Row strips that one workgroup takes of a slice on the matrix cores, in a launch of
+// `slices` slices: all of them (one staging serves up to eight), but at most four
+// where even halves leave every workgroup a CU of its own.  More than four strips
+// share the matrix pipes of four SIMDs, and the rest of the chip has nothing to do
+// (FP64 matvec at the 8 x 8 root of m = 80,
+// 96, 128: 71, 128 and 389 us in one workgroup a slice, 51, 84 and 218 this way).
+inline int sw_wg_strips(int strips, int64_t slices) { return strips > 4 && slices <= 128 ? 4 : strips; }
 
 // The items of one task or output, from `first` on, into the order that the
 // FP64 and FP32 kernels rely on: those without B first (their loop over the rest

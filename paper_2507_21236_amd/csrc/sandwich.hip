@@ -475,14 +475,16 @@ __device__ __forceinline__ f4 mfma_bf(bf8 a, bf8 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// One work unit is a slice, a wavefront of it two row strips, so that a fragment
+// One work unit is a slice, a wavefront of it two row strips (MW), so that a fragment
 // of X_s or B serves both strips' products: with one strip a wavefront the 2 KiB
 // of a fragment feed 96 cycles of products, more than the L1 of a CU delivers to
 // its four SIMDs.  Heaviest node of 8 x 8 m = 96: 1.31 ms with one strip, 0.98 with
 // two; of m = 128: 4.60 and 3.25 (1.50 and 7.1 with flat loads and four strips a
 // work unit).  Two workgroups to a CU bound the registers (256; a few addresses
-// are spilled at legs 128).
-template <int NB>
+// are spilled at legs 128).  Launches of few slices, whose work units are parts of
+// a slice, have most of the chip idle: one strip a wavefront
+// (8 x 8 root of m = 96 and 128: 98 and 251 us with two, 86 and 211 this way).
+template <int NB, int MW>
 __global__ __launch_bounds__(256, 2) void k_sandwich_bf2(const SWTask* __restrict__ tasks,
                                                       const SWItem* __restrict__ items,
                                                       const int4* __restrict__ wus,
@@ -492,7 +494,7 @@ __global__ __launch_bounds__(256, 2) void k_sandwich_bf2(const SWTask* __restric
   const SWTask& t = tasks[wu.x];
   const int s = wu.y;
   const int ma = t.ma;
-  constexpr int mb = 16 * NB, MW = 2;
+  constexpr int mb = 16 * NB;
   const int lda = ma + 8;                      // LDS row = one column b of X_s
   __bf16* xh = reinterpret_cast<__bf16*>(smem_raw);
   __bf16* xl = xh + mb * lda;
@@ -508,7 +510,7 @@ __global__ __launch_bounds__(256, 2) void k_sandwich_bf2(const SWTask* __restric
   }
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int strip = wu.z + MW * wave;          // legs are multiples of 32: whole pairs
+  const int strip = wu.z + MW * wave;          // legs are multiples of 32: whole pairs where MW = 2
   if (strip * 16 >= ma) return;
   const int l16 = lane & 15, g = lane >> 4;
   const int arow = strip * 16 + l16;
@@ -1384,13 +1386,13 @@ void k_batch_matvec(const PMArgs a) {
 // ============================================================================ launchers
 template <typename T, int NB>
 static hipError_t sand_launch(const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
-                              int ma, int mb, const void* xbase, hipStream_t s, const SWOut* outs) {
+                              int ma, int mb, const void* xbase, hipStream_t s, const SWOut* outs, int strips) {
   const size_t lds = sw_mfma_lds(ma, 16 * NB, sizeof(T));
   if (ma == 16 * NB && mb == 16 * NB)
-    hipLaunchKernelGGL((k_sandwich<T, NB, true>), dim3(nwu), dim3(64 * sw_strips(ma)), lds, s, tasks, items, wus,
+    hipLaunchKernelGGL((k_sandwich<T, NB, true>), dim3(nwu), dim3(64 * strips), lds, s, tasks, items, wus,
                        (const T*)xbase, outs);
   else
-    hipLaunchKernelGGL((k_sandwich<T, NB, false>), dim3(nwu), dim3(64 * sw_strips(ma)), lds, s, tasks, items, wus,
+    hipLaunchKernelGGL((k_sandwich<T, NB, false>), dim3(nwu), dim3(64 * strips), lds, s, tasks, items, wus,
                        (const T*)xbase, outs);
   return hipGetLastError();
 }
@@ -1428,16 +1430,22 @@ hipError_t launch_sandwich_mode(int ma, int mb, const SWTask* tasks, const SWIte
 
 template <int NB>
 static hipError_t sand_bf2_launch(const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
-                                  int ma, const void* xbase, hipStream_t s) {
+                                  int ma, const void* xbase, hipStream_t s, int strips) {
   const size_t lds = (size_t)2 * (16 * NB) * (ma + 8) * sizeof(__bf16);
-  hipLaunchKernelGGL((k_sandwich_bf2<NB>), dim3(nwu), dim3(32 * sw_strips(ma)), lds, s, tasks, items, wus,
-                     (const float*)xbase);
+  if (strips < sw_strips(ma))
+    hipLaunchKernelGGL((k_sandwich_bf2<NB, 1>), dim3(nwu), dim3(64 * strips), lds, s, tasks, items, wus,
+                       (const float*)xbase);
+  else
+    hipLaunchKernelGGL((k_sandwich_bf2<NB, 2>), dim3(nwu), dim3(32 * strips), lds, s, tasks, items, wus,
+                       (const float*)xbase);
   return hipGetLastError();
 }
 
 hipError_t launch_sandwich(int dtype, int ma, int mb, const SWTask* tasks, const SWItem* items,
-                           const int4* wus, int nwu, const void* xbase, hipStream_t s, const SWOut* outs) {
+                           const int4* wus, int nwu, const void* xbase, hipStream_t s, const SWOut* outs,
+                           int wg_strips) {
   if (nwu == 0) return hipSuccess;
+  const int strips = wg_strips > 0 ? wg_strips : sw_strips(ma);
   if (dtype == 3) {   // split BF16, one slice per wave (legs 32 or 64)
 #define BF2W(MA, NB)                                                                             \
   {                                                                                              \
@@ -1467,10 +1475,10 @@ hipError_t launch_sandwich(int dtype, int ma, int mb, const SWTask* tasks, const
   if (dtype == 2) {
     if (!(ma % 32 == 0 && mb % 32 == 0 && ma <= 128 && mb <= 128)) return hipErrorInvalidValue;
     switch (mb / 32) {
-      case 1: return sand_bf2_launch<2>(tasks, items, wus, nwu, ma, xbase, s);
-      case 2: return sand_bf2_launch<4>(tasks, items, wus, nwu, ma, xbase, s);
-      case 3: return sand_bf2_launch<6>(tasks, items, wus, nwu, ma, xbase, s);
-      case 4: return sand_bf2_launch<8>(tasks, items, wus, nwu, ma, xbase, s);
+      case 1: return sand_bf2_launch<2>(tasks, items, wus, nwu, ma, xbase, s, strips);
+      case 2: return sand_bf2_launch<4>(tasks, items, wus, nwu, ma, xbase, s, strips);
+      case 3: return sand_bf2_launch<6>(tasks, items, wus, nwu, ma, xbase, s, strips);
+      case 4: return sand_bf2_launch<8>(tasks, items, wus, nwu, ma, xbase, s, strips);
     }
     return hipErrorInvalidValue;
   }
@@ -1482,14 +1490,14 @@ hipError_t launch_sandwich(int dtype, int ma, int mb, const SWTask* tasks, const
       return hipGetLastError();
     }
     switch (sw_strips(mb)) {
-      case 1: return sand_launch<double, 1>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 2: return sand_launch<double, 2>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 3: return sand_launch<double, 3>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 4: return sand_launch<double, 4>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 5: return sand_launch<double, 5>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 6: return sand_launch<double, 6>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 7: return sand_launch<double, 7>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 8: return sand_launch<double, 8>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 1: return sand_launch<double, 1>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 2: return sand_launch<double, 2>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 3: return sand_launch<double, 3>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 4: return sand_launch<double, 4>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 5: return sand_launch<double, 5>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 6: return sand_launch<double, 6>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 7: return sand_launch<double, 7>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 8: return sand_launch<double, 8>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
     }
   } else {
     if (!mf) {
@@ -1498,14 +1506,14 @@ hipError_t launch_sandwich(int dtype, int ma, int mb, const SWTask* tasks, const
       return hipGetLastError();
     }
     switch (sw_strips(mb)) {
-      case 1: return sand_launch<float, 1>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 2: return sand_launch<float, 2>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 3: return sand_launch<float, 3>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 4: return sand_launch<float, 4>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 5: return sand_launch<float, 5>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 6: return sand_launch<float, 6>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 7: return sand_launch<float, 7>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
-      case 8: return sand_launch<float, 8>(tasks, items, wus, nwu, ma, mb, xbase, s, outs);
+      case 1: return sand_launch<float, 1>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 2: return sand_launch<float, 2>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 3: return sand_launch<float, 3>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 4: return sand_launch<float, 4>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 5: return sand_launch<float, 5>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 6: return sand_launch<float, 6>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 7: return sand_launch<float, 7>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
+      case 8: return sand_launch<float, 8>(tasks, items, wus, nwu, ma, mb, xbase, s, outs, strips);
     }
   }
   return hipErrorInvalidValue;
@@ -1561,10 +1569,13 @@ hipError_t prepare_sandwich_attributes() {
       (const void*)k_sandwich_mode<double, 2, true>, (const void*)k_sandwich_mode<double, 2, false>,
       (const void*)k_sandwich_mode<double, 3, true>, (const void*)k_sandwich_mode<double, 3, false>,
       (const void*)k_sandwich_mode<double, 4, true>, (const void*)k_sandwich_mode<double, 4, false>,
-      (const void*)k_sandwich_bf2<2>, (const void*)k_sandwich_bf2<4>,
+      (const void*)k_sandwich_bf2<2, 1>, (const void*)k_sandwich_bf2<2, 2>,
+      (const void*)k_sandwich_bf2<4, 1>, (const void*)k_sandwich_bf2<4, 2>,
+      (const void*)k_sandwich_bf2<6, 1>, (const void*)k_sandwich_bf2<6, 2>,
+      (const void*)k_sandwich_bf2<8, 1>, (const void*)k_sandwich_bf2<8, 2>,
       (const void*)k_sandwich_bf2w<2, 2>, (const void*)k_sandwich_bf2w<2, 4>,
       (const void*)k_sandwich_bf2w<4, 2>, (const void*)k_sandwich_bf2d<4, 4>,
-      (const void*)k_sandwich_bf2<6>, (const void*)k_sandwich_bf2<8>, (const void*)k_sandwich_w2<float>};
+      (const void*)k_sandwich_w2<float>};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;

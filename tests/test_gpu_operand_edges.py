@@ -3,7 +3,8 @@ sandwiches on operator blocks and tensors that lie in the middle of an allocatio
 full of NaN give finite results, equal to FP64 (FP32: to 1e-5) products of the same
 operands.  The kernels pad K steps and tiles with zeros; memory behind a block is
 usually finite, so a read past its end would not show elsewhere.  1e-12 and 1e-5
-relative: unit roundoff times a few hundred summands."""
+relative: unit roundoff times a few hundred summands.  The same for slices of more
+than four row strips that are cut into work units of four."""
 import ctypes
 
 import numpy as np
@@ -92,6 +93,16 @@ def test_mode_products_of_ragged_legs(mj, f32):
 @pytest.mark.parametrize("ma,mb", [(17, 17), (31, 33), (50, 50), (49, 64), (64, 50), (65, 65), (100, 90), (7, 100),
                                    (113, 97), (127, 127), (127, 17), (3, 127)])
 def test_sandwiches_of_ragged_slices(ma, mb, f32):
+    _sandwich(ma, mb, f32, 0)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("ma,mb", [(65, 65), (80, 80), (96, 33), (100, 90), (112, 112), (127, 127), (128, 128), (128, 64)])
+def test_slices_in_units_of_four_strips(ma, mb, f32):
+    _sandwich(ma, mb, f32, 4)
+
+
+def _sandwich(ma, mb, f32, strips):
     import torch
     dt = torch.float32 if f32 else torch.float64
     rng = np.random.default_rng(1000 * ma + mb)
@@ -105,9 +116,10 @@ def test_sandwiches_of_ragged_slices(ma, mb, f32):
     # items without B first: 0.5 A X, then A X B^T and X B^T
     k2 = _upload(Job(pa, None, 0.5), Job(pa, pb, 1.0), Job(None, pb, -0.25))
     k1 = _upload(SWTask(px, py, ma * mb, mb, ma * mb, mb, ma, mb, 0, 3, 0, 0))
-    k3 = _upload(np.array([[0, s, 0, 0] for s in range(ns)], dtype=np.int32))
-    _launch("_ZN4attn15launch_sandwichEiiiPKNS_6SWTaskEPKNS_6SWItemEPK15HIP_vector_typeIiLj4EEiPKvP12ihipStream_tPKNS_5SWOutE",
-            int(f32), ma, mb, _ptr(k1[1]), _ptr(k2[1]), _ptr(k3[1]), ns, None, None, None)
+    units = [[0, s, st, 0] for s in range(ns) for st in range(0, -(-ma // 16), strips or 8)]
+    k3 = _upload(np.array(units, dtype=np.int32))
+    _launch("_ZN4attn15launch_sandwichEiiiPKNS_6SWTaskEPKNS_6SWItemEPK15HIP_vector_typeIiLj4EEiPKvP12ihipStream_tPKNS_5SWOutEi",
+            int(f32), ma, mb, _ptr(k1[1]), _ptr(k2[1]), _ptr(k3[1]), len(units), None, None, None, strips)
     got = ty[GUARD:GUARD + x.size].double().cpu().numpy().reshape(x.shape)
     ax = np.einsum("ij,sjk->sik", A, x)
     want = 0.5 * ax + ax @ B.T - 0.25 * x @ B.T
