@@ -483,9 +483,11 @@ __device__ __forceinline__ f4 mfma_bf(bf8 a, bf8 b, f4 c) {
 // work unit).  Two workgroups to a CU bound the registers (256; a few addresses
 // are spilled at legs 128).  Launches of few slices, whose work units are parts of
 // a slice, have most of the chip idle: one strip a wavefront
-// (8 x 8 root of m = 96 and 128: 98 and 251 us with two, 86 and 211 this way).
+// with the registers to keep many loads in flight (8 x 8 root of m = 96 and 128: 98
+// and 251 us with two, 86 and 211 with one and registers for three wavefronts a
+// SIMD, 72 and 211 for two).
 template <int NB, int MW>
-__global__ __launch_bounds__(256, 2) void k_sandwich_bf2(const SWTask* __restrict__ tasks,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MW, 2))) void k_sandwich_bf2(const SWTask* __restrict__ tasks,
                                                       const SWItem* __restrict__ items,
                                                       const int4* __restrict__ wus,
                                                       const float* __restrict__ xbase) {
