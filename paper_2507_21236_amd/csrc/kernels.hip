@@ -103,7 +103,11 @@ __global__ __launch_bounds__(256) void k_copy(double* __restrict__ dst, const do
 
 // ============================================================================ gram
 // partial[j][j'] (column-major) = sum_{f in [f0, f1)} X[f][j] Z[f][j'].
-template <int NI>
+// RAG: a leg that is no multiple of 16 or a free range that is none of 64, staged
+// with zeros up to the tile edges.  Whole tiles go without the guards (centre moves
+// between nodes of legs 96 and 80: 8.64 and 5.23 ms of grams with them, 8.31 and 4.89
+// without).
+template <int NI, bool RAG>
 __global__ __launch_bounds__(256) void k_gram(const GRTask* __restrict__ tasks) {
   constexpr int mjp = 16 * NI;
   constexpr int ld = mjp + 2;
@@ -114,7 +118,7 @@ __global__ __launch_bounds__(256) void k_gram(const GRTask* __restrict__ tasks) 
   double* lz = lx + 64 * ld;
   const GRTask& t = tasks[blockIdx.x];
   const int j = t.j, d0 = t.d0, d1 = t.d1, d2 = t.d2;
-  const int mj = j == 0 ? d0 : (j == 1 ? d1 : d2);   // <= 16 NI: tiles past the end are staged as zeros
+  const int mj = RAG ? (j == 0 ? d0 : (j == 1 ? d1 : d2)) : mjp;
   const double* X = (const double*)t.X;
   const double* Z = (const double*)t.Z;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(256) void k_gram(const GRTask* __restrict__ tasks) 
     if (j == 2) {
       for (int e = threadIdx.x; e < 64 * mjp; e += 256) {
         const int fl = e / mjp, i = e - fl * mjp;
-        const bool in = i < mj && fb + fl < t.f1;
+        const bool in = !RAG || (i < mj && fb + fl < t.f1);
         const int64_t ad = in ? mode_addr(j, d0, d1, d2, i, fb + fl) : 0;
         lx[fl * ld + i] = in ? X[ad] : 0.0;
         lz[fl * ld + i] = in ? Z[ad] : 0.0;
@@ -135,7 +139,7 @@ __global__ __launch_bounds__(256) void k_gram(const GRTask* __restrict__ tasks) 
     } else {
       for (int e = threadIdx.x; e < 64 * mjp; e += 256) {
         const int i = e >> 6, fl = e & 63;
-        const bool in = i < mj && fb + fl < t.f1;
+        const bool in = !RAG || (i < mj && fb + fl < t.f1);
         const int64_t ad = in ? mode_addr(j, d0, d1, d2, i, fb + fl) : 0;
         lx[fl * ld + i] = in ? X[ad] : 0.0;
         lz[fl * ld + i] = in ? Z[ad] : 0.0;
@@ -164,7 +168,7 @@ __global__ __launch_bounds__(256) void k_gram(const GRTask* __restrict__ tasks) 
 #pragma unroll
       for (int i = 0; i < 4; i++) {
         const int r = 16 * tj + drow<double>(l4, i), c = 16 * tk + l16;
-        if (r < mj && c < mj) P[(int64_t)c * mj + r] = acc[q][i];
+        if (!RAG || (r < mj && c < mj)) P[(int64_t)c * mj + r] = acc[q][i];
       }
     }
   }
@@ -2582,15 +2586,16 @@ hipError_t launch_mode(int dtype, int mj, bool mfma, const MPTask* tasks, const 
 }
 
 template <int NI>
-static hipError_t gram_launch(const GRTask* tasks, int ntask, hipStream_t s) {
+static hipError_t gram_launch(const GRTask* tasks, int ntask, bool whole, hipStream_t s) {
   const size_t lds = (size_t)2 * 64 * (16 * NI + 2) * sizeof(double);
-  hipLaunchKernelGGL(k_gram<NI>, dim3(ntask), dim3(256), lds, s, tasks);
+  if (whole) hipLaunchKernelGGL((k_gram<NI, false>), dim3(ntask), dim3(256), lds, s, tasks);
+  else hipLaunchKernelGGL((k_gram<NI, true>), dim3(ntask), dim3(256), lds, s, tasks);
   return hipGetLastError();
 }
 
-hipError_t launch_gram(int mj, bool mfma, const GRTask* tasks, int ntask, hipStream_t s, bool nt) {
+hipError_t launch_gram(int mj, bool mfma, const GRTask* tasks, int ntask, hipStream_t s, GramForm form) {
   if (ntask == 0) return hipSuccess;
-  if (mfma && nt) {
+  if (mfma && form == GRAM_DIRECT) {
     switch (mj / 16) {
       case 1: hipLaunchKernelGGL(k_gram_nt<1>, dim3(ntask), dim3(256), 0, s, tasks); return hipGetLastError();
       case 2: hipLaunchKernelGGL(k_gram_nt<2>, dim3(ntask), dim3(256), 0, s, tasks); return hipGetLastError();
@@ -2603,15 +2608,16 @@ hipError_t launch_gram(int mj, bool mfma, const GRTask* tasks, int ntask, hipStr
     hipLaunchKernelGGL(k_gram_gen, dim3(grid1((int64_t)mj * mj), ntask), dim3(256), 0, s, tasks, mj);
     return hipGetLastError();
   }
+  const bool whole = form == GRAM_WHOLE;
   switch (sw_strips(mj)) {
-    case 1: return gram_launch<1>(tasks, ntask, s);
-    case 2: return gram_launch<2>(tasks, ntask, s);
-    case 3: return gram_launch<3>(tasks, ntask, s);
-    case 4: return gram_launch<4>(tasks, ntask, s);
-    case 5: return gram_launch<5>(tasks, ntask, s);
-    case 6: return gram_launch<6>(tasks, ntask, s);
-    case 7: return gram_launch<7>(tasks, ntask, s);
-    case 8: return gram_launch<8>(tasks, ntask, s);
+    case 1: return gram_launch<1>(tasks, ntask, whole, s);
+    case 2: return gram_launch<2>(tasks, ntask, whole, s);
+    case 3: return gram_launch<3>(tasks, ntask, whole, s);
+    case 4: return gram_launch<4>(tasks, ntask, whole, s);
+    case 5: return gram_launch<5>(tasks, ntask, whole, s);
+    case 6: return gram_launch<6>(tasks, ntask, whole, s);
+    case 7: return gram_launch<7>(tasks, ntask, whole, s);
+    case 8: return gram_launch<8>(tasks, ntask, whole, s);
   }
   return hipErrorInvalidValue;
 }

@@ -23,8 +23,11 @@ hipError_t launch_mode(int dtype, int mj, bool mfma, const MPTask* tasks, const 
 hipError_t launch_sandwich_mode(int ma, int mb, const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
                                 int mj, const MPTask* mtasks, const MPJob* mjobs, const int2* mwus, int nmwu,
                                 const void* xbase, hipStream_t s);
-// nt: every task has j in {0, 1}, 16 | d2 and 16-aligned free ranges (register-direct kernel, mj <= 64)
-hipError_t launch_gram(int mj, bool mfma, const GRTask* tasks, int ntask, hipStream_t s, bool nt = false);
+// Forms of the matrix-core grams: any leg and range; legs of whole 16-wide tiles and
+// ranges of whole 64-wide blocks; and every task with j in {0, 1}, 16 | d2 and
+// 16-aligned free ranges (register-direct kernel, mj <= 64)
+enum GramForm { GRAM_RAGGED, GRAM_WHOLE, GRAM_DIRECT };
+hipError_t launch_gram(int mj, bool mfma, const GRTask* tasks, int ntask, hipStream_t s, GramForm form);
 hipError_t launch_gram_reduce(const GRReduce* r, int nr, int maxm, hipStream_t s);
 hipError_t launch_combine(const CBTask* tasks, const CBTerm* terms, int ntask, int maxn,
                           hipStream_t s);
