@@ -114,7 +114,7 @@ T* bupload(attn_batch* b, const std::vector<T>& v) {
 int target_for(const attn_batch* b, int ma, int mb) {
   for (auto& t : b->tuned)
     if (t.ma == ma && t.mb == mb) return t.target;
-  return (int)mv_target(ma);   // the single-handle split
+  return (int)mv_target(ma, mb);   // the single-handle split
 }
 
 int tile_for(const attn_batch* b, int ma, int mb) {
@@ -608,7 +608,7 @@ void autotune(attn_batch* b) {
   HIPCHK(hipEventCreate(&e1));
   const int nsteps = (int)b->steps.size();
   for (auto& sh : shapes) {
-    const int cands[4] = {64, 256, (int)mv_target(sh.first), 4096};   // the single-handle split among them
+    const int cands[4] = {64, 256, (int)mv_target(sh.first, sh.second), 4096};   // the single-handle split among them
     float best = 1e30f;
     int best_c = cands[2], best_tile = 1;
     const int ntile = w2_allowed(b, sh.first, sh.second) ? 2 : 1;

@@ -455,12 +455,17 @@ void slice_geom(int spect, const int* dm, int& ma, int& mb, int& ns, int64_t& sl
 // four per CU; measured at the heaviest 16 x 16 m = 64 node (contraction + sum of
 // the partial outputs) 1141 + 43 us, against 1158 + 34 with 768 and 1178 + 29
 // with 683.  Fewer strips: 768, where the launches are shorter than the spread
-// of their workgroups.  The batched form takes the same split unless it is
-// autotuned.
-inline int64_t mv_target(int ma) { return sw_strips(ma) >= 4 ? 1024 : 768; }
+// of their workgroups; and off the matrix cores (legs above 128: 4 x 4 m = 256, root,
+// 21.3 ms with 768 and 28.4 with 1024, whose workgroups walk more blocks at once
+// than the L2 holds).  The batched form takes the same split unless it is autotuned.
+inline int64_t mv_target(int ma, int mb) { return sw_strips(ma) >= 4 && sw_on_mfma(ma, mb) ? 1024 : 768; }
 inline void mv_targets(const int* dm, int64_t target[3]) {
-  target[0] = mv_target(dm[1]);   // the a leg of each spectator's slices
-  target[1] = target[2] = mv_target(dm[0]);
+  for (int sp = 0; sp < 3; sp++) {
+    int ma, mb, ns;
+    int64_t sl, row;
+    slice_geom(sp, dm, ma, mb, ns, sl, row);
+    target[sp] = mv_target(ma, mb);
+  }
 }
 void mv_chunks(const MatvecPlan& P, const int* dm, const int64_t target[3], int out[3]);
 bool sw_mfma(int ma, int mb);

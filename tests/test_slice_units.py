@@ -32,3 +32,16 @@ def test_lists_of_wide_roots_in_bounds(L, m):
     a = AttnHandle(make_problem("wide", L, "ising", m, m, 4), flags=ATTN_DRYRUN)
     a.validate()
     a.close()
+
+
+def test_work_units_of_a_matvec_by_slice_shape(tmp_path):
+    # 1024 a spectator where four and more strips run on the matrix cores, 768 elsewhere
+    out = run_host(r"""
+#include <cstdio>
+#include "runtime.hpp"
+int main() {
+  for (auto [ma, mb] : {std::pair{16, 16}, {48, 48}, {64, 64}, {50, 64}, {128, 128}, {129, 64}, {64, 129}, {256, 256}, {200, 1}})
+    std::printf("%d ", (int)rt::mv_target(ma, mb));
+}
+""", tmp_path)
+    assert out.split() == ["768", "768", "1024", "1024", "1024", "768", "768", "768", "768"], out
