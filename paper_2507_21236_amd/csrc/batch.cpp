@@ -603,7 +603,7 @@ void autotune(attn_batch* b) {
       }
     }
   }
-    hipEvent_t e0, e1;
+  hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
   const int nsteps = (int)b->steps.size();

@@ -232,8 +232,6 @@ void build_mv_dev(attn_handle* h, int n, std::vector<int64_t>& comb_off_out) {
   int64_t total = 0;
   build_comb(h, P.combines, h->d_mvcomb, D.comb, off, total);
   comb_off_out = off;
-  h->comb_blocks[n].clear();
-  for (size_t i = 0; i < P.combines.size(); i++) h->comb_blocks[n].push_back({off[i], P.combines[i].dim});
   int64_t part_used = 0;
   int nchs[3];
   int64_t target[3];
@@ -1500,7 +1498,6 @@ attn_status attn_build_tpo(const attn_problem* p, attn_handle** out) {
     h->d_st = (KrylovState*)dev_alloc(h, sizeof(KrylovState));
     // device plans
     h->mv.assign(nn, MVDev());
-    h->comb_blocks.assign(nn, {});
     h->env_up.assign(nn, EnvDev());
     h->env_down[0].assign(nn, EnvDev());
     h->env_down[1].assign(nn, EnvDev());

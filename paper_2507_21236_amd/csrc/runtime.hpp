@@ -396,7 +396,6 @@ struct attn_handle {
   void* comb_lp[2] = {nullptr, nullptr};
   int64_t mvcomb_elems = 0;
   std::vector<MVDev> mvlp[2];
-  std::vector<std::vector<std::pair<int64_t, int>>> comb_blocks;   // per node: (offset, dim)
   std::vector<EnvDev> env_up, env_down[2];
   std::vector<QRDev> qr[3];   // per leg, per node
   std::vector<ABDev> ab[3];   // absorb into node along leg

@@ -1164,7 +1164,7 @@ __global__ __launch_bounds__(256) void k_sandwich_w2(const SWTask* __restrict__ 
 // ============================================================================ mixed-shape launches
 // One launch over the work units of many tasks of different shapes (several
 // nodes of several problem instances): the kind of each unit selects the body.
-// Sandwich: wu.w = NB (legs multiples of 16, mb = 16 NB <= 64) or 0 (generic).
+// Sandwich: wu.w = NB (matrix cores, the tiles of mb <= 64) or 0 (generic).
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_batch_sandwich(const SWTask* __restrict__ tasks,
                                                         const SWItem* __restrict__ items,
