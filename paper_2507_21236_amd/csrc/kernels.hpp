@@ -52,15 +52,14 @@ struct MPJob {
 // (against four wavefronts at every leg: FP64 legs 40, 16.9 us before, 12.8 now;
 // FP32 legs 96, 98 and 82); legs of 96 take two each in three wavefronts, legs of
 // 128 two each for two column tiles (each A element then serves two products).
+// The same inside a sandwich launch (three row tiles in each of two wavefronts
+// at legs of 48: 4.42 ms a solve of the heaviest 8 x 8 node, 4.24 this way; legs of 36
+// and 40 equal within 1 %).
 struct ModeTile {
   int qs, ft, nw = 4;
 };
 constexpr ModeTile mode_tile(int NI) {
   return NI == 8 ? ModeTile{4, 2, 4} : NI == 6 ? ModeTile{3, 1, 3} : ModeTile{NI, 1, NI};
-}
-// within a sandwich launch (a workgroup of NI wavefronts there)
-constexpr ModeTile joint_mode_tile(int NI) {
-  return NI == 1 ? ModeTile{1, 1, 1} : NI == 2 ? ModeTile{2, 1, 2} : NI == 3 ? ModeTile{1, 1, 2} : ModeTile{4, 1, 4};
 }
 constexpr int mode_width(ModeTile m) { return 16 * m.ft * (m.nw / m.qs); }
 // LDS bytes of the staged tile (whole K steps of rows, two elements of padding)

@@ -338,7 +338,7 @@ void k_sandwich_mode(const SWTask* __restrict__ tasks, const SWItem* __restrict_
                      const MPJob* __restrict__ mjobs, const int2* __restrict__ mwus, int nmwu,
                      const T* __restrict__ xbase) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  constexpr ModeTile m = joint_mode_tile(NB);
+  constexpr ModeTile m = mode_tile(NB);
   constexpr int ny = 64 / mode_width(m);
   const int b = blockIdx.x;
   if (b < nmwu * ny) {
@@ -1403,7 +1403,7 @@ template <int NB>
 static hipError_t sand_mode_launch(int ma, int mb, const SWTask* tasks, const SWItem* items, const int4* wus, int nwu,
                                    int mj, const MPTask* mtasks, const MPJob* mjobs, const int2* mwus, int nmwu,
                                    const double* x, hipStream_t s) {
-  constexpr ModeTile m = joint_mode_tile(NB);
+  constexpr ModeTile m = mode_tile(NB);
   const size_t l0 = sw_mfma_lds(ma, 16 * NB, 8), l1 = mode_lds(mj, m, 8);
   const dim3 grid(nwu + nmwu * (64 / mode_width(m)));
   const int w = sw_strips(ma);
