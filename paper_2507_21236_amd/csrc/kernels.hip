@@ -344,13 +344,13 @@ __global__ __launch_bounds__(256) void k_combine(const CBTask* __restrict__ task
   ((double*)t.out)[e] = acc;
 }
 
-// Sum of the partial outputs of one entry by the S = (block size) / c threads that
-// share it (thread g c + i: group g of entry e0 + i of the block's c entries):
-// the total is returned in thread i < c.  part holds a value per thread.
-template <typename TI>
+// Sum of the partial outputs of one entry by the S = B / c threads of a block of B
+// that share it (thread g c + i: group g of entry e0 + i of the block's c entries):
+// the total is returned in thread i < c.  part holds B values.
+template <typename TI, int B>
 __device__ __forceinline__ double sum_split(const RDSrc* __restrict__ srcs, int nsrc, int c, int64_t e, int64_t et,
                                             bool on, double* part) {
-  const int S = blockDim.x / c, g = threadIdx.x / c;
+  const int S = B / c, g = threadIdx.x / c;
   double acc = on ? sum_sources<TI>(srcs, nsrc * g / S, nsrc * (g + 1) / S, e, et) : 0.0;
   if (S == 1) return acc;
   __syncthreads();
@@ -362,10 +362,10 @@ __device__ __forceinline__ double sum_split(const RDSrc* __restrict__ srcs, int 
 }
 
 // y = sum of the partial outputs, c entries per block
-template <typename TI, typename TO>
-__global__ __launch_bounds__(1024) void k_reduce_out(const RDSrc* __restrict__ srcs, int nsrc, int c,
+template <typename TI, typename TO, int B>
+__global__ __launch_bounds__(B) void k_reduce_out(const RDSrc* __restrict__ srcs, int nsrc, int c,
                                                      TO* __restrict__ y, int ml, int mr, int mp) {
-  __shared__ double part[1024];
+  __shared__ double part[B];
   const int64_t M = (int64_t)ml * mr * mp;
   const int64_t e = (int64_t)blockIdx.x * c + threadIdx.x % c;
   const bool on = e < M;
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(1024) void k_reduce_out(const RDSrc* __restrict__ s
   const int64_t rem = e - l * mr * mp;
   const int64_t r = rem / mp, p = rem - r * mp;
   const int64_t et = p * ml * mr + l * mr + r;
-  const double acc = sum_split<TI>(srcs, nsrc, c, e, et, on, part);
+  const double acc = sum_split<TI, B>(srcs, nsrc, c, e, et, on, part);
   if (on && (int)threadIdx.x < c) y[e] = (TO)acc;
 }
 
@@ -719,7 +719,7 @@ __device__ __forceinline__ void reduce_dots(const RDSrc* __restrict__ srcs, int 
     const int64_t l = e / ((int64_t)mr * mp);
     const int64_t rem = e - l * mr * mp;
     const int64_t r = rem / mp, p = rem - r * mp;
-    const double acc = sum_split<double>(srcs, nsrc, c, e, p * ml * mr + l * mr + r, e < M, part);
+    const double acc = sum_split<double, 1024>(srcs, nsrc, c, e, p * ml * mr + l * mr + r, e < M, part);
     __syncthreads();
     if ((int)threadIdx.x < c) {
       part[threadIdx.x] = acc;
@@ -2641,15 +2641,14 @@ hipError_t launch_reduce_out(int dtype_in, const RDSrc* srcs, int nsrc, void* y,
   // FP32 partials into an FP64 vector (the low-precision solves): one run per
   // entry, a thread each, in small blocks that spread over the chip (root of 8 x 8
   // m = 64, 4096 entries: an FP32 solve 1.43 ms in blocks of 1024, 1.28 in 256)
-  const bool run = dtype_in == 1 && dtype_out == 0;
-  const int c = run ? 256 : dot_chunk(M), block = run ? 256 : 1024;
+  const int c = dtype_in == 1 && dtype_out == 0 ? 256 : dot_chunk(M);
   const dim3 grid((unsigned)((M + c - 1) / c));
   if (dtype_in == 0 && dtype_out == 0)
-    hipLaunchKernelGGL((k_reduce_out<double, double>), grid, dim3(block), 0, s, srcs, nsrc, c, (double*)y, ml, mr, mp);
+    hipLaunchKernelGGL((k_reduce_out<double, double, 1024>), grid, dim3(1024), 0, s, srcs, nsrc, c, (double*)y, ml, mr, mp);
   else if (dtype_in == 1 && dtype_out == 0)
-    hipLaunchKernelGGL((k_reduce_out<float, double>), grid, dim3(block), 0, s, srcs, nsrc, c, (double*)y, ml, mr, mp);
+    hipLaunchKernelGGL((k_reduce_out<float, double, 256>), grid, dim3(256), 0, s, srcs, nsrc, c, (double*)y, ml, mr, mp);
   else if (dtype_in == 1 && dtype_out == 1)
-    hipLaunchKernelGGL((k_reduce_out<float, float>), grid, dim3(block), 0, s, srcs, nsrc, c, (float*)y, ml, mr, mp);
+    hipLaunchKernelGGL((k_reduce_out<float, float, 1024>), grid, dim3(1024), 0, s, srcs, nsrc, c, (float*)y, ml, mr, mp);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
