@@ -50,16 +50,16 @@ PEAKS = {"f64": 78.6, "f32": 157.3, "bf16x2": 2500.0 / 3}
 KERNELS = {"f64": "k_sandwich<double,4,true>", "f32": "k_sandwich_w2<float>",
            "bf16x2": "k_sandwich_bf2d<4,4>"}
 # HBM bytes per launch of the FP64 contraction kernel at legs of dimension 64,
-# averaged like the live timing over the 620 matvec launches of a sweep of
-# this workload (600 launches at the (64,64,64) nodes, of 3072 workgroups and up
-# to 1024 more of the last chain stage that shares the launch, 20 at the root):
+# averaged like the live timing over the 620 matvec launches of a timed sweep of
+# this workload (600 launches at the (64,64,64) nodes, of 3072 workgroups, 20 at
+# the root; a timed sweep runs the last chain stage in launches of its own):
 # rocprofv3 --pmc FETCH_SIZE (x 2) and WRITE_SIZE (x 1) on
 # `bench.py --traffic-probe`, the factors read off a plain 1 GiB device copy
 # (profiles/k_sandwich_f64_legs64_hbm_traffic.md).  The writes are the
 # kernel's partial outputs (one per item chunk, streaming stores); the reads
 # are X and the operator blocks.  Valid for the kernel as measured: None once
 # it changes.
-TRAFFIC_F64 = {"read": 85.1e6, "write": 113.4e6}
+TRAFFIC_F64 = {"read": 63.8e6, "write": 112.0e6}
 
 
 def host_info():
